@@ -204,12 +204,14 @@ hipError_t enqueue_score(const float *qh, const float *lh, const int32_t *plen, 
 // stream (the greedy pass, the carry) finds room on whichever XCD it is
 // dispatched to instead of waiting for the scan to drain.
 // rb_workspace_size covers both plans.
-rb_status plan(int B, int N, int d, rb_dtype dt, int k, rb::KnnPlan *p, bool overlap = false)
+// `limit`: bytes of scan maxima the workspace may hold.
+rb_status plan(int B, int N, int d, rb_dtype dt, int k, rb::KnnPlan *p, bool overlap = false,
+               size_t limit = rb::MAXIMA_LIMIT)
 {
     int cu = 0;
     if (num_cu(&cu) != 0)
         return RB_ERR_HIP;
-    if (rb::plan_knn(B, N, d, (int)dt, k, cu, p, overlap ? 1 : 0) != 0)
+    if (rb::plan_knn(B, N, d, (int)dt, k, cu, p, overlap ? 1 : 0, limit) != 0)
         return RB_ERR_DIMS;
     return RB_OK;
 }
@@ -222,7 +224,7 @@ rb_status route_batch(const void *queries, const void *bank, const float *bank_n
                       const rb_instances *inst, int I, rb_weights w, const rb_options *o,
                       int32_t *assign, float *chosen_score, int32_t *nbr_idx, float *nbr_dist,
                       float *q_hat, float *l_hat, float *score0, void *ws, size_t ws_bytes,
-                      void *stream)
+                      void *stream, size_t limit = rb::MAXIMA_LIMIT)
 {
     rb_status s = check_knn_dims(dtype, B, N, d, k);
     if (s != RB_OK)
@@ -242,7 +244,7 @@ rb_status route_batch(const void *queries, const void *bank, const float *bank_n
     if (!aligned(queries, 16) || !aligned(bank, 16))
         return RB_ERR_ALIGN;
     rb::KnnPlan p;
-    if ((s = plan(B, N, d, dtype, k, &p, (o->flags & RB_FLAG_OVERLAP) != 0)) != RB_OK)
+    if ((s = plan(B, N, d, dtype, k, &p, (o->flags & RB_FLAG_OVERLAP) != 0, limit)) != RB_OK)
         return s;
     const RouteExtra ex = route_extra(p.bytes, B, k, M);
     if (!ws || ws_bytes < ex.bytes)
@@ -518,8 +520,12 @@ rb_status rb_route_batch_noalloc(const void *queries, const void *bank, const fl
         return route_batch(queries, bank, bank_norms, dtype, B, N, d, k, bank_qual, bank_len, M,
                            prompt_len, inst, I, w, &k_default_opts, assign, chosen_score, nbr_idx,
                            nbr_dist, q_hat, l_hat, score0, nullptr, 0, stream);
+    // the maxima of a scan take what the static array has left: a large bank
+    // goes by in parts
+    const size_t rest = route_extra(0, B, k, M).bytes;
+    const size_t limit = rest < RB_SCRATCH_BYTES ? RB_SCRATCH_BYTES - rest : 0;
     rb::KnnPlan p;
-    if ((s = plan(B, N, d, dtype, k, &p)) != RB_OK)
+    if ((s = plan(B, N, d, dtype, k, &p, false, limit)) != RB_OK)
         return s;
     if (route_extra(p.bytes, B, k, M).bytes > (size_t)RB_SCRATCH_BYTES)
         return RB_ERR_SCRATCH;
@@ -528,7 +534,7 @@ rb_status rb_route_batch_noalloc(const void *queries, const void *bank, const fl
         return RB_ERR_HIP;
     return route_batch(queries, bank, bank_norms, dtype, B, N, d, k, bank_qual, bank_len, M,
                        prompt_len, inst, I, w, &k_default_opts, assign, chosen_score, nbr_idx,
-                       nbr_dist, q_hat, l_hat, score0, ws, RB_SCRATCH_BYTES, stream);
+                       nbr_dist, q_hat, l_hat, score0, ws, RB_SCRATCH_BYTES, stream, limit);
 }
 
 rb_status rb_profile_scan_events(void *begin, void *end)

@@ -52,6 +52,25 @@ constexpr int GM_KST = 64;
 constexpr int GM_SLOTS = 2;
 constexpr int GM_STAGE = 64;   // per-wave LDS staging of one macro tile's candidates
 
+// The LDS-resident scan: up to RES_WAVES waves per workgroup, each with
+// RES_RING k-steps of bank loads in flight; request tiles of up to RES_MAX_NG
+// groups of 16.
+constexpr int RES_WAVES = 8;
+constexpr int RES_RING = 8;
+constexpr int RES_MAX_NG = 8;
+// The selection: one workgroup of SEL_THREADS threads per request; up to
+// SEL_CAP super tiles or rows held in LDS at once; SEL_ROUND row tiles
+// recomputed per round.
+constexpr int SEL_THREADS = 512;
+constexpr int SEL_CAP = 2048;
+constexpr int SEL_ROUND = 64;
+constexpr int SEL_MAX_EPS = 16;            // row tiles per super tile, at most
+constexpr int SEL_MAX_ROW_BYTES = 8192;    // of one embedding (RB_MAX_D fp32)
+constexpr long SEL_WANT_SUP = 16384;       // super tiles per request worth reading one by one
+// Bytes of maxima a call's workspace takes at most: a bank that would leave
+// more goes by in parts, each with its own scan and selection.
+constexpr size_t MAXIMA_LIMIT = (size_t)1 << 30;
+
 // How one rb_knn_topk call is split (the tile scan; the query-resident scan
 // differs in that one workgroup holds the whole batch, so n_qt = 1; the
 // GEMM-structured scan in its request tiles of GM_QRY, one workgroup per
@@ -69,7 +88,8 @@ constexpr int GM_STAGE = 64;   // per-wave LDS staging of one macro tile's candi
 //  * merge: per query, the k smallest of its W lists (W = n_chunks, times
 //    the row halves rs of the query-resident scan).
 struct KnnPlan {
-    int kind;           // 0 tile scan, 1 query-resident scan, 2 GEMM-structured scan
+    int kind;           // 0 tile scan, 1 query-resident scan, 2 GEMM-structured scan,
+                        // 3 LDS-resident scan
     int qw, rs, spb;    // query-resident scan: query groups per wave, row halves, stages per block,
     int stages;         //   ring slots
     int dtype;          // 0 fp32, 1 bf16
@@ -83,11 +103,20 @@ struct KnnPlan {
     int grid;           // scan workgroups
     int ovf_cap;        // candidates per scan wave that the workspace takes past LDS
     size_t lds_bytes;
-    size_t off_tau, off_qn, off_gmin, off_ccnt, off_ckey, off_cidx, off_ovf, bytes;
+    size_t off_tau, off_qn, off_gmin, off_ccnt, off_ckey, off_cidx, off_ovf;
+    // scans that leave maxima: the bank in n_seg parts of seg_rows rows, per
+    // part n_sup super tiles of eps row tiles per request
+    int n_seg, eps, wg_waves;
+    long seg_rows, n_sup;
+    size_t off_sup, off_ent, off_lkey, off_lidx;
+    size_t bytes;       // of the workspace
 };
 
 // reserve: compute units per XCD to leave free for kernels of other streams.
-int plan_knn(int B, int N, int d, int dtype, int k, int num_cu, KnnPlan *p, int reserve = 0);
+// limit: bytes the maxima may take (they are cut to it by taking the bank in
+// parts).
+int plan_knn(int B, int N, int d, int dtype, int k, int num_cu, KnnPlan *p, int reserve = 0,
+             size_t limit = MAXIMA_LIMIT);
 
 // Events recorded around the bank-scan kernel when set (per host thread).
 void set_scan_events(hipEvent_t begin, hipEvent_t end);

@@ -317,53 +317,6 @@ struct MergeArgs {
     bool inv_dist;
 };
 
-// Weight of a neighbour at squared distance d2 in the distance-weighted
-// average: the inverse of its Euclidean distance, finite at distance 0 (a
-// negative d2 from fp32 cancellation counts as 0).
-__device__ __forceinline__ float inv_dist_weight(float d2)
-{
-    return 1.f / (sqrtf(fmaxf(d2, 0.f)) + 1e-6f);
-}
-
-// The label gather and average: sum over neighbours j = 0..k-1 in order,
-// divided by k, or (wts non-null) weighted by wts[j] and divided by the sum
-// of the weights. A neighbour index outside [0, N) makes both averages NaN
-// instead of reading out of bounds (the check does not end the loop, so the
-// k loads can all be in flight together).
-__device__ __forceinline__ void average_labels(const int32_t *nbr, const float *wts, int k,
-                                               const float *qual, const float *len, int N, int M,
-                                               int m, float *q_out, float *l_out)
-{
-    float sq = 0.f, sl = 0.f, sw = 0.f;
-    bool bad = false;
-    if (wts) {
-#pragma unroll 8
-        for (int j = 0; j < k; ++j) {
-            const int32_t n = nbr[j];
-            const bool ok = n >= 0 && n < N;
-            bad |= !ok;
-            const size_t o = (size_t)(ok ? n : 0) * M + m;
-            const float w = wts[j];
-            sq = fmaf(w, qual[o], sq);
-            sl = fmaf(w, len[o], sl);
-            sw += w;
-        }
-    } else {
-#pragma unroll 8
-        for (int j = 0; j < k; ++j) {
-            const int32_t n = nbr[j];
-            const bool ok = n >= 0 && n < N;
-            bad |= !ok;
-            const size_t o = (size_t)(ok ? n : 0) * M + m;
-            sq += qual[o];
-            sl += len[o];
-        }
-        sw = (float)k;
-    }
-    *q_out = bad ? __builtin_nanf("") : sq / sw;
-    *l_out = bad ? __builtin_nanf("") : sl / sw;
-}
-
 // One wave per query (MERGE_WAVES queries per workgroup, no workgroup
 // barrier): the wave's lanes take the lists w = lane + 64*u, a wave prefix
 // sum places their entries as packed (key << 32 | index) values in LDS, then
@@ -565,7 +518,78 @@ void set_scan_events(hipEvent_t begin, hipEvent_t end)
     t_scan_end = end;
 }
 
-int plan_knn(int B, int N, int d, int dtype, int k, int num_cu, KnnPlan *p, int reserve)
+namespace {
+
+// The LDS-resident scan's split of `rows` bank rows, and the workspace.
+// Request tiles: as many groups of 16 requests as fit LDS for every k-step,
+// at most RES_MAX_NG, evenly over the tiles. Waves: eight per compute unit's
+// workgroup, fewer when there are not enough super tiles to go round (a bank
+// of 2,048 rows is 128 row tiles: one wave on each of 128 compute units).
+void plan_res(KnnPlan *p, int num_cu, int reserve, size_t limit)
+{
+    const int B = p->B;
+    const long rowb = (long)p->d * (p->dtype == 1 ? 2 : 4);
+    const int groups = B > 0 ? (B + 15) / 16 : 1;
+    int ng = (int)(LDS_LIMIT / ((size_t)p->nks * WAVE * 16));
+    if (ng > RES_MAX_NG)
+        ng = RES_MAX_NG;
+    p->n_qt = (groups + ng - 1) / ng;
+    p->ng = (groups + p->n_qt - 1) / p->n_qt;
+    p->lds_bytes = (size_t)p->nks * p->ng * WAVE * 16;
+    // super tiles: single row tiles up to SEL_WANT_SUP of them
+    const long all_tiles = ((long)p->N + 15) / 16;
+    p->eps = 1;
+    while (p->eps < SEL_MAX_EPS && all_tiles > SEL_WANT_SUP * p->eps)
+        p->eps *= 2;
+    // the bank in equal parts whose maxima stay within the limit
+    const size_t lists = 2 * align256((size_t)B * p->k * 4) + 4 * 256;
+    const size_t per_sup = (size_t)(B > 0 ? B : 1) * 4 * (p->eps > 1 ? 1 + p->eps : 1);
+    const long all_sup = (all_tiles + p->eps - 1) / p->eps;
+    long fit = limit > lists ? (long)((limit - lists) / per_sup) : 0;
+    if (fit < 1)
+        fit = 1;
+    p->n_seg = (int)((all_sup + fit - 1) / fit);
+    p->n_sup = (all_sup + p->n_seg - 1) / p->n_seg;
+    p->seg_rows = p->n_sup * p->eps * 16;
+    // one workgroup per compute unit; with `reserve`, that many units of each
+    // XCD stay free (workgroups go to the XCDs round robin and the tiles of a
+    // chunk share one)
+    long chunks = num_cu / p->n_qt;
+    if (reserve > 0) {
+        const long per_xcd = (num_cu / 8 - reserve) / p->n_qt;
+        if (per_xcd >= 1)
+            chunks = per_xcd * 8;
+    }
+    if (chunks < 1)
+        chunks = 1;
+    long waves = (p->n_sup + chunks - 1) / chunks;
+    if (waves > RES_WAVES)
+        waves = RES_WAVES;
+    p->wg_waves = (int)waves;
+    if (chunks > (p->n_sup + waves - 1) / waves)
+        chunks = (p->n_sup + waves - 1) / waves;
+    // a wave's share is addressed with 32-bit offsets
+    while ((p->n_sup / (chunks * waves) + 1) * p->eps * 16 * rowb >= (1L << 31) - (1L << 20))
+        chunks *= 2;
+    p->n_chunks = (int)chunks;
+    p->grid = ((p->n_chunks + 7) / 8) * 8 * p->n_qt;
+    size_t off = 0;
+    p->off_sup = off;
+    off += align256((size_t)B * p->n_sup * 4);
+    p->off_ent = off;
+    off += p->eps > 1 ? align256((size_t)B * p->n_sup * p->eps * 4) : 0;
+    p->off_lkey = off;
+    off += align256((size_t)B * p->k * 4);
+    p->off_lidx = off;
+    off += align256((size_t)B * p->k * 4);
+    if (off > p->bytes)
+        p->bytes = off;
+}
+
+}  // namespace
+
+int plan_knn(int B, int N, int d, int dtype, int k, int num_cu, KnnPlan *p, int reserve,
+             size_t limit)
 {
     const int vec = dtype == 1 ? 8 : 4;
     p->dtype = dtype;
@@ -773,6 +797,12 @@ int plan_knn(int B, int N, int d, int dtype, int k, int num_cu, KnnPlan *p, int 
     p->off_ovf = off;
     off += align256((size_t)p->grid * waves_per_wg * 3 * (p->ovf_cap > 0 ? p->ovf_cap : 1) * 4);
     p->bytes = off;
+    // The LDS-resident scan takes every fp32 batch, and bf16 batches of at
+    // most 64 requests that the query-resident scan leaves.
+    if (p->kind == 0 && (dtype == 0 || B <= 64)) {
+        p->kind = 3;
+        plan_res(p, num_cu, reserve, limit);
+    }
     return 0;
 }
 
@@ -805,6 +835,75 @@ hipError_t launch_knn(const KnnPlan &p, const void *queries, const void *bank,
     uint32_t *ckey = (uint32_t *)(w + p.off_ckey);
     int32_t *cidx = (int32_t *)(w + p.off_cidx);
     hipError_t e;
+    const bool timed = t_scan_begin && t_scan_end;
+
+    if (p.kind == 3) {
+        SelectArgs sa;
+        sa.queries = (const uint8_t *)queries;
+        sa.bank = (const uint8_t *)bank;
+        sa.bank_norms = bank_norms;
+        sa.B = p.B;
+        sa.d = p.d;
+        sa.nks = p.nks;
+        sa.k = p.k;
+        sa.eps = p.eps;
+        sa.n_sup = p.n_sup;
+        sa.sup = (const float *)(w + p.off_sup);
+        sa.ent = (const float *)(w + p.off_ent);
+        sa.list_key = (uint32_t *)(w + p.off_lkey);
+        sa.list_idx = (int32_t *)(w + p.off_lidx);
+        sa.qual = bank_qual;
+        sa.len = bank_len;
+        sa.N = p.N;
+        sa.M = M;
+        sa.inv_dist = inv_dist;
+        const bool merge = (phases & KNN_MERGE) != 0;
+        if (!(phases & KNN_LISTS)) {
+            sa.nbr_idx = nbr_idx;
+            sa.nbr_dist = nbr_dist;
+            sa.q_hat = q_hat;
+            sa.l_hat = l_hat;
+            return launch_from_list(sa, s);
+        }
+        MinScanArgs a;
+        a.queries = sa.queries;
+        a.bank = sa.bank;
+        a.bank_norms = bank_norms;
+        a.B = p.B;
+        a.d = p.d;
+        a.nks = p.nks;
+        a.n_chunks = p.n_chunks;
+        a.n_qt = p.n_qt;
+        a.eps = p.eps;
+        a.sup = (float *)(w + p.off_sup);
+        a.ent = (float *)(w + p.off_ent);
+        for (int seg = 0; seg < p.n_seg; ++seg) {
+            const bool last = seg == p.n_seg - 1;
+            a.row0 = seg * p.seg_rows;
+            a.rows = last ? p.N - a.row0 : p.seg_rows;
+            a.n_tiles = (a.rows + 15) / 16;
+            a.n_sup = (a.n_tiles + p.eps - 1) / p.eps;
+            if (timed && seg == 0 && (e = hipEventRecord(t_scan_begin, s)) != hipSuccess)
+                return e;
+            e = p.dtype == 1 ? launch_scan_res_bf16(p, a, s) : launch_scan_res_f32(p, a, s);
+            if (e != hipSuccess)
+                return e;
+            if (timed && last && (e = hipEventRecord(t_scan_end, s)) != hipSuccess)
+                return e;
+            sa.row0 = a.row0;
+            sa.rows = a.rows;
+            sa.n_sup = a.n_sup;
+            sa.carry_in = seg > 0;
+            const bool out = last && merge;
+            sa.nbr_idx = out ? nbr_idx : nullptr;
+            sa.nbr_dist = out ? nbr_dist : nullptr;
+            sa.q_hat = out ? q_hat : nullptr;
+            sa.l_hat = out ? l_hat : nullptr;
+            if ((e = launch_select(p.dtype, sa, s)) != hipSuccess)
+                return e;
+        }
+        return hipSuccess;
+    }
 
     if (phases & KNN_LISTS) {
         if (p.S > 0) {
@@ -867,7 +966,6 @@ hipError_t launch_knn(const KnnPlan &p, const void *queries, const void *bank,
         a.cidx = cidx;
         a.ovf = (uint32_t *)(w + p.off_ovf);
         a.ovf_cap = p.ovf_cap;
-        const bool timed = t_scan_begin && t_scan_end;
         if (timed && (e = hipEventRecord(t_scan_begin, s)) != hipSuccess)
             return e;
         const bool ragged = p.d % (p.dtype == 1 ? 32 : 16) != 0;

@@ -23,6 +23,42 @@ struct ScanArgs {
     int ovf_cap;      // 16*RT*16*NG - STAGE_CAP (every (row, query) pair of an iteration)
 };
 
+// A scan that leaves maxima (MinScanArgs) writes, per request and 16-row tile
+// of the bank, the largest <q, x> - |x|^2/2 of the tile's rows (the nearest
+// row's distance is |q|^2 - 2 times that), and the maximum over every eps
+// consecutive such entries (a super tile). Entries past the bank hold NaN.
+struct MinScanArgs {
+    const uint8_t *queries, *bank;
+    const float *bank_norms;
+    int B, d, nks, n_chunks, n_qt;
+    long row0, rows;      // bank rows [row0, row0 + rows) of this launch
+    long n_tiles, n_sup;  // their 16-row tiles; super tiles per request
+    int eps;
+    float *sup;           // [B][n_sup]
+    float *ent;           // [B][n_sup][eps]; unused when eps is 1
+};
+
+// The selection from those maxima.
+struct SelectArgs {
+    const uint8_t *queries, *bank;
+    const float *bank_norms;
+    int B, d, nks, k, eps;
+    long row0, rows, n_sup;
+    const float *sup, *ent;
+    uint32_t *list_key;   // [B][k] neighbours as distance keys and indices, in and out
+    int32_t *list_idx;    //   (null: not kept)
+    bool carry_in;        // the lists hold the neighbours of earlier parts of the bank
+    int32_t *nbr_idx;     // results, null in all but the last part
+    float *nbr_dist;
+    const float *qual, *len;
+    int N, M;
+    float *q_hat, *l_hat;
+    bool inv_dist;
+};
+
+hipError_t launch_select(int dtype, const SelectArgs &a, hipStream_t s);
+hipError_t launch_from_list(const SelectArgs &a, hipStream_t s);
+
 // Byte offsets of the scan's LDS regions for a tile of ng query groups of
 // which the first gr are resident for the whole kernel, with a ring of
 // `slots` k-steps for the others.
@@ -119,6 +155,8 @@ __host__ __device__ inline GemmLayout gemm_layout(int k)
 // The bank-scan launchers, one translation unit per element type and
 // k-step raggedness (they are the bulk of the compile time), and one per row
 // length for the query-resident scan.
+hipError_t launch_scan_res_bf16(const KnnPlan &p, const MinScanArgs &a, hipStream_t s);
+hipError_t launch_scan_res_f32(const KnnPlan &p, const MinScanArgs &a, hipStream_t s);
 hipError_t launch_scan_gemm(const KnnPlan &p, const ScanArgs &a, hipStream_t s);
 hipError_t launch_scan_rq(const KnnPlan &p, const ScanArgs &a, hipStream_t s);
 hipError_t launch_scan_rq12(const KnnPlan &p, const ScanArgs &a, hipStream_t s);
@@ -179,6 +217,26 @@ __device__ __forceinline__ f32x4 mfma_step(const i32x4 &a, const i32x4 &b, const
                                                      0, 0, 0);
         return d;
     }
+}
+
+__device__ __forceinline__ float max4(const f32x4 &v)
+{
+    return fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));
+}
+
+// Maxima of four registers over the wave's four rows of 16 lanes, column by
+// column: lane row r of the result holds the maximum of argument
+// (r with its two bits swapped) in that column.
+__device__ __forceinline__ float rows_max4(float m0, float m1, float m2, float m3)
+{
+    auto swap32 = [](float a, float b) {
+        const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b),
+                                                        false, false);
+        return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+    };
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(swap32(m0, m1)),
+                                                    __float_as_uint(swap32(m2, m3)), false, false);
+    return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
 }
 
 __device__ __forceinline__ i32x4 load16(const uint8_t *p) { return *(const i32x4 *)p; }
@@ -278,6 +336,53 @@ __device__ __forceinline__ bool lds_cas64(uint64_t *p, uint64_t expect, uint64_t
 __device__ __forceinline__ uint64_t lds_load64(const uint64_t *p)
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Weight of a neighbour at squared distance d2 in the distance-weighted
+// average: the inverse of its Euclidean distance, finite at distance 0 (a
+// negative d2 from fp32 cancellation counts as 0).
+__device__ __forceinline__ float inv_dist_weight(float d2)
+{
+    return 1.f / (sqrtf(fmaxf(d2, 0.f)) + 1e-6f);
+}
+
+// The label gather and average: sum over neighbours j = 0..k-1 in order,
+// divided by k, or (wts non-null) weighted by wts[j] and divided by the sum
+// of the weights. A neighbour index outside [0, N) makes both averages NaN
+// instead of reading out of bounds (the check does not end the loop, so the
+// k loads can all be in flight together).
+__device__ __forceinline__ void average_labels(const int32_t *nbr, const float *wts, int k,
+                                               const float *qual, const float *len, int N, int M,
+                                               int m, float *q_out, float *l_out)
+{
+    float sq = 0.f, sl = 0.f, sw = 0.f;
+    bool bad = false;
+    if (wts) {
+#pragma unroll 8
+        for (int j = 0; j < k; ++j) {
+            const int32_t n = nbr[j];
+            const bool ok = n >= 0 && n < N;
+            bad |= !ok;
+            const size_t o = (size_t)(ok ? n : 0) * M + m;
+            const float w = wts[j];
+            sq = fmaf(w, qual[o], sq);
+            sl = fmaf(w, len[o], sl);
+            sw += w;
+        }
+    } else {
+#pragma unroll 8
+        for (int j = 0; j < k; ++j) {
+            const int32_t n = nbr[j];
+            const bool ok = n >= 0 && n < N;
+            bad |= !ok;
+            const size_t o = (size_t)(ok ? n : 0) * M + m;
+            sq += qual[o];
+            sl += len[o];
+        }
+        sw = (float)k;
+    }
+    *q_out = bad ? __builtin_nanf("") : sq / sw;
+    *l_out = bad ? __builtin_nanf("") : sl / sw;
 }
 
 // Inclusive prefix sum over the wave.

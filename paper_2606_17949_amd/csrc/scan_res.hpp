@@ -1,0 +1,225 @@
+// The bank scan of the exact k-nearest-neighbour search (RouteBalance Sec. 4.2:
+// the KNN lookup of Alg. 1) for request tiles that stay in LDS: fp32 banks,
+// and bf16 batches of at most 64 requests over rows or banks the
+// query-resident scan does not take.
+#pragma once
+
+#include "knn_common.hpp"
+
+namespace rb {
+
+namespace {
+
+// What bounds it: fp32 batches of some tens of requests the fp32 MFMA rate
+// (64 flop per cycle and SIMD), small batches the bank stream, small banks
+// the latency of one row tile's loads. So the request tile (NG groups of 16,
+// every k-step) is loaded into LDS once per workgroup and then only read; a
+// wave takes 16-row tiles of its own contiguous share of the bank, which come
+// from HBM straight into MFMA operand registers, RES_RING k-steps ahead
+// across tile ends, and no wave waits for another after the request tile has
+// landed. A row tile leaves one value per request, the largest
+// <q, x> - |x|^2/2 of its 16 rows; eps consecutive tiles (a super tile, all
+// one wave's) one more. There is no bound, no list and no candidate test: the
+// selection takes the k best super tiles and recomputes the few row tiles
+// that matter.
+template <int DT, int NG>
+__global__ __launch_bounds__(RES_WAVES * WAVE, 1) void res_scan_kernel(const MinScanArgs A)
+{
+    constexpr int VEC = Elem<DT>::VEC, ESZ = Elem<DT>::ESZ;
+    constexpr int KS = 4 * VEC;              // elements of one k-step
+    constexpr int R = RES_RING;
+    constexpr int NQ = (NG + 3) / 4;         // result registers: four groups each
+    constexpr int NB = NG < 4 ? NG : 4;      // request fragments in flight
+    extern __shared__ __align__(16) uint8_t smem[];
+    i32x4 *qs = (i32x4 *)smem;               // [nks][NG][64] request fragments
+
+    // Workgroup -> (chunk c, request tile t): workgroups go to the XCDs round
+    // robin, so this map puts the request tiles of one chunk on one XCD.
+    const int per8 = 8 * A.n_qt;
+    const int rem = blockIdx.x % per8;
+    const int t = rem / 8;
+    const int c = (blockIdx.x / per8) * 8 + rem % 8;
+    if (c >= A.n_chunks)
+        return;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int n_waves = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 15, jg = lane >> 4;
+    const int q0 = t * NG * 16;
+    const int nks = A.nks;
+    const uint32_t rowb = (uint32_t)A.d * ESZ;
+
+    // this wave's super tiles [s0, s1), its row tiles [t0, t1)
+    const long gw = (long)c * n_waves + wave, n_gw = (long)A.n_chunks * n_waves;
+    const long s0 = gw * A.n_sup / n_gw, s1 = (gw + 1) * A.n_sup / n_gw;
+    const long t0 = s0 * A.eps;
+    const int n_tiles = (int)(min(s1 * A.eps, A.n_tiles) - t0);
+    const int nrows = (int)(min(A.rows, (t0 + n_tiles) * 16) - t0 * 16);   // of the share
+
+    // bank fragments: k-step ls of the share's tile lt into registers; rows
+    // past the bank fall outside the resource and load zero, and so do the
+    // lanes past the row in its last k-step
+    const __amdgpu_buffer_rsrc_t rbk = make_rsrc(A.bank + (size_t)(A.row0 + t0 * 16) * rowb,
+                                                 n_tiles > 0 ? (uint32_t)nrows * rowb : 0u);
+    const __amdgpu_buffer_rsrc_t rnm =
+        make_rsrc(A.bank_norms + A.row0 + t0 * 16, n_tiles > 0 ? (uint32_t)nrows * 4u : 0u);
+    const bool tail_ok = (nks - 1) * KS + jg * VEC < A.d;
+    uint32_t lvo = (uint32_t)col * rowb + jg * 16;   // tile lt, k-step ls
+    int ls = 0;
+    auto issue = [&](i32x4 &a) {
+        a = buffer_load16(rbk, ls == nks - 1 && !tail_ok ? OFF_NONE : lvo);
+        lvo += KSTEP_BYTES;
+        if (++ls == nks) {
+            ls = 0;
+            lvo += 16 * rowb - (uint32_t)nks * KSTEP_BYTES;
+        }
+    };
+    i32x4 ring[R];
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+        issue(ring[u]);
+    auto load_norms = [&](int tile) -> f32x4 {
+        return __builtin_bit_cast(f32x4, buffer_load16(rnm, (uint32_t)(tile * 16 + jg * 4) * 4u));
+    };
+    f32x4 xn = load_norms(0);
+
+    // the request tile (zero past the batch and past the row)
+    for (int item = tid; item < nks * NG * WAVE; item += blockDim.x) {
+        const int s = item / (NG * WAVE), g = (item / WAVE) % NG, l = item % WAVE;
+        const int q = q0 + g * 16 + (l & 15);
+        const i32x4 z = {0, 0, 0, 0};
+        qs[item] = q < A.B && s * KS + (l >> 4) * VEC < A.d
+                       ? load16(A.queries + (size_t)q * rowb + s * KSTEP_BYTES + (l >> 4) * 16)
+                       : z;
+    }
+    __syncthreads();
+
+    // where this lane's results go: lane row r of result register v holds
+    // group 4*v + (r with its two bits swapped), request col
+    const int gsw = (jg >> 1) | ((jg & 1) << 1);
+    float *sup[NQ], *ent[NQ];
+    bool own[NQ];
+#pragma unroll
+    for (int v = 0; v < NQ; ++v) {
+        const int g = 4 * v + gsw, q = q0 + g * 16 + col;
+        own[v] = g < NG && q < A.B;
+        sup[v] = A.sup + (size_t)(own[v] ? q : 0) * A.n_sup + s0;
+        ent[v] = A.ent + ((size_t)(own[v] ? q : 0) * A.n_sup + s0) * A.eps;
+    }
+
+    f32x4 acc[NG];
+    float smax[NQ];
+#pragma unroll
+    for (int v = 0; v < NQ; ++v)
+        smax[v] = __builtin_nanf("");
+    int tile = 0, s = 0, es = 0;   // tile of the share, its k-step, its place in the super tile
+    auto start_tile = [&]() {
+        // the accumulators start from -|x|^2/2 of their rows (-inf past the bank)
+        f32x4 h;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            h[e] = tile * 16 + jg * 4 + e < nrows ? -0.5f * xn[e] : -INFINITY;
+#pragma unroll
+        for (int g = 0; g < NG; ++g)
+            acc[g] = h;
+        xn = load_norms(tile + 1);
+    };
+    auto end_tile = [&]() {
+        float m[4 * NQ];
+#pragma unroll
+        for (int g = 0; g < 4 * NQ; ++g)
+            m[g] = g < NG ? max4(acc[g < NG ? g : 0]) : -INFINITY;
+        const bool last = es == A.eps - 1 || tile == n_tiles - 1;
+#pragma unroll
+        for (int v = 0; v < NQ; ++v) {
+            const float r = rows_max4(m[4 * v], m[4 * v + 1], m[4 * v + 2], m[4 * v + 3]);
+            if (A.eps > 1) {
+                smax[v] = fmaxf(smax[v], r);
+                if (own[v])
+                    ent[v][tile] = r;
+                if (last) {
+                    if (own[v])
+                        *sup[v] = smax[v];
+                    smax[v] = __builtin_nanf("");
+                }
+            } else if (own[v]) {
+                *sup[v] = r;
+            }
+            if (last)
+                ++sup[v];
+        }
+        es = last ? 0 : es + 1;
+        s = 0;
+        ++tile;
+    };
+    if (n_tiles > 0)
+        start_tile();
+    // One position per (tile, k-step), in order; position x sits in ring slot
+    // x % R and, once used, makes room for position x + R.
+    const long n_pos = (long)n_tiles * nks;
+    for (long x = 0; x < n_pos; x += R) {
+        static_for<0, R>([&](auto U) {
+            constexpr int u = decltype(U)::value;
+            if (x + u >= n_pos)
+                return;
+            const i32x4 *fr = qs + s * NG * WAVE + lane;
+            i32x4 bq[NB];
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+                bq[j] = fr[j * WAVE];
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                acc[g] = mfma_step<DT>(ring[u], bq[g % NB], acc[g]);
+                if (g + NB < NG)
+                    bq[g % NB] = fr[(g + NB) * WAVE];
+            }
+            issue(ring[u]);
+            if (++s == nks) {
+                end_tile();
+                if (tile < n_tiles)
+                    start_tile();
+            }
+        });
+    }
+    // entries of the last super tile past the bank
+    if (A.eps > 1 && s1 > s0 && s1 * A.eps > t0 + n_tiles) {
+#pragma unroll
+        for (int v = 0; v < NQ; ++v)
+            if (own[v])
+                for (long e = n_tiles; e < s1 * A.eps - t0; ++e)
+                    ent[v][e] = __builtin_nanf("");
+    }
+}
+
+template <int DT, int NG>
+hipError_t launch_res_scan(const KnnPlan &p, const MinScanArgs &a, hipStream_t s)
+{
+    auto kern = res_scan_kernel<DT, NG>;
+    hipError_t e = hipFuncSetAttribute((const void *)kern,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)p.lds_bytes);
+    if (e != hipSuccess)
+        return e;
+    hipLaunchKernelGGL(kern, dim3(p.grid), dim3(p.wg_waves * WAVE), p.lds_bytes, s, a);
+    return hipGetLastError();
+}
+
+template <int DT>
+hipError_t launch_res(const KnnPlan &p, const MinScanArgs &a, hipStream_t s)
+{
+    switch (p.ng) {
+    case 1: return launch_res_scan<DT, 1>(p, a, s);
+    case 2: return launch_res_scan<DT, 2>(p, a, s);
+    case 3: return launch_res_scan<DT, 3>(p, a, s);
+    case 4: return launch_res_scan<DT, 4>(p, a, s);
+    case 5: return launch_res_scan<DT, 5>(p, a, s);
+    case 6: return launch_res_scan<DT, 6>(p, a, s);
+    case 7: return launch_res_scan<DT, 7>(p, a, s);
+    case 8: return launch_res_scan<DT, 8>(p, a, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+}  // namespace rb

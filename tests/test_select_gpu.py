@@ -1,0 +1,119 @@
+"""Scans that leave maxima, and the selection from them, at the edges of their
+tiles (GPU).
+
+Embeddings are small integers, so every product, sum and distance is exact in
+fp32 and bf16 and many rows are equally far: the reference is an integer
+computation sorted by (distance, index), and the neighbours must match it
+exactly, ties included.
+"""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda"
+
+
+def draw(B, N, d, dtype, lo, hi, seed):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    bank = torch.randint(lo, hi + 1, (N, d), generator=g, device=DEV).to(t)
+    q = torch.randint(lo, hi + 1, (B, d), generator=g, device=DEV).to(t)
+    return q, bank
+
+
+def reference(q, bank, k):
+    """(index, distance) of the k first rows by (distance, index); chunks of the
+    bank in float64 (exact for these integers)."""
+    q = q.double()
+    keys = []
+    for r0 in range(0, bank.shape[0], 1 << 18):
+        x = bank[r0:r0 + (1 << 18)].double()
+        dist = (q * q).sum(1)[:, None] + (x * x).sum(1)[None] - 2 * (q @ x.t().contiguous())
+        key = dist * float(1 << 32) + torch.arange(r0, r0 + x.shape[0], device=DEV)
+        keys.append(torch.topk(key, min(k, x.shape[0]), dim=1, largest=False).values)
+    key = torch.topk(torch.cat(keys, 1), k, dim=1, largest=False).values.sort(dim=1).values
+    dist = torch.floor(key / float(1 << 32))
+    return (key - dist * float(1 << 32)).to(torch.int32), dist.float()
+
+
+def check(q, bank, k, label):
+    import paper_2606_17949_amd as rb
+    print(label, flush=True)
+    idx, dist = rb.rb_knn_topk(q, bank, rb.rb_bank_norms(bank), k)
+    torch.cuda.synchronize()
+    ref_idx, ref_dist = reference(q, bank, k)
+    assert torch.equal(dist, ref_dist), label
+    assert torch.equal(idx, ref_idx), label
+
+
+@pytest.mark.parametrize("dtype,B,N,d,k", [
+    ("f32", 1, 1, 4, 1),              # one row, one k-step, one lane group
+    ("f32", 1, 17, 8, 17),            # fewer super tiles than neighbours
+    ("f32", 17, 2_047, 20, 10),       # second request group nearly empty, ragged row
+    ("f32", 100, 5_003, 300, 20),     # seven groups, rows of 18.75 k-steps
+    ("f32", 130, 40_001, 12, 64),     # two request tiles, k at its maximum
+    ("f32", 33, 300_017, 16, 10),     # super tiles of two row tiles, the last partial
+    ("f32", 3, 70, 2_048, 5),         # the longest rows
+    ("bf16", 1, 1_000, 8, 10),
+    ("bf16", 64, 100_003, 64, 10),
+    ("bf16", 49, 33_333, 1_000, 7),   # ragged bf16 rows, four groups
+    ("bf16", 64, 4_100, 1_536, 10),   # two request tiles of two groups
+])
+def test_neighbours_are_exact(dtype, B, N, d, k):
+    q, bank = draw(B, N, d, dtype, -2, 2, 1)
+    check(q, bank, k, f"exact {dtype} B={B} N={N} d={d} k={k}")
+
+
+@pytest.mark.parametrize("dtype,B,d", [("f32", 5, 16), ("bf16", 5, 64)])
+def test_equal_rows_come_in_index_order(dtype, B, d):
+    """Every row equal: more equal super tiles than the selection holds, and
+    the first k rows win."""
+    q, bank = draw(B, 40_000, d, dtype, -2, 2, 2)
+    bank[:] = bank[0]
+    check(q, bank, 10, f"equal rows {dtype}")
+    bank[39_000] = q[0]   # and one nearer row
+    check(q, bank, 64, f"equal rows but one {dtype}")
+
+
+def test_rows_that_are_no_numbers_are_no_neighbours():
+    """Fewer rows with a distance than neighbours: index -1, distance NaN."""
+    import paper_2606_17949_amd as rb
+    q, bank = draw(2, 40, 16, "f32", -2, 2, 3)
+    norms = rb.rb_bank_norms(bank)
+    norms[7:] = float("nan")
+    print("rows without a distance", flush=True)
+    idx, dist = rb.rb_knn_topk(q, bank, norms, 10)
+    torch.cuda.synchronize()
+    assert torch.all(idx[:, 7:] == -1) and torch.all(torch.isnan(dist[:, 7:]))
+    assert torch.equal(idx[:, :7].sort(1).values.cpu(),
+                       torch.arange(7, dtype=torch.int32).repeat(2, 1))
+
+
+def test_bank_in_parts_matches_one_pass():
+    """The no-allocation call holds the maxima of 64 MiB; a longer bank goes by
+    in parts whose neighbours are merged, with the results of one pass."""
+    import paper_2606_17949_amd as rb
+    B, N, d, k, M, I = 64, 4_200_005, 8, 10, 2, 3
+    q, bank = draw(B, N, d, "f32", -3, 3, 4)
+    norms = rb.rb_bank_norms(bank)
+    g = torch.Generator(device=DEV).manual_seed(5)
+    qual = torch.rand(N, M, generator=g, device=DEV)
+    length = 100.0 + qual
+    plen = torch.full((B,), 50, dtype=torch.int32, device=DEV)
+    out = []
+    for fn in (rb.rb_route_batch, rb.rb_route_batch_noalloc):
+        inst = rb.DeviceInstances(torch.tensor([0, 1, 1], dtype=torch.int32, device=DEV),
+                                  *[torch.ones(I, device=DEV) for _ in range(6)])
+        r = dict(assign=torch.empty(B, dtype=torch.int32, device=DEV),
+                 nbr_idx=torch.empty(B, k, dtype=torch.int32, device=DEV),
+                 nbr_dist=torch.empty(B, k, device=DEV), q_hat=torch.empty(B, M, device=DEV),
+                 l_hat=torch.empty(B, M, device=DEV))
+        print("bank in parts", fn.__name__, flush=True)
+        fn(q, bank, norms, k, qual, length, plen, inst, (0.4, 0.3, 0.3), **r)
+        torch.cuda.synchronize()
+        out.append(r)
+    for f in out[0]:
+        assert torch.equal(out[0][f], out[1][f]), f
+    ref_idx, ref_dist = reference(q, bank, k)
+    assert torch.equal(out[0]["nbr_idx"], ref_idx) and torch.equal(out[0]["nbr_dist"], ref_dist)
