@@ -61,7 +61,7 @@ constexpr int RES_MAX_NG = 8;
 // The selection: one workgroup of SEL_THREADS threads per request; up to
 // SEL_CAP super tiles or rows held in LDS at once; SEL_ROUND row tiles
 // recomputed per round.
-constexpr int SEL_THREADS = 512;
+constexpr int SEL_THREADS = 1024;
 constexpr int SEL_CAP = 2048;
 constexpr int SEL_ROUND = 64;
 constexpr int SEL_MAX_EPS = 16;            // row tiles per super tile, at most
@@ -70,6 +70,9 @@ constexpr long SEL_WANT_SUP = 16384;       // super tiles per request worth read
 // Bytes of maxima a call's workspace takes at most: a bank that would leave
 // more goes by in parts, each with its own scan and selection.
 constexpr size_t MAXIMA_LIMIT = (size_t)1 << 30;
+
+// Bytes of single values a scan keeps at most (KEEP_LIMIT in the plan).
+constexpr size_t KEEP_LIMIT = (size_t)8 << 20;
 
 // How one rb_knn_topk call is split (the tile scan; the query-resident scan
 // differs in that one workgroup holds the whole batch, so n_qt = 1; the
@@ -108,6 +111,7 @@ struct KnnPlan {
     // part n_sup super tiles of eps row tiles per request
     int n_seg, eps, wg_waves;
     long seg_rows, n_sup;
+    bool keep_acc;      // the scan keeps every row's value (at off_ent)
     size_t off_sup, off_ent, off_lkey, off_lidx;
     size_t bytes;       // of the workspace
 };

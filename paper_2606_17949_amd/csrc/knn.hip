@@ -530,12 +530,13 @@ void plan_res(KnnPlan *p, int num_cu, int reserve, size_t limit)
     const int B = p->B;
     const long rowb = (long)p->d * (p->dtype == 1 ? 2 : 4);
     const int groups = B > 0 ? (B + 15) / 16 : 1;
-    int ng = (int)(LDS_LIMIT / ((size_t)p->nks * WAVE * 16));
+    const size_t norms = RES_WAVES * 2 * 256 * sizeof(float);   // of every wave's tiles
+    int ng = (int)((LDS_LIMIT - norms) / ((size_t)p->nks * WAVE * 16));
     if (ng > RES_MAX_NG)
         ng = RES_MAX_NG;
     p->n_qt = (groups + ng - 1) / ng;
     p->ng = (groups + p->n_qt - 1) / p->n_qt;
-    p->lds_bytes = (size_t)p->nks * p->ng * WAVE * 16;
+    p->lds_bytes = (size_t)p->nks * p->ng * WAVE * 16 + norms;
     // super tiles: single row tiles up to SEL_WANT_SUP of them
     const long all_tiles = ((long)p->N + 15) / 16;
     p->eps = 1;
@@ -577,7 +578,9 @@ void plan_res(KnnPlan *p, int num_cu, int reserve, size_t limit)
     p->off_sup = off;
     off += align256((size_t)B * p->n_sup * 4);
     p->off_ent = off;
-    off += p->eps > 1 ? align256((size_t)B * p->n_sup * p->eps * 4) : 0;
+    const size_t keep = align256((size_t)B * p->n_sup * p->eps * 16 * 4);
+    p->keep_acc = p->n_seg == 1 && keep <= KEEP_LIMIT && off + keep + lists <= limit;
+    off += p->keep_acc ? keep : p->eps > 1 ? align256((size_t)B * p->n_sup * p->eps * 4) : 0;
     p->off_lkey = off;
     off += align256((size_t)B * p->k * 4);
     p->off_lidx = off;
@@ -850,6 +853,8 @@ hipError_t launch_knn(const KnnPlan &p, const void *queries, const void *bank,
         sa.n_sup = p.n_sup;
         sa.sup = (const float *)(w + p.off_sup);
         sa.ent = (const float *)(w + p.off_ent);
+        sa.acc = p.keep_acc ? sa.ent : nullptr;
+        sa.ld_acc = p.n_sup * p.eps * 16;
         sa.list_key = (uint32_t *)(w + p.off_lkey);
         sa.list_idx = (int32_t *)(w + p.off_lidx);
         sa.qual = bank_qual;
@@ -877,6 +882,8 @@ hipError_t launch_knn(const KnnPlan &p, const void *queries, const void *bank,
         a.eps = p.eps;
         a.sup = (float *)(w + p.off_sup);
         a.ent = (float *)(w + p.off_ent);
+        a.acc = p.keep_acc ? a.ent : nullptr;
+        a.ld_acc = sa.ld_acc;
         for (int seg = 0; seg < p.n_seg; ++seg) {
             const bool last = seg == p.n_seg - 1;
             a.row0 = seg * p.seg_rows;

@@ -35,7 +35,9 @@ struct MinScanArgs {
     long n_tiles, n_sup;  // their 16-row tiles; super tiles per request
     int eps;
     float *sup;           // [B][n_sup]
-    float *ent;           // [B][n_sup][eps]; unused when eps is 1
+    float *ent;           // [B][n_sup][eps]; unused when eps is 1 or with acc
+    float *acc;           // [B][ld_acc] every row's <q, x> - |x|^2/2, or null
+    long ld_acc;
 };
 
 // The selection from those maxima.
@@ -44,7 +46,8 @@ struct SelectArgs {
     const float *bank_norms;
     int B, d, nks, k, eps;
     long row0, rows, n_sup;
-    const float *sup, *ent;
+    const float *sup, *ent, *acc;   // as MinScanArgs has them
+    long ld_acc;
     uint32_t *list_key;   // [B][k] neighbours as distance keys and indices, in and out
     int32_t *list_idx;    //   (null: not kept)
     bool carry_in;        // the lists hold the neighbours of earlier parts of the bank

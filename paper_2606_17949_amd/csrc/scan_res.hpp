@@ -19,7 +19,8 @@ namespace {
 // across tile ends, and no wave waits for another after the request tile has
 // landed. A row tile leaves one value per request, the largest
 // <q, x> - |x|^2/2 of its 16 rows; eps consecutive tiles (a super tile, all
-// one wave's) one more. There is no bound, no list and no candidate test: the
+// one wave's) one more; a small scan keeps every row's value too, which spares
+// the selection from computing any again. There is no bound, no list and no candidate test: the
 // selection takes the k best super tiles and recomputes the few row tiles
 // that matter.
 template <int DT, int NG>
@@ -63,6 +64,7 @@ __global__ __launch_bounds__(RES_WAVES * WAVE, 1) void res_scan_kernel(const Min
                                                  n_tiles > 0 ? (uint32_t)nrows * rowb : 0u);
     const __amdgpu_buffer_rsrc_t rnm =
         make_rsrc(A.bank_norms + A.row0 + t0 * 16, n_tiles > 0 ? (uint32_t)nrows * 4u : 0u);
+    float *norms = (float *)(smem + (size_t)nks * NG * WAVE * 16) + wave * 2 * 256;
     const bool tail_ok = (nks - 1) * KS + jg * VEC < A.d;
     uint32_t lvo = (uint32_t)col * rowb + jg * 16;   // tile lt, k-step ls
     int ls = 0;
@@ -74,25 +76,39 @@ __global__ __launch_bounds__(RES_WAVES * WAVE, 1) void res_scan_kernel(const Min
             lvo += 16 * rowb - (uint32_t)nks * KSTEP_BYTES;
         }
     };
+    // the request tile, straight into LDS (zero past the batch and past the
+    // row), ahead of the bank's loads
+    {
+        const __amdgpu_buffer_rsrc_t rq = make_rsrc(A.queries, (uint32_t)A.B * rowb);
+        for (int f = wave; f < nks * NG; f += n_waves) {
+            const int sf = f / NG, q = q0 + (f - sf * NG) * 16 + col;
+            dma16(rq, qs + f * WAVE,
+                  q < A.B && (sf < nks - 1 || tail_ok)
+                      ? (uint32_t)q * rowb + sf * KSTEP_BYTES + jg * 16
+                      : OFF_NONE);
+        }
+    }
+    // |x|^2 of the rows of 16 tiles at a time, into the wave's own LDS (two
+    // slots): like the request tile not through registers, whose use would
+    // make the wave wait for the bank loads in flight. The norms of tiles
+    // 16b .. 16b + 15 are sent for at tile 16(b - 1), at least 16 k-steps and
+    // so more than a ring of bank loads before their use.
+    static_assert(R < 16, "norms land before the bank loads sent for after them are used");
+    auto issue_norms = [&](int batch) {
+        dma16(rnm, (i32x4 *)(norms + (batch & 1) * 256), (uint32_t)(batch * 256 + lane * 4) * 4u);
+    };
+    issue_norms(0);
+    __builtin_amdgcn_sched_barrier(0);
     i32x4 ring[R];
 #pragma unroll
     for (int u = 0; u < R; ++u)
         issue(ring[u]);
-    auto load_norms = [&](int tile) -> f32x4 {
-        return __builtin_bit_cast(f32x4, buffer_load16(rnm, (uint32_t)(tile * 16 + jg * 4) * 4u));
-    };
-    f32x4 xn = load_norms(0);
-
-    // the request tile (zero past the batch and past the row)
-    for (int item = tid; item < nks * NG * WAVE; item += blockDim.x) {
-        const int s = item / (NG * WAVE), g = (item / WAVE) % NG, l = item % WAVE;
-        const int q = q0 + g * 16 + (l & 15);
-        const i32x4 z = {0, 0, 0, 0};
-        qs[item] = q < A.B && s * KS + (l >> 4) * VEC < A.d
-                       ? load16(A.queries + (size_t)q * rowb + s * KSTEP_BYTES + (l >> 4) * 16)
-                       : z;
-    }
-    __syncthreads();
+    // the request tile has landed once at most the loads after it are
+    // outstanding, and after the barrier in every wave
+    __builtin_amdgcn_sched_barrier(0);
+    wait_vmcnt<R>();
+    stream_barrier();
+    __builtin_amdgcn_sched_barrier(0);
 
     // where this lane's results go: lane row r of result register v holds
     // group 4*v + (r with its two bits swapped), request col
@@ -115,6 +131,7 @@ __global__ __launch_bounds__(RES_WAVES * WAVE, 1) void res_scan_kernel(const Min
     int tile = 0, s = 0, es = 0;   // tile of the share, its k-step, its place in the super tile
     auto start_tile = [&]() {
         // the accumulators start from -|x|^2/2 of their rows (-inf past the bank)
+        const f32x4 xn = *(const f32x4 *)(norms + (tile & 31) * 16 + jg * 4);
         f32x4 h;
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -122,20 +139,29 @@ __global__ __launch_bounds__(RES_WAVES * WAVE, 1) void res_scan_kernel(const Min
 #pragma unroll
         for (int g = 0; g < NG; ++g)
             acc[g] = h;
-        xn = load_norms(tile + 1);
+        if ((tile & 15) == 0)
+            issue_norms(tile / 16 + 1);
     };
     auto end_tile = [&]() {
         float m[4 * NQ];
 #pragma unroll
         for (int g = 0; g < 4 * NQ; ++g)
             m[g] = g < NG ? max4(acc[g < NG ? g : 0]) : -INFINITY;
+        if (A.acc) {
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                const int q = q0 + g * 16 + col;
+                if (q < A.B)
+                    *(f32x4 *)(A.acc + (size_t)q * A.ld_acc + (t0 + tile) * 16 + jg * 4) = acc[g];
+            }
+        }
         const bool last = es == A.eps - 1 || tile == n_tiles - 1;
 #pragma unroll
         for (int v = 0; v < NQ; ++v) {
             const float r = rows_max4(m[4 * v], m[4 * v + 1], m[4 * v + 2], m[4 * v + 3]);
             if (A.eps > 1) {
                 smax[v] = fmaxf(smax[v], r);
-                if (own[v])
+                if (own[v] && !A.acc)
                     ent[v][tile] = r;
                 if (last) {
                     if (own[v])
@@ -149,19 +175,18 @@ __global__ __launch_bounds__(RES_WAVES * WAVE, 1) void res_scan_kernel(const Min
                 ++sup[v];
         }
         es = last ? 0 : es + 1;
-        s = 0;
         ++tile;
     };
     if (n_tiles > 0)
         start_tile();
     // One position per (tile, k-step), in order; position x sits in ring slot
-    // x % R and, once used, makes room for position x + R.
+    // x % R and, once used, makes room for position x + R. Every position
+    // sends its load whether or not there is anything left to fetch, so that
+    // a slot's load always has R - 1 others behind it when it is waited for.
     const long n_pos = (long)n_tiles * nks;
     for (long x = 0; x < n_pos; x += R) {
         static_for<0, R>([&](auto U) {
             constexpr int u = decltype(U)::value;
-            if (x + u >= n_pos)
-                return;
             const i32x4 *fr = qs + s * NG * WAVE + lane;
             i32x4 bq[NB];
 #pragma unroll
@@ -175,20 +200,24 @@ __global__ __launch_bounds__(RES_WAVES * WAVE, 1) void res_scan_kernel(const Min
             }
             issue(ring[u]);
             if (++s == nks) {
-                end_tile();
-                if (tile < n_tiles)
+                s = 0;
+                if (tile < n_tiles) {   // (past the share: nothing to write)
+                    end_tile();
                     start_tile();
+                }
             }
         });
     }
     // entries of the last super tile past the bank
-    if (A.eps > 1 && s1 > s0 && s1 * A.eps > t0 + n_tiles) {
+    if (A.eps > 1 && !A.acc && s1 > s0 && s1 * A.eps > t0 + n_tiles) {
 #pragma unroll
         for (int v = 0; v < NQ; ++v)
             if (own[v])
                 for (long e = n_tiles; e < s1 * A.eps - t0; ++e)
                     ent[v][e] = __builtin_nanf("");
     }
+    // (no global-to-LDS load may still be in flight when the workgroup ends)
+    wait_vmcnt<0>();
 }
 
 template <int DT, int NG>

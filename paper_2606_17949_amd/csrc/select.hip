@@ -17,18 +17,36 @@ __device__ __forceinline__ uint64_t wave_min_u64(uint64_t m)
     return ((uint64_t)~hi << 32) | ~lo;
 }
 
-// Sorts the n pairs of `cand` in LDS (distinct but for PAIR_NONE) by counting,
-// for each, the pairs below it; the k smallest go to out[0 .. min(k, n)).
-// Every thread of the workgroup takes part; no barrier inside.
-__device__ __forceinline__ void rank_pairs(const uint64_t *cand, int n, int k, uint64_t *out)
+// Sorts the n pairs of `cand` in LDS (distinct) by counting, for each, the
+// pairs below it; the k smallest go to out[0 .. min(k, n)). The threads split
+// the pairs to rank and, where there are more threads, the pairs to count
+// over; rank[] holds n counts, zero on entry. Every thread of the workgroup
+// takes part; `out` is complete after the next barrier.
+__device__ __forceinline__ void rank_pairs(const uint64_t *cand, int n, int k, int *rank,
+                                           uint64_t *out)
 {
+    const int width = (n + WAVE - 1) / WAVE * WAVE;
+    const int parts = width > 0 && width < SEL_THREADS ? SEL_THREADS / width : 1;
+    const int part = width > 0 ? threadIdx.x / width : 0;
+    if (part < parts || parts == 1) {
+        const int j0 = parts == 1 ? 0 : n * part / parts;
+        const int j1 = parts == 1 ? n : n * (part + 1) / parts;
+        for (int i = parts == 1 ? threadIdx.x : threadIdx.x - part * width; i < n;
+             i += SEL_THREADS) {
+            const uint64_t mine = cand[i];
+            int r = 0;
+#pragma unroll 8
+            for (int j = j0; j < j1; ++j)
+                r += cand[j] < mine ? 1 : 0;
+            atomicAdd(&rank[i], r);
+        }
+    }
+    __syncthreads();
     for (int i = threadIdx.x; i < n; i += SEL_THREADS) {
-        const uint64_t mine = cand[i];
-        int r = 0;
-        for (int j = 0; j < n; ++j)
-            r += cand[j] < mine ? 1 : 0;
+        const int r = rank[i];
+        rank[i] = 0;
         if (r < k)
-            out[r] = mine;
+            out[r] = cand[i];
     }
 }
 
@@ -39,32 +57,36 @@ __device__ __forceinline__ void rank_pairs(const uint64_t *cand, int n, int k, u
 // index) order, one in each of those k. Within them only row tiles whose own
 // nearest row is no farther than the k-th super tile's can hold one of the k
 // (k rows lie at or below that distance), in random order about k of them.
-// Those tiles' distances are computed again, with the scan's own sequence of
-// MFMA steps (so with its bits), and the k smallest (distance, index) pairs
-// of their rows are the result. What bounds it: a chain of about five
-// dependent memory accesses at small batches, at large ones the reading of
-// k tiles (16 rows) per request.
-//   1. a bound: every wave takes the k-th smallest of its lanes' two smallest
-//      super-tile distances; the workgroup the least of those. The super
-//      tiles at or below the bound go to LDS (about k times the wave count
-//      in random order) and are ranked by counting. More than fit (a bank of
-//      mostly equal rows) are taken k times the smallest instead.
-//   2. the row tiles of the k super tiles under the k-th distance.
-//   3. their rows' distances, SEL_ROUND tiles at a time: one wave per tile,
-//      the request replicated over the MFMA's columns; rows at or below the
-//      bound join the list, which is ranked after each round.
+// Those tiles' distances are read where the scan kept every one (acc), else
+// computed again with the scan's own sequence of MFMA steps (so with its
+// bits); the k smallest (distance, index) pairs of their rows are the result.
+// What bounds it: a chain of dependent memory accesses and barriers at small
+// batches, at large ones the reading of k tiles of 16 rows per request.
+//   1. a bound: the largest of at least k groups' least super-tile distances,
+//      a group being what one wave's threads hold, or one row of 16 lanes for
+//      k above the wave count. The super tiles at or below it go to LDS (50 to
+//      300 in random order) and are ranked by counting. More than fit (a bank
+//      of mostly equal rows) are taken k times the smallest instead.
+//   2. the row tiles of the k super tiles under the k-th distance (with kept
+//      distances, all of them).
+//   3. their rows' distances, SEL_ROUND tiles at a time, computed one wave per
+//      tile with the request replicated over the MFMA's columns; rows at or
+//      below the bound join the list, which is ranked after each round.
 //   4. the neighbours, and the label average.
 struct SelectShared {
     uint64_t cand[SEL_CAP];
     uint64_t best[RB_MAX_K_DEV], prev[RB_MAX_K_DEV];
-    uint32_t wave_t[SEL_THREADS / WAVE];
+    uint32_t group_min[SEL_THREADS / 16];
     uint64_t wave_min[SEL_THREADS / WAVE];
     int tiles[RB_MAX_K_DEV * SEL_MAX_EPS];
+    int sup[RB_MAX_K_DEV];
+    int rank[SEL_CAP];
     int n_cand, n_tiles;
     int32_t nbr[RB_MAX_K_DEV];
     float wts[RB_MAX_K_DEV];
     __align__(16) uint8_t q[SEL_MAX_ROW_BYTES];
 };
+static_assert(SEL_THREADS / 16 == WAVE, "one group per lane, k groups for every k");
 static_assert(SEL_ROUND * 16 + RB_MAX_K_DEV <= SEL_CAP, "a round's rows and the running best");
 
 template <int DT>
@@ -73,7 +95,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
     constexpr int VEC = Elem<DT>::VEC, ESZ = Elem<DT>::ESZ;
     constexpr int KS = 4 * VEC;
     constexpr int NW = SEL_THREADS / WAVE;
-    constexpr int LD = 12;   // k-steps of bank loads in flight
+    constexpr int LD = 8;   // k-steps of one block of bank loads
     __shared__ SelectShared S;
     const int b = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -83,6 +105,18 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
     const float *sup = A.sup + (size_t)b * A.n_sup;
     const float *ent = A.ent + (size_t)b * A.n_sup * A.eps;
 
+    // the first super tiles stay in registers: their loads go out before
+    // anything is waited for
+    // (a wave's share is contiguous, so that every wave has some)
+    constexpr int SV = SEL_WANT_SUP / SEL_THREADS;
+    const long share = (A.n_sup + NW - 1) / NW;
+    const long sup0 = wave * share, sup1 = min(A.n_sup, sup0 + share);
+    float sv[SV];
+#pragma unroll
+    for (int u = 0; u < SV; ++u) {
+        const long j = sup0 + lane + u * WAVE;
+        sv[u] = j < sup1 ? sup[j] : __builtin_nanf("");
+    }
     // |q|^2 (in every wave: the same sums in the same order), and the request
     // in LDS, zero past the row
     const uint8_t *qrow = A.queries + (size_t)b * rowb;
@@ -94,8 +128,11 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
             *(i32x4 *)(S.q + off) = v;
     }
     qn = wave_sum(qn);
-    for (uint32_t off = rowb + tid * 16; off < (uint32_t)A.nks * KSTEP_BYTES; off += SEL_THREADS * 16)
+    const uint32_t padded = (uint32_t)(A.nks + LD - 1) / LD * LD * KSTEP_BYTES;
+    for (uint32_t off = rowb + tid * 16; off < padded; off += SEL_THREADS * 16)
         *(i32x4 *)(S.q + off) = i32x4{0, 0, 0, 0};
+    for (int i = tid; i < SEL_CAP; i += SEL_THREADS)
+        S.rank[i] = 0;
     if (tid == 0)
         S.n_cand = S.n_tiles = 0;
     // a maximum as a distance key; an entry past the bank (NaN) is absent
@@ -104,59 +141,43 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
     };
 
     // ---- 1. the k super tiles
-    uint32_t m1 = KEY_NONE, m2 = KEY_NONE;
-    for (long i = tid; i < A.n_sup; i += 8 * SEL_THREADS) {
-        float v[8];
+    uint32_t least = KEY_NONE;
+    auto each_sup = [&](auto f) {   // f(key, index) of this thread's super tiles
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const long j = i + (long)u * SEL_THREADS;
-            v[u] = j < A.n_sup ? sup[j] : __builtin_nanf("");
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const uint32_t key = key_of(v[u]);
-            m2 = min(m2, max(m1, key));
-            m1 = min(m1, key);
-        }
+        for (int u = 0; u < SV; ++u)
+            f(key_of(sv[u]), (int)sup0 + lane + u * WAVE);
+        for (long j = sup0 + lane + SV * WAVE; j < sup1; j += WAVE)
+            f(key_of(sup[j]), (int)j);
+    };
+    each_sup([&](uint32_t key, int) { least = min(least, key); });
+    const auto umin = [](uint32_t x, uint32_t y) { return x < y ? x : y; };
+    const auto umax = [](uint32_t x, uint32_t y) { return x > y ? x : y; };
+    // the largest of the least distances of at least k groups (waves, half
+    // waves or rows of lanes) has a super tile of each at or below it
+    least = row16_reduce(least, umin);
+    if (k <= NW) {
+        least = wave_reduce(least, umin);
+    } else if (k <= 2 * NW) {
+        least = umin(least, dpp<0x142, 0xa>(least));   // row_bcast:15 into rows 1 and 3
+        if (!(lane & 16))
+            least = 0;   // (rows 0 and 2: no group of their own)
     }
-    {
-        // the k-th smallest of the wave's lane values: the largest prefix
-        // with fewer than k of them below it
-        uint32_t prefix = 0;
-        for (int bit = 31; bit >= 0; --bit) {
-            const uint32_t trial = prefix | (1u << bit);
-            if (popc(ballot(m1 < trial)) + popc(ballot(m2 < trial)) < k)
-                prefix = trial;
-        }
-        if (lane == 0)
-            S.wave_t[wave] = prefix;
-    }
+    if ((lane & 15) == 0)
+        S.group_min[wave * 4 + (lane >> 4)] = least;
     __syncthreads();
-    uint32_t bound = KEY_NONE - 1;   // absent entries stay out
-#pragma unroll
-    for (int w = 0; w < NW; ++w)
-        bound = min(bound, S.wave_t[w]);
-    for (long i = tid; i < A.n_sup; i += 8 * SEL_THREADS) {
-        float v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const long j = i + (long)u * SEL_THREADS;
-            v[u] = j < A.n_sup ? sup[j] : __builtin_nanf("");
+    // absent entries stay out
+    uint32_t bound = min(KEY_NONE - 1, wave_reduce(S.group_min[lane], umax));
+    each_sup([&](uint32_t key, int j) {
+        if (key <= bound) {
+            const int pos = atomicAdd(&S.n_cand, 1);
+            if (pos < SEL_CAP)
+                S.cand[pos] = pack(key, j);
         }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const uint32_t key = key_of(v[u]);
-            if (key <= bound) {
-                const int pos = atomicAdd(&S.n_cand, 1);
-                if (pos < SEL_CAP)
-                    S.cand[pos] = pack(key, (int32_t)(i + (long)u * SEL_THREADS));
-            }
-        }
-    }
+    });
     __syncthreads();
     int n_best = min(S.n_cand, k);
     if (S.n_cand <= SEL_CAP) {
-        rank_pairs(S.cand, S.n_cand, k, S.best);
+        rank_pairs(S.cand, S.n_cand, k, S.rank, S.best);
     } else {
         uint64_t last = 0;
         for (int r = 0; r < k; ++r) {
@@ -188,31 +209,49 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
         const float t = key2f((uint32_t)(S.best[k - 1] >> 32));
         bound = min(KEY_NONE - 1, f2key(t + ldexpf(qn + fabsf(t) + 1.f, -18)));
     }
-    for (int i = tid; i < n_best * A.eps; i += SEL_THREADS) {
-        const int j = i / A.eps, e = i - j * A.eps;
-        const int s = (int)(uint32_t)S.best[j];
-        bool in = true;
-        if (A.eps > 1)
-            in = key_of(ent[(size_t)s * A.eps + e]) <= bound;
-        if (in)
-            S.tiles[atomicAdd(&S.n_tiles, 1)] = s * A.eps + e;
+    int n_items;   // what a round takes SEL_ROUND * 16 rows of
+    if (A.acc) {
+        n_items = n_best * A.eps * 16;
+        if (tid < n_best)
+            S.sup[tid] = (int)(uint32_t)S.best[tid];
+    } else {
+        for (int i = tid; i < n_best * A.eps; i += SEL_THREADS) {
+            const int j = i / A.eps, e = i - j * A.eps;
+            const int s = (int)(uint32_t)S.best[j];
+            if (A.eps == 1 || key_of(ent[(size_t)s * A.eps + e]) <= bound)
+                S.tiles[atomicAdd(&S.n_tiles, 1)] = s * A.eps + e;
+        }
     }
     // the rows found in earlier launches over other parts of the bank
     if (tid < k && A.carry_in)
         S.prev[tid] = pack(A.list_key[(size_t)b * k + tid], A.list_idx[(size_t)b * k + tid]);
     __syncthreads();
-    const int n_tiles = S.n_tiles;
+    if (!A.acc)
+        n_items = S.n_tiles * 16;
 
     // ---- 3. their rows
     int n_prev = A.carry_in ? k : 0;
-    for (int r0 = 0; r0 == 0 || r0 < n_tiles; r0 += SEL_ROUND) {
+    for (int r0 = 0; r0 == 0 || r0 < n_items; r0 += SEL_ROUND * 16) {
         if (tid == 0)
             S.n_cand = 0;
         __syncthreads();
+        const int r1 = min(n_items, r0 + SEL_ROUND * 16);
         for (int i = tid; i < n_prev; i += SEL_THREADS)
             if ((uint32_t)(S.prev[i] >> 32) != KEY_NONE)
                 S.cand[atomicAdd(&S.n_cand, 1)] = S.prev[i];
-        for (int ti = r0 + wave; ti < min(n_tiles, r0 + SEL_ROUND); ti += NW) {
+        if (A.acc) {
+            for (int i = r0 + tid; i < r1; i += SEL_THREADS) {
+                const int per = A.eps * 16, j = i / per;
+                const long row = (long)S.sup[j] * per + (i - j * per);
+                const float v = row < A.rows ? A.acc[(size_t)b * A.ld_acc + row]
+                                             : __builtin_nanf("");
+                const uint32_t key = f2key(fmaf(-2.f, v, qn));
+                // (a distance that is not a number is no neighbour)
+                if (v == v && key <= bound)
+                    S.cand[atomicAdd(&S.n_cand, 1)] = pack(key, (int32_t)(A.row0 + row));
+            }
+        }
+        for (int ti = r0 / 16 + wave; !A.acc && ti < r1 / 16; ti += NW) {
             const int te = __builtin_amdgcn_readfirstlane(S.tiles[ti]);
             const long row = A.row0 + (long)te * 16;      // first row of the tile
             const long rend = A.row0 + A.rows;
@@ -227,26 +266,37 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
                                             ? OFF_NONE
                                             : vo + s * KSTEP_BYTES);
             };
-            f32x4 acc;
+            // two blocks of LD k-steps in flight (past the row, zeros)
+            i32x4 a[2][LD];
+#pragma unroll
+            for (int u = 0; u < 2 * LD; ++u)
+                a[u / LD][u % LD] = load(u);
+            f32x4 acc = __builtin_bit_cast(
+                f32x4, buffer_load16(make_rsrc(A.bank_norms + row, (uint32_t)n_in * 4u), jg * 16));
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                acc[e] = jg * 4 + e < n_in ? -0.5f * A.bank_norms[row + jg * 4 + e] : -INFINITY;
-            for (int s0 = 0; s0 < A.nks; s0 += LD) {
-                i32x4 a[LD];
+                acc[e] = jg * 4 + e < n_in ? -0.5f * acc[e] : -INFINITY;
+            for (int s0 = 0; s0 < A.nks; s0 += 2 * LD) {
 #pragma unroll
-                for (int u = 0; u < LD; ++u)
-                    a[u] = load(s0 + u);
+                for (int h = 0; h < 2; ++h) {
+                    const uint8_t *qf = S.q + (s0 + h * LD) * KSTEP_BYTES + jg * 16;
 #pragma unroll
-                for (int u = 0; u < LD; ++u)
-                    if (s0 + u < A.nks)
-                        acc = mfma_step<DT>(
-                            a[u], *(const i32x4 *)(S.q + (s0 + u) * KSTEP_BYTES + jg * 16), acc);
+                    for (int u = 0; u < LD; ++u)
+                        acc = mfma_step<DT>(a[h][u], *(const i32x4 *)(qf + u * KSTEP_BYTES), acc);
+                    if (s0 + (h + 2) * LD < A.nks) {
+#pragma unroll
+                        for (int u = 0; u < LD; ++u)
+                            a[h][u] = load(s0 + (h + 2) * LD + u);
+                    }
+                    if (s0 + (h + 1) * LD >= A.nks)
+                        break;
+                }
             }
             // lane (col, jg) holds rows jg*4 .. +3; every column the same
+            // (a distance that is not a number is no neighbour)
             if (col < 4) {
                 const float v = col == 0 ? acc[0] : col == 1 ? acc[1] : col == 2 ? acc[2] : acc[3];
                 const uint32_t key = f2key(fmaf(-2.f, v, qn));
-                // (a distance that is not a number is no neighbour)
                 if (v == v && jg * 4 + col < n_in && key <= bound)
                     S.cand[atomicAdd(&S.n_cand, 1)] = pack(key, (int32_t)(row + jg * 4 + col));
             }
@@ -256,7 +306,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
         if (tid < k)
             S.best[tid] = PAIR_NONE;
         __syncthreads();
-        rank_pairs(S.cand, n, k, S.best);
+        rank_pairs(S.cand, n, k, S.rank, S.best);
         __syncthreads();
         if (tid < k)
             S.prev[tid] = S.best[tid];
@@ -284,9 +334,46 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
     if (!A.q_hat)
         return;
     __syncthreads();
-    for (int m = tid; m < A.M; m += SEL_THREADS)
-        average_labels(S.nbr, A.inv_dist ? S.wts : nullptr, k, A.qual, A.len, A.N, A.M, m,
-                       A.q_hat + (size_t)b * A.M + m, A.l_hat + (size_t)b * A.M + m);
+    // every (neighbour, model) label in flight at once, then the averages in
+    // neighbour order, as average_labels takes them (whose loop serves more
+    // labels than threads)
+    const int M = A.M;
+    if (k * M <= SEL_THREADS) {
+        float *lq = (float *)S.cand, *ll = lq + SEL_THREADS;
+        if (tid < k * M) {
+            const int j = tid / M;
+            const int32_t n = S.nbr[j];
+            const bool ok = n >= 0 && n < A.N;
+            const size_t o = (size_t)(ok ? n : 0) * M + (tid - j * M);
+            lq[tid] = ok ? A.qual[o] : __builtin_nanf("");
+            ll[tid] = ok ? A.len[o] : __builtin_nanf("");
+        }
+        __syncthreads();
+        if (tid < M) {
+            float sq = 0.f, sl = 0.f, sw = 0.f;
+#pragma unroll 8
+            for (int j = 0; j < k; ++j) {
+                const float q = lq[j * M + tid], l = ll[j * M + tid];
+                if (A.inv_dist) {
+                    const float w = S.wts[j];
+                    sq = fmaf(w, q, sq);
+                    sl = fmaf(w, l, sl);
+                    sw += w;
+                } else {
+                    sq += q;
+                    sl += l;
+                }
+            }
+            if (!A.inv_dist)
+                sw = (float)k;
+            A.q_hat[(size_t)b * M + tid] = sq / sw;
+            A.l_hat[(size_t)b * M + tid] = sl / sw;
+        }
+        return;
+    }
+    for (int m = tid; m < M; m += SEL_THREADS)
+        average_labels(S.nbr, A.inv_dist ? S.wts : nullptr, k, A.qual, A.len, A.N, M, m,
+                       A.q_hat + (size_t)b * M + m, A.l_hat + (size_t)b * M + m);
 }
 
 // The second half of a lookup taken in two calls: the neighbours from the
