@@ -16,8 +16,7 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librouteb.so")
-SOURCES = ["api.hip", "knn.hip", "route.hip", "scan_bf16.hip", "scan_bf16_ragged.hip",
-           "scan_f32.hip", "scan_f32_ragged.hip", "scan_rq.hip", "scan_rq12.hip", "scan_rq16.hip",
+SOURCES = ["api.hip", "knn.hip", "route.hip", "scan_rq.hip", "scan_rq12.hip", "scan_rq16.hip",
            "scan_rq24.hip", "scan_rq32.hip", "scan_gemm.hip", "scan_res_bf16.hip",
            "scan_res_f32.hip", "select.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

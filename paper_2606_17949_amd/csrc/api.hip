@@ -147,6 +147,9 @@ RouteExtra route_extra(size_t base, int B, int k, int M)
     return e;
 }
 
+// Workspace bytes of a plan: its layout, and at least what its sizes ask for.
+size_t plan_bytes(const rb::KnnPlan &p) { return p.bytes > p.contract ? p.bytes : p.contract; }
+
 const rb_options k_default_opts = {RB_ORDER_ARRIVAL, RB_KNN_UNIFORM, nullptr, nullptr, nullptr,
                                    0u};
 
@@ -246,7 +249,7 @@ rb_status route_batch(const void *queries, const void *bank, const float *bank_n
     rb::KnnPlan p;
     if ((s = plan(B, N, d, dtype, k, &p, (o->flags & RB_FLAG_OVERLAP) != 0, limit)) != RB_OK)
         return s;
-    const RouteExtra ex = route_extra(p.bytes, B, k, M);
+    const RouteExtra ex = route_extra(plan_bytes(p), B, k, M);
     if (!ws || ws_bytes < ex.bytes)
         return RB_ERR_WORKSPACE;
     if (!aligned(ws, 256))
@@ -308,7 +311,8 @@ rb_status rb_workspace_size(int B, int N, int d, rb_dtype dtype, int k, int M, s
         return s;
     if ((s = plan(B, N, d, dtype, k, &q, true)) != RB_OK)
         return s;
-    *bytes = route_extra(p.bytes > q.bytes ? p.bytes : q.bytes, B, k, M).bytes;
+    const size_t pb = plan_bytes(p), qb = plan_bytes(q);
+    *bytes = route_extra(pb > qb ? pb : qb, B, k, M).bytes;
     return RB_OK;
 }
 
@@ -341,7 +345,7 @@ rb_status rb_knn_topk(const void *queries, const void *bank, const float *bank_n
     rb::KnnPlan p;
     if ((s = plan(B, N, d, dtype, k, &p)) != RB_OK)
         return s;
-    if (!ws || ws_bytes < p.bytes)
+    if (!ws || ws_bytes < plan_bytes(p))
         return RB_ERR_WORKSPACE;
     if (!aligned(ws, 256))
         return RB_ERR_ALIGN;
@@ -462,7 +466,7 @@ rb_status rb_knn_predict(const void *queries, const void *bank, const float *ban
     rb::KnnPlan p;
     if ((s = plan(B, N, d, dtype, k, &p, (o->flags & RB_FLAG_OVERLAP) != 0)) != RB_OK)
         return s;
-    const RouteExtra ex = route_extra(p.bytes, B, k, M);
+    const RouteExtra ex = route_extra(plan_bytes(p), B, k, M);
     if (!ws || ws_bytes < ex.bytes)
         return RB_ERR_WORKSPACE;
     if (!aligned(ws, 256))
@@ -527,7 +531,7 @@ rb_status rb_route_batch_noalloc(const void *queries, const void *bank, const fl
     rb::KnnPlan p;
     if ((s = plan(B, N, d, dtype, k, &p, false, limit)) != RB_OK)
         return s;
-    if (route_extra(p.bytes, B, k, M).bytes > (size_t)RB_SCRATCH_BYTES)
+    if (route_extra(plan_bytes(p), B, k, M).bytes > (size_t)RB_SCRATCH_BYTES)
         return RB_ERR_SCRATCH;
     void *ws = scratch_ptr();
     if (!ws)

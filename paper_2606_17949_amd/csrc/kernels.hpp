@@ -7,51 +7,30 @@
 
 namespace rb {
 
-// The scan runs 8 waves, two per SIMD, each within half the register file
-// (256 registers: 128 accumulators for 2 row tiles x 16 query groups): the
-// workgroup covers 256 bank rows per iteration, so every streamed query byte
-// serves 256 rows, and each SIMD has a second wave to cover load latency.
-constexpr int SCAN_THREADS = 512;   // 8 waves, two per SIMD
-constexpr int SCAN_WAVES = 8;
-constexpr int SCAN_RT = 2;          // 16-row MFMA tiles per wave per iteration (32 rows)
-constexpr int SCAN_KPAD = 4;        // k-steps per row are padded to a multiple of this
-// Ring depth of the scan's loads, in k-steps (the loop is unrolled by it):
-// bank fragments go to a register ring and streamed query fragments to an LDS
-// ring of as many slots, both depth - 1 k-steps ahead of the MFMAs. Four for
-// tiles below 256 queries. For a full tile, four only for bf16 rows of whole
-// k-steps with less than half the tile resident (the fp32 MFMA steps and the
-// lane masks of a partial k-step take the registers, and with half the tile
-// resident or more the LDS serves better as resident queries than as ring
-// slots).
-__host__ __device__ constexpr int scan_ring(int dtype, int ng, int gr, bool ragged)
-{
-    return ng < 16 || (dtype == 1 && !ragged && gr < ng / 2) ? 4 : 2;
-}
-constexpr int STAGE_CAP = 128;      // per-wave LDS staging of one iteration's candidates
 constexpr size_t LDS_LIMIT = 160 * 1024;
-constexpr int MERGE_WAVES = 4;      // queries per merge workgroup, one wave each
-constexpr int MERGE_CAP = 2048;     // candidates per query the merge holds in LDS
-constexpr int MERGE_MAX_LISTS = 64 * 64;   // 64 lists per lane
 constexpr int RB_MAX_K_DEV = 64;    // largest k (the ABI limit)
-constexpr int SEED_MAX_GROUPS = 2048;  // S / 16 for S <= 32768
 // The query-resident scan (bf16 rows of 384, 512, 768 or 1024 elements, a
 // batch that fits its waves' registers): RQ_WAVES waves, blocks of RQ_ROWS
 // bank rows, a ring of stages of a block's k-steps in LDS.
 constexpr int RQ_WAVES = 8;
 constexpr int RQ_ROWS = 32;
+constexpr int RQ_EPS = 16;     // row tiles of a super tile
+constexpr int RQ_SLOTS = 4;    // ring slots
+// super tiles whose maxima wait in LDS, as many as fit beside the ring
+__host__ __device__ constexpr int rq_hold(int qw, int rs) { return qw == 4 && rs == 1 ? 8 : 16; }
+// stages of a block: whole blocks of 12 k-steps, else half blocks
+constexpr int rq_spb(int nks) { return nks == 12 ? 1 : 2; }
 constexpr int RQ_SMALL_B_MIN_ROWS = 2048;   // bank rows per compute unit, batches of <= 64
-constexpr int RQ_SPLIT_MIN_ROWS = 1024;     // chunk rows from which the scan may go in two passes
-// The GEMM-structured scan (bf16 rows, d a multiple of GM_KST, more than 256
-// requests): GM_WAVES waves per workgroup, macro tiles of GM_ROWS bank rows by
-// a tile of GM_QRY requests, K in stages of GM_KST elements in GM_SLOTS LDS
-// slots.
+// The GEMM-structured scan (bf16 rows): GM_WAVES waves per workgroup, macro
+// tiles of GM_ROWS bank rows by a tile of 128 or 256 requests, K in stages of
+// GM_KST elements in GM_SLOTS LDS slots of up to GM_SLOT_LOADS loads.
 constexpr int GM_WAVES = 8;
 constexpr int GM_ROWS = 256;
-constexpr int GM_QRY = 256;
 constexpr int GM_KST = 64;
 constexpr int GM_SLOTS = 2;
-constexpr int GM_STAGE = 64;   // per-wave LDS staging of one macro tile's candidates
-
+constexpr int GM_SLOT_LOADS = 64;
+constexpr int GM_EPS = 16;     // entries of a macro tile
+constexpr int GM_HOLD = 8;     // macro tiles whose maxima wait in LDS
 // The LDS-resident scan: up to RES_WAVES waves per workgroup, each with
 // RES_RING k-steps of bank loads in flight; request tiles of up to RES_MAX_NG
 // groups of 16.
@@ -71,52 +50,35 @@ constexpr long SEL_WANT_SUP = 16384;       // super tiles per request worth read
 // more goes by in parts, each with its own scan and selection.
 constexpr size_t MAXIMA_LIMIT = (size_t)1 << 30;
 
-// Bytes of single values a scan keeps at most (KEEP_LIMIT in the plan).
+// Bytes of single values a scan keeps at most: then the selection takes 10 us
+// for 19 (it computes no row tile again), while 26 MB of them made a scan of
+// 64 x 100,000 take 55 us for 44.
 constexpr size_t KEEP_LIMIT = (size_t)8 << 20;
 
-// How one rb_knn_topk call is split (the tile scan; the query-resident scan
-// differs in that one workgroup holds the whole batch, so n_qt = 1; the
-// GEMM-structured scan in its request tiles of GM_QRY, one workgroup per
-// (chunk, tile) with the chunk in macro tiles of GM_ROWS rows).
-//  * seed: S bank rows spread evenly over the bank, scored in groups of 16;
-//    per query, the k-th smallest of 128 of the S/16 group minima (each
-//    lane's two smallest of its share) bounds the k-th nearest distance from
-//    above (k distinct rows lie at or below it).
-//  * scan: query tiles of 16*ng queries, whose first gr groups stay in LDS
-//    for the whole call while the others stream through it; the
-//    bank in n_chunks contiguous row ranges (multiples of 16 rows); one
-//    workgroup per (chunk, tile); each of its SCAN_WAVES waves owns 16*rt rows per
-//    iteration; the workgroup keeps, per query, one list of the k best
-//    candidates that pass the bound.
-//  * merge: per query, the k smallest of its W lists (W = n_chunks, times
-//    the row halves rs of the query-resident scan).
+// How one rb_knn_topk call is split.
+//  * the bank in n_seg parts of seg_rows rows (one, unless the maxima would
+//    pass the limit), each scanned and selected from by itself;
+//  * scan: the part in n_chunks row ranges, the requests in n_qt tiles, one
+//    workgroup per (chunk, tile), `grid` of them; per request it leaves n_sup
+//    super tiles of eps row tiles;
+//  * selection: one workgroup per request.
 struct KnnPlan {
-    int kind;           // 0 tile scan, 1 query-resident scan, 2 GEMM-structured scan,
-                        // 3 LDS-resident scan
-    int qw, rs, spb;    // query-resident scan: query groups per wave, row halves, stages per block,
-    int stages;         //   ring slots
+    int kind;           // 0 LDS-resident scan, 1 query-resident scan, 2 GEMM-structured scan
     int dtype;          // 0 fp32, 1 bf16
     int B, N, d, k;
-    int nks, nksp;      // 64-byte k-steps per row, padded to SCAN_KPAD
-    int ng, gr, rt;     // query groups of 16 per tile (gr of them resident), 16-row tiles per wave
-    int n_qt, n_chunks, W;   // request tiles, bank chunks, lists per query the scan leaves
-    long rows_per_chunk;
-    int S, G;           // seed rows and groups (0 = no seed)
-    int rq_split;       // query-resident scan: rows of every chunk in its first pass (0 = one pass)
-    int grid;           // scan workgroups
-    int ovf_cap;        // candidates per scan wave that the workspace takes past LDS
+    int nks;            // 64-byte k-steps per row
+    int ng;             // LDS-resident scan: groups of 16 requests per tile,
+    int wg_waves;       //   waves per workgroup,
+    bool keep_acc;      //   every row's value kept (at off_ent)
+    int qw, rs;         // query-resident scan: query groups per wave, row halves; GEMM-structured
+                        //   scan: 32-request tiles per wave (qw)
+    int n_seg, n_qt, n_chunks, eps, grid;
+    long seg_rows, n_sup, rows_per_chunk, sup_per_chunk;
     size_t lds_bytes;
-    size_t off_tau, off_qn, off_gmin, off_ccnt, off_ckey, off_cidx, off_ovf;
-    // scans that leave maxima: the bank in n_seg parts of seg_rows rows, per
-    // part n_sup super tiles of eps row tiles per request
-    int n_seg, eps, wg_waves;
-    long seg_rows, n_sup;
-    bool keep_acc;      // the scan keeps every row's value (at off_ent)
-    size_t off_sup, off_ent, off_lkey, off_lidx;
-    size_t bytes;       // of the workspace
+    size_t off_sup, off_ent, off_lkey, off_lidx, bytes;
+    size_t contract;    // bytes of workspace a call asks for at least
 };
 
-// reserve: compute units per XCD to leave free for kernels of other streams.
 // limit: bytes the maxima may take (they are cut to it by taking the bank in
 // parts).
 int plan_knn(int B, int N, int d, int dtype, int k, int num_cu, KnnPlan *p, int reserve = 0,

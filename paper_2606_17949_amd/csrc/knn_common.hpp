@@ -8,36 +8,28 @@
 
 namespace rb {
 
-struct ScanArgs {
-    const uint8_t *queries, *bank;
-    const float *bank_norms, *qn;
-    int B, N, d, k, nks, nksp, n_chunks, n_qt;
-    long rows_per_chunk;
-    long row_lo, row_hi;      // query-resident scan: rows [row_lo, row_hi) of every chunk;
-    int n_lists, list_base;   // its lists: list_base + c*RS + half of n_lists per query
-    uint32_t *tau;    // [B] shared bound (distance keys), lowered with atomicMin
-    int32_t *ccnt;    // [B][lists] list lengths
-    uint32_t *ckey;   // [B][lists][k]
-    int32_t *cidx;    // [B][lists][k]
-    uint32_t *ovf;    // per wave: [3][ovf_cap] candidates past the LDS staging area
-    int ovf_cap;      // 16*RT*16*NG - STAGE_CAP (every (row, query) pair of an iteration)
+// Every scan writes, per request and 16-row tile of the bank, the largest
+// <q, x> - |x|^2/2 of the tile's rows (the nearest row's distance is |q|^2 - 2
+// times that), and the maximum over every eps such entries (a super tile, of
+// eps * 16 consecutive rows). The rows go by in chunks, each with super tiles
+// of its own; entries and super tiles without a row hold NaN.
+struct Maxima {
+    float *sup;          // of request q: super tile s at s + q*sup_q
+    float *ent;          // its entry e at s*ent_s + e + q*ent_q (unused when eps is 1 or when
+    long sup_q;          //   every row's value is kept)
+    long ent_s, ent_q;
 };
 
-// A scan that leaves maxima (MinScanArgs) writes, per request and 16-row tile
-// of the bank, the largest <q, x> - |x|^2/2 of the tile's rows (the nearest
-// row's distance is |q|^2 - 2 times that), and the maximum over every eps
-// consecutive such entries (a super tile). Entries past the bank hold NaN.
-struct MinScanArgs {
+struct ScanArgs {
     const uint8_t *queries, *bank;
     const float *bank_norms;
-    int B, d, nks, n_chunks, n_qt;
+    int B, d, nks, n_chunks, n_qt;   // nks: k-steps of a row (GEMM scan: stages)
     long row0, rows;      // bank rows [row0, row0 + rows) of this launch
-    long n_tiles, n_sup;  // their 16-row tiles; super tiles per request
+    long n_tiles, n_sup;  // their 16-row tiles (LDS-resident scan); super tiles per request
     int eps;
-    float *sup;           // [B][n_sup]
-    float *ent;           // [B][n_sup][eps]; unused when eps is 1 or with acc
-    float *acc;           // [B][ld_acc] every row's <q, x> - |x|^2/2, or null
-    long ld_acc;
+    long rows_per_chunk, sup_per_chunk;   // (LDS-resident scan: one chunk of all rows)
+    Maxima m;
+    float *acc;           // [n_sup * eps][B][16] every row's <q, x> - |x|^2/2, or null
 };
 
 // The selection from those maxima.
@@ -45,11 +37,13 @@ struct SelectArgs {
     const uint8_t *queries, *bank;
     const float *bank_norms;
     int B, d, nks, k, eps;
-    long row0, rows, n_sup;
-    const float *sup, *ent, *acc;   // as MinScanArgs has them
-    long ld_acc;
+    long row0, rows, n_sup, rows_per_chunk, sup_per_chunk;
+    Maxima m;
+    const float *acc;     // as ScanArgs has it
     uint32_t *list_key;   // [B][k] neighbours as distance keys and indices, in and out
     int32_t *list_idx;    //   (null: not kept)
+    bool split_tiles;     // entries 2t and 2t + 1 of a super tile are rows 0-3, 8-11, 16-19,
+                          // 24-27 and the others of its 32-row tile t
     bool carry_in;        // the lists hold the neighbours of earlier parts of the bank
     int32_t *nbr_idx;     // results, null in all but the last part
     float *nbr_dist;
@@ -62,51 +56,12 @@ struct SelectArgs {
 hipError_t launch_select(int dtype, const SelectArgs &a, hipStream_t s);
 hipError_t launch_from_list(const SelectArgs &a, hipStream_t s);
 
-// Byte offsets of the scan's LDS regions for a tile of ng query groups of
-// which the first gr are resident for the whole kernel, with a ring of
-// `slots` k-steps for the others.
-struct ScanLayout {
-    uint32_t res, strm, list, qn, gb, lmk, nu, nx, sq, sk, si, bytes;
-};
-
-__host__ __device__ inline ScanLayout scan_layout(int ng, int gr, int nksp, int k, int rt, int slots)
-{
-    ScanLayout L;
-    const uint32_t bm = (uint32_t)ng * 16, frag = WAVE * 16;
-    uint32_t o = 0;
-    L.res = o;     // [nksp][gr][64] fragments of the resident groups, every k-step
-    o += (uint32_t)nksp * gr * frag;
-    L.strm = o;    // [slots][ng - gr][64] fragments of the other groups, one k-step per
-    // slot, and a sink fragment for loads with no destination
-    o += gr < ng ? (uint32_t)(slots * (ng - gr) + 1) * frag : 0u;
-    L.list = o;    // [bm][k] (key << 32 | index), the workgroup's candidate lists
-    o += bm * k * 8;
-    L.qn = o;      // [bm] |q|^2
-    o += bm * 4;
-    L.gb = o;      // [bm] snapshot of the shared bound
-    o += bm * 4;
-    L.lmk = o;     // [bm] an upper bound of each list's largest key
-    o += bm * 4;
-    L.nu = o;      // [bm] each query's candidate threshold on the accumulators
-    o += bm * 4;
-    L.nx = o;      // [waves][2][16*rt] -|x|^2/2 of this and the next iteration's rows
-    o += SCAN_WAVES * 2 * rt * 16 * 4;
-    L.sq = o;      // [waves][STAGE_CAP] staged candidates: tile query,
-    o += SCAN_WAVES * STAGE_CAP * 4;
-    L.sk = o;      //   distance key,
-    o += SCAN_WAVES * STAGE_CAP * 4;
-    L.si = o;      //   bank row
-    o += SCAN_WAVES * STAGE_CAP * 4;
-    L.bytes = o;
-    return L;
-}
-
 // Byte offsets of the query-resident scan's LDS regions.
 struct RqLayout {
-    uint32_t ring, norms, lists, qinfo, bytes;
+    uint32_t ring, norms, stage, sup, bytes;
 };
 
-__host__ __device__ inline RqLayout rq_layout(int k, int qw, int kstg, int stages)
+__host__ __device__ inline RqLayout rq_layout(int qw, int rs, int kstg, int stages)
 {
     RqLayout L;
     uint32_t o = 0;
@@ -114,62 +69,46 @@ __host__ __device__ inline RqLayout rq_layout(int k, int qw, int kstg, int stage
     o += (uint32_t)stages * kstg * (RQ_ROWS / 16) * WAVE * 16;
     L.norms = o;   // [stages][64] |x|^2 of the rows of a block (with its first stage)
     o += (uint32_t)stages * WAVE * 4;
-    L.lists = o;   // [waves][16 * qw][k] (key << 32 | index), one list per owned query
-    o += (uint32_t)RQ_WAVES * qw * 16 * k * 8;
-    L.qinfo = o;   // [waves][16 * qw] |q|^2, then [waves][16 * qw] the shared bound
-    o += (uint32_t)RQ_WAVES * qw * 16 * 8;
+    L.stage = o;   // [rs][RQ_WAVES / rs * 16 * qw][RQ_EPS] maxima of a super tile (two
+    // buffers where two waves share a request)
+    o += (uint32_t)RQ_WAVES * qw * 16 * RQ_EPS * 4;
+    L.sup = o;     // [RQ_WAVES / rs * 16 * qw][rq_hold] maxima of the last super tiles
+    o += (uint32_t)RQ_WAVES / rs * qw * 16 * rq_hold(qw, rs) * 4;
     L.bytes = o;
     return L;
 }
 
 // Byte offsets of the GEMM-structured scan's LDS regions.
 struct GemmLayout {
-    uint32_t ring, norms, list, qn, gb, lmk, nu, sq, sk, si, bytes;
+    uint32_t ring, norms, stage, sup, bytes;
 };
 
-__host__ __device__ inline GemmLayout gemm_layout(int k)
+__host__ __device__ inline GemmLayout gemm_layout(int tpq)
 {
     GemmLayout L;
     uint32_t o = 0;
-    L.ring = o;    // [GM_SLOTS][2 * GM_ROWS / 8][64] row and request fragments of a stage
-    o += (uint32_t)GM_SLOTS * (2 * GM_ROWS / 8) * WAVE * 16;
+    L.ring = o;    // [GM_SLOTS][GM_SLOT_LOADS][64] row and request fragments of a stage
+    o += (uint32_t)GM_SLOTS * GM_SLOT_LOADS * WAVE * 16;
     L.norms = o;   // [2][GM_ROWS] |x|^2 of a macro tile's rows
     o += 2u * GM_ROWS * 4;
-    L.list = o;    // [GM_QRY][k] (key << 32 | index), the workgroup's candidate lists
-    o += (uint32_t)GM_QRY * k * 8;
-    L.qn = o;      // [GM_QRY] |q|^2
-    o += GM_QRY * 4;
-    L.gb = o;      // [GM_QRY] snapshot of the shared bound
-    o += GM_QRY * 4;
-    L.lmk = o;     // [GM_QRY] an upper bound of each list's largest key
-    o += GM_QRY * 4;
-    L.nu = o;      // [GM_QRY] each request's candidate threshold on the accumulators
-    o += GM_QRY * 4;
-    L.sq = o;      // [waves][GM_STAGE] staged candidates: tile request,
-    o += GM_WAVES * GM_STAGE * 4;
-    L.sk = o;      //   distance key,
-    o += GM_WAVES * GM_STAGE * 4;
-    L.si = o;      //   bank row
-    o += GM_WAVES * GM_STAGE * 4;
+    L.stage = o;   // [64 * tpq][GM_EPS] a macro tile's maxima
+    o += 64u * tpq * GM_EPS * 4;
+    L.sup = o;     // [64 * tpq][GM_HOLD] maxima of the last macro tiles
+    o += 64u * tpq * GM_HOLD * 4;
     L.bytes = o;
     return L;
 }
 
-// The bank-scan launchers, one translation unit per element type and
-// k-step raggedness (they are the bulk of the compile time), and one per row
-// length for the query-resident scan.
-hipError_t launch_scan_res_bf16(const KnnPlan &p, const MinScanArgs &a, hipStream_t s);
-hipError_t launch_scan_res_f32(const KnnPlan &p, const MinScanArgs &a, hipStream_t s);
+// The bank-scan launchers (LDS-resident: one translation unit per element
+// type; query-resident: one per row length).
+hipError_t launch_scan_res_bf16(const KnnPlan &p, const ScanArgs &a, hipStream_t s);
+hipError_t launch_scan_res_f32(const KnnPlan &p, const ScanArgs &a, hipStream_t s);
 hipError_t launch_scan_gemm(const KnnPlan &p, const ScanArgs &a, hipStream_t s);
 hipError_t launch_scan_rq(const KnnPlan &p, const ScanArgs &a, hipStream_t s);
 hipError_t launch_scan_rq12(const KnnPlan &p, const ScanArgs &a, hipStream_t s);
 hipError_t launch_scan_rq16(const KnnPlan &p, const ScanArgs &a, hipStream_t s);
 hipError_t launch_scan_rq24(const KnnPlan &p, const ScanArgs &a, hipStream_t s);
 hipError_t launch_scan_rq32(const KnnPlan &p, const ScanArgs &a, hipStream_t s);
-hipError_t launch_scan_bf16(const KnnPlan &p, const ScanArgs &a, hipStream_t s);
-hipError_t launch_scan_bf16_ragged(const KnnPlan &p, const ScanArgs &a, hipStream_t s);
-hipError_t launch_scan_f32(const KnnPlan &p, const ScanArgs &a, hipStream_t s);
-hipError_t launch_scan_f32_ragged(const KnnPlan &p, const ScanArgs &a, hipStream_t s);
 
 namespace {
 
@@ -259,6 +198,14 @@ __device__ __forceinline__ i32x4 buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_
 
 constexpr uint32_t OFF_NONE = 0x80000000u;   // a buffer offset past any resource
 
+// 16 bytes per lane, not kept in the caches for their own sake (256 requests
+// over 1,000,000 x 768: 425 us a batch for 434 with plain stores).
+__device__ __forceinline__ void store16_nt(__amdgpu_buffer_rsrc_t r, uint32_t voffset,
+                                           const f32x4 &v)
+{
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, v), r, (int)voffset, 0, 2);
+}
+
 // Global -> LDS load of 16 bytes per lane through the buffer resource: lane l's
 // bytes land at dst + 16*l (dst is the same for the whole wave); a lane whose
 // offset falls outside the resource writes zeros. Completion is counted by
@@ -295,15 +242,6 @@ __device__ __forceinline__ void static_for(F &&f)
     }
 }
 
-// Workgroup barrier that orders LDS only (waits for this wave's LDS traffic),
-// leaving global loads in flight across it.
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // Workgroup barrier once this wave's LDS reads have returned, with no release
 // fence (which would also wait for the wave's global-to-LDS loads still in
 // flight); the acquire fence keeps later LDS accesses below it.
@@ -314,31 +252,9 @@ __device__ __forceinline__ void stream_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-__device__ __forceinline__ uint32_t lds_load_relaxed(const uint32_t *p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-__device__ __forceinline__ void lds_store_relaxed(uint32_t *p, uint32_t v)
-{
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
 __device__ __forceinline__ uint64_t pack(uint32_t key, int32_t idx)
 {
     return ((uint64_t)key << 32) | (uint32_t)idx;
-}
-
-// 64-bit compare-and-swap in LDS; true when *p held `expect` and now holds `v`.
-__device__ __forceinline__ bool lds_cas64(uint64_t *p, uint64_t expect, uint64_t v)
-{
-    return atomicCAS((unsigned long long *)p, (unsigned long long)expect,
-                     (unsigned long long)v) == (unsigned long long)expect;
-}
-
-__device__ __forceinline__ uint64_t lds_load64(const uint64_t *p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // Weight of a neighbour at squared distance d2 in the distance-weighted
@@ -386,27 +302,6 @@ __device__ __forceinline__ void average_labels(const int32_t *nbr, const float *
     }
     *q_out = bad ? __builtin_nanf("") : sq / sw;
     *l_out = bad ? __builtin_nanf("") : sl / sw;
-}
-
-// Inclusive prefix sum over the wave.
-__device__ __forceinline__ int wave_incl_scan(int v)
-{
-    const int lane = lane_id();
-#pragma unroll
-    for (int m = 1; m < WAVE; m <<= 1) {
-        const int o = __shfl_up(v, m);
-        if (lane >= m)
-            v += o;
-    }
-    return v;
-}
-
-__device__ __forceinline__ int wave_sum_int(int v)
-{
-#pragma unroll
-    for (int m = 1; m < WAVE; m <<= 1)
-        v += __shfl_xor(v, m);
-    return v;
 }
 
 }  // namespace

@@ -3,15 +3,26 @@
 
 namespace rb {
 
-hipError_t launch_scan_gemm(const KnnPlan &p, const ScanArgs &a, hipStream_t s)
+namespace {
+
+template <int TPQ>
+hipError_t launch_gemm(const KnnPlan &p, const ScanArgs &a, hipStream_t s)
 {
-    hipError_t e = hipFuncSetAttribute((const void *)gemm_scan_kernel,
+    auto kern = gemm_scan_kernel<TPQ>;
+    hipError_t e = hipFuncSetAttribute((const void *)kern,
                                        hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)p.lds_bytes);
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL(gemm_scan_kernel, dim3(p.grid), dim3(GM_WAVES * WAVE), p.lds_bytes, s, a);
+    hipLaunchKernelGGL(kern, dim3(p.grid), dim3(GM_WAVES * WAVE), p.lds_bytes, s, a);
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_scan_gemm(const KnnPlan &p, const ScanArgs &a, hipStream_t s)
+{
+    return p.qw == 2 ? launch_gemm<2>(p, a, s) : launch_gemm<4>(p, a, s);
 }
 
 }  // namespace rb

@@ -24,7 +24,7 @@ namespace {
 // selection takes the k best super tiles and recomputes the few row tiles
 // that matter.
 template <int DT, int NG>
-__global__ __launch_bounds__(RES_WAVES * WAVE, 1) void res_scan_kernel(const MinScanArgs A)
+__global__ __launch_bounds__(RES_WAVES * WAVE, 1) void res_scan_kernel(const ScanArgs A)
 {
     constexpr int VEC = Elem<DT>::VEC, ESZ = Elem<DT>::ESZ;
     constexpr int KS = 4 * VEC;              // elements of one k-step
@@ -119,8 +119,8 @@ __global__ __launch_bounds__(RES_WAVES * WAVE, 1) void res_scan_kernel(const Min
     for (int v = 0; v < NQ; ++v) {
         const int g = 4 * v + gsw, q = q0 + g * 16 + col;
         own[v] = g < NG && q < A.B;
-        sup[v] = A.sup + (size_t)(own[v] ? q : 0) * A.n_sup + s0;
-        ent[v] = A.ent + ((size_t)(own[v] ? q : 0) * A.n_sup + s0) * A.eps;
+        sup[v] = A.m.sup + s0 + (own[v] ? q : 0) * A.m.sup_q;
+        ent[v] = A.m.ent + t0 + (own[v] ? q : 0) * A.m.ent_q;
     }
 
     f32x4 acc[NG];
@@ -152,7 +152,7 @@ __global__ __launch_bounds__(RES_WAVES * WAVE, 1) void res_scan_kernel(const Min
             for (int g = 0; g < NG; ++g) {
                 const int q = q0 + g * 16 + col;
                 if (q < A.B)
-                    *(f32x4 *)(A.acc + (size_t)q * A.ld_acc + (t0 + tile) * 16 + jg * 4) = acc[g];
+                    *(f32x4 *)(A.acc + ((size_t)(t0 + tile) * A.B + q) * 16 + jg * 4) = acc[g];
             }
         }
         const bool last = es == A.eps - 1 || tile == n_tiles - 1;
@@ -221,7 +221,7 @@ __global__ __launch_bounds__(RES_WAVES * WAVE, 1) void res_scan_kernel(const Min
 }
 
 template <int DT, int NG>
-hipError_t launch_res_scan(const KnnPlan &p, const MinScanArgs &a, hipStream_t s)
+hipError_t launch_res_scan(const KnnPlan &p, const ScanArgs &a, hipStream_t s)
 {
     auto kern = res_scan_kernel<DT, NG>;
     hipError_t e = hipFuncSetAttribute((const void *)kern,
@@ -234,7 +234,7 @@ hipError_t launch_res_scan(const KnnPlan &p, const MinScanArgs &a, hipStream_t s
 }
 
 template <int DT>
-hipError_t launch_res(const KnnPlan &p, const MinScanArgs &a, hipStream_t s)
+hipError_t launch_res(const KnnPlan &p, const ScanArgs &a, hipStream_t s)
 {
     switch (p.ng) {
     case 1: return launch_res_scan<DT, 1>(p, a, s);

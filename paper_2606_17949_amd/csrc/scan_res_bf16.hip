@@ -3,7 +3,7 @@
 
 namespace rb {
 
-hipError_t launch_scan_res_bf16(const KnnPlan &p, const MinScanArgs &a, hipStream_t s)
+hipError_t launch_scan_res_bf16(const KnnPlan &p, const ScanArgs &a, hipStream_t s)
 {
     return launch_res<1>(p, a, s);
 }

@@ -50,11 +50,14 @@ __device__ __forceinline__ uint32_t rq_chunk(int ri, int rg, int c)
 // into SPB stages, which global-to-LDS loads bring in whole 128-byte lines
 // into a ring of S slots, S - 1 stages ahead of the MFMAs, so
 // that every bank byte crosses from L2 into the compute unit once and serves
-// all the waves. Each wave keeps, per owned query, its own list of the k
-// best candidates of its rows of the chunk (no other wave touches it) and its
-// own candidate threshold; the lists start from the shared bound the seed
-// pass computed. A chunk therefore leaves RS lists per query (per pass, when
-// the scan takes the rows of every chunk in two launches).
+// all the waves. A block leaves, per request and row tile, the largest
+// <q, x> - |x|^2/2 of the tile's rows: a few maxima over registers and lane
+// rows, which wait in LDS until a super tile (RQ_EPS row tiles) is complete
+// and then go out, 64 bytes per request and all requests of a super tile side
+// by side (request by request, as many DRAM pages took them and a batch of 64
+// over 1,000,000 x 768 took 305 us for 286), with the super tile's maximum. No
+// bound, list or candidate test holds a wave up between two blocks (one at a
+// time, the candidates of the bounded scan took about a tenth of it).
 template <int NKS, int QW, int RS, int SPB, int S>
 __global__ __launch_bounds__(RQ_WAVES * WAVE, 1) void rq_scan_kernel(const ScanArgs A)
 {
@@ -65,6 +68,7 @@ __global__ __launch_bounds__(RQ_WAVES * WAVE, 1) void rq_scan_kernel(const ScanA
     constexpr int QPW = QW * 16;                // queries of one wave
     constexpr int NQS = RQ_WAVES / RS;          // query slots
     constexpr int TW = TT / RS;                 // tiles of a block each wave takes
+    constexpr int BPS = RQ_EPS / TT;            // blocks of a super tile
     static_assert(NKS % SPB == 0 && F % RQ_WAVES == 0, "whole stages, equal shares");
     static_assert(KSTG % 2 == 0 && TT == 2, "stages of whole k-step pairs, 32-row blocks");
     // With four query groups a wave holds 192 registers of query fragments;
@@ -74,15 +78,16 @@ __global__ __launch_bounds__(RQ_WAVES * WAVE, 1) void rq_scan_kernel(const ScanA
     constexpr int TA = TSEQ ? 1 : TW;           // tiles whose accumulators are live together
     static_assert(!TSEQ || SPB == 1, "tiles one after the other within one stage");
     static_assert(RS == 1 || RS == 2, "one or two row halves");
+    constexpr int NM = TA * QW;                 // maxima of one block (TSEQ: of one tile)
+    static_assert(NM == 1 || NM == 2 || NM == 4, "one register holds a block's results");
     static_assert(RQ_ROWS <= WAVE, "one norm per lane");
 
     extern __shared__ __align__(16) uint8_t smem[];
-    const RqLayout L = rq_layout(A.k, QW, KSTG, S);
+    const RqLayout L = rq_layout(QW, RS, KSTG, S);
     i32x4 *ring = (i32x4 *)(smem + L.ring);              // [S][F][64] fragments
     float *nslot = (float *)(smem + L.norms);            // [S][64] |x|^2 of a block's rows
-    uint64_t *lists = (uint64_t *)(smem + L.lists);      // [waves][QPW][k]
-    float *qn_l = (float *)(smem + L.qinfo);             // [waves][QPW] |q|^2
-    uint32_t *tau_l = (uint32_t *)(smem + L.qinfo) + RQ_WAVES * QPW;   // [waves][QPW] bound
+    float *stg = (float *)(smem + L.stage);              // [RS][NQS * QPW][RQ_EPS] maxima
+    float *sst = (float *)(smem + L.sup);                // [NQS * QPW][rq_hold] super tiles' maxima
 
     const int c = blockIdx.x;
     if (c >= A.n_chunks)
@@ -92,13 +97,11 @@ __global__ __launch_bounds__(RQ_WAVES * WAVE, 1) void rq_scan_kernel(const ScanA
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int slot_q = wave % NQS, half = wave / NQS;   // query slot, row half
     const int col = lane & 15, jg = lane >> 4;
-    const int k = A.k;
     const uint32_t rowb = (uint32_t)A.d * 2;
-    // rows [row_lo, row_hi) of chunk c
-    const long cbeg = (long)c * A.rows_per_chunk;
-    const long rbeg = cbeg + A.row_lo;
-    const long rend = min((long)A.N, cbeg + min(A.rows_per_chunk, A.row_hi));
-    const int nrows = rend > rbeg ? (int)(rend - rbeg) : 0;
+    const long cbeg = (long)c * A.rows_per_chunk;        // of the launch's rows
+    const long nleft = min(A.rows - cbeg, A.rows_per_chunk);
+    const int nrows = nleft > 0 ? (int)nleft : 0;
+    const long rbeg = A.row0 + cbeg;
     const int n_blk = (nrows + RQ_ROWS - 1) / RQ_ROWS;
     const int n_stg = n_blk * SPB;
     const int qw0 = slot_q * QPW;
@@ -115,35 +118,6 @@ __global__ __launch_bounds__(RQ_WAVES * WAVE, 1) void rq_scan_kernel(const ScanA
         for (int s = 0; s < NKS; ++s)
             qf[g][s] = buffer_load16(rq, base + s * KSTEP_BYTES);
     }
-    // |q|^2 and the shared bound from the seed pass of the wave's queries, in
-    // LDS (they are needed only for candidates)
-    float *qn_w = qn_l + wave * QPW;
-    uint32_t *tau_w = tau_l + wave * QPW;
-    for (int i = lane; i < QPW; i += WAVE) {
-        const int q = qw0 + i;
-        qn_w[i] = q < A.B ? A.qn[q] : 0.f;
-        tau_w[i] = q < A.B ? A.tau[q] : KEY_NONE;
-    }
-    // Filter threshold on the accumulators for bound key tk: a value is a
-    // candidate if acc >= nu (a superset of distance <= the bound).
-    auto nu_of = [](uint32_t tk, float qn, bool valid) -> float {
-        const float th = key2f(tk);
-        const float v = 0.5f * (qn - th);
-        const float nu = v - ldexpf(fabsf(qn) + fabsf(th) + fabsf(v), -21);
-        return !valid ? INFINITY : tk == KEY_NONE ? -FLT_MAX : nu;
-    };
-    // the threshold of the lane's query of each group
-    auto nu_q = [&](int i, uint32_t listmax) -> float {
-        return nu_of(min(tau_w[i], listmax), qn_w[i], qw0 + i < A.B);
-    };
-    float nu[QW];
-#pragma unroll
-    for (int g = 0; g < QW; ++g)
-        nu[g] = nu_q(g * 16 + col, KEY_NONE);
-    // the wave's lists; empty slots hold distinct sentinels above every entry
-    uint64_t *wl = lists + (size_t)wave * QPW * k;
-    for (int e = lane; e < QPW * k; e += WAVE)
-        wl[e] = pack(KEY_NONE, IDX_NONE - e % k);
 
     // ---- stage z (block z / SPB, its k-steps from (z % SPB) * KSTG) into
     // slot z % S: this wave's FPW fragments and, with a block's first stage,
@@ -175,32 +149,6 @@ __global__ __launch_bounds__(RQ_WAVES * WAVE, 1) void rq_scan_kernel(const ScanA
                  lane < RQ_ROWS ? (uint32_t)(bz * RQ_ROWS + lane) * 4u : OFF_NONE);
     };
 
-    // Insert (ckey, cidx) into the list of the wave's query g*16 + cq (a wave
-    // call; the list keeps the k smallest pairs inserted so far) and lower
-    // that query's threshold to the list's new largest key.
-    auto insert = [&](int g, int cq, uint32_t ckey, int32_t cidx) {
-        uint64_t *li = wl + (g * 16 + cq) * k;
-        const uint64_t cand = pack(ckey, cidx);
-        uint64_t v = lane < k ? li[lane] : 0ull;
-        uint32_t hi = (uint32_t)(v >> 32), lo = (uint32_t)v;
-        reduce_max_pair<WAVE>(hi, lo);
-        const uint64_t mx = pack(hi, (int32_t)lo);
-        if (cand >= mx)
-            return;
-        const int pos = __builtin_ctzll(ballot(lane < k && v == mx));
-        if (lane == pos) {
-            li[lane] = cand;
-            v = cand;
-        }
-        hi = (uint32_t)(v >> 32);
-        lo = (uint32_t)v;
-        reduce_max_pair<WAVE>(hi, lo);   // hi: an upper bound of the list's largest key
-#pragma unroll
-        for (int gg = 0; gg < QW; ++gg)
-            if (gg == g && col == cq)
-                nu[gg] = nu_q(gg * 16 + col, hi);
-    };
-
     // ---- pipeline prologue: stages 0 .. S-2
 #pragma unroll
     for (int z = 0; z < S - 1; ++z) {
@@ -213,16 +161,23 @@ __global__ __launch_bounds__(RQ_WAVES * WAVE, 1) void rq_scan_kernel(const ScanA
     // the block tile of wave tile t
     auto tile_of = [&](int t) { return RS == 2 ? half : t; };
     // accumulators of wave tiles t0 .. t0+TA-1 from -|x|^2/2 of their rows
-    // (-inf for rows past the chunk), the norms of block b in norm slot `slot`
+    // (past the chunk -inf, or no number in a tile with no row of it), the
+    // norms of block b in norm slot `slot`
     auto init_acc = [&](f32x4(&ac)[TA][QW], int slot, int b, int t0) {
 #pragma unroll
         for (int t = 0; t < TA; ++t) {
-            const int tt = tile_of(t0 + t);
+            const int tt = tile_of(t0 + t), r0 = b * RQ_ROWS + tt * 16;
             const f32x4 xn = *(const f32x4 *)(nslot + slot * WAVE + tt * 16 + jg * 4);
             f32x4 h;
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                h[e] = b * RQ_ROWS + tt * 16 + jg * 4 + e < nrows ? -0.5f * xn[e] : -INFINITY;
+                h[e] = -0.5f * xn[e];
+            if (r0 + 16 > nrows) {   // (the chunk's last block only)
+                const float past = r0 < nrows ? -INFINITY : __builtin_nanf("");
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    h[e] = r0 + jg * 4 + e < nrows ? h[e] : past;
+            }
 #pragma unroll
             for (int g = 0; g < QW; ++g)
                 ac[t][g] = h;
@@ -264,45 +219,102 @@ __global__ __launch_bounds__(RQ_WAVES * WAVE, 1) void rq_scan_kernel(const ScanA
                 __builtin_amdgcn_sched_group_barrier(0x100, TA, 0);
         });
     };
-    // candidates of wave tiles t0 .. t0+TA-1 of block b: acc = -|x|^2/2 +
-    // <q, x>, distance |q|^2 - 2*acc; a value passes if acc >= nu of its query
-    auto test_tiles = [&](f32x4(&ac)[TA][QW], int b, int t0) {
-        static_for<0, QW>([&](auto G) {
-            constexpr int g = decltype(G)::value;
-            float m = -INFINITY;
-#pragma unroll
-            for (int t = 0; t < TA; ++t)
-                m = fmaxf(m, fmaxf(fmaxf(ac[t][g][0], ac[t][g][1]),
-                                   fmaxf(ac[t][g][2], ac[t][g][3])));
-            if (!ballot(m >= nu[g]))
-                return;
-            const float qg = qn_w[g * 16 + col];
-#pragma unroll
-            for (int t = 0; t < TA; ++t) {
-                const int tt = tile_of(t0 + t);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float a = ac[t][g][e];
-                    uint64_t mk = ballot(a >= nu[g]);
-                    const uint32_t key = f2key(fmaf(-2.f, a, qg));
-                    const int32_t idx = (int32_t)(rbeg + b * RQ_ROWS + tt * 16 + jg * 4 + e);
-                    while (mk) {
-                        const int src = __builtin_ctzll(mk);
-                        mk &= mk - 1;
-                        insert(g, src & 15, (uint32_t)__builtin_amdgcn_readlane((int)key, src),
-                               __builtin_amdgcn_readlane(idx, src));
-                    }
-                }
-            }
+    // ---- results. What emit and flush derive from the lane is computed each
+    // time, from a lane index the compiler cannot hoist it from: held through
+    // the MFMA loops beside 192 registers of requests, it takes the registers
+    // that keep bank fragments in flight.
+    auto fresh_lane = [&]() -> int {
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        return l;
+    };
+    constexpr int STG_BUF = NQS * QPW * RQ_EPS;   // floats of one staging buffer
+    auto stg_of = [&](int sl) { return RS == 2 ? (sl & 1) * STG_BUF : 0; };
+    auto emit = [&](f32x4(&ac)[TA][QW], int b, int t0) {
+        float m[4];
+        static_for<0, 4>([&](auto I) {
+            constexpr int i = decltype(I)::value, j = NM == 4 ? i : NM == 2 ? i / 2 : 0;
+            m[i] = max4(ac[j / QW][j % QW]);
         });
+        const float r = rows_max4(m[0], m[1], m[2], m[3]);
+        // lane row lr holds maximum (wave tile, group) = (i / QW, i % QW), i =
+        // lr with its two bits swapped (NM = 4) or lr % NM
+        const int l = fresh_lane(), lr = l >> 4;
+        const int i = NM == 4 ? (lr >> 1) | ((lr & 1) << 1) : lr % NM;
+        const int e = (b % BPS) * TT + tile_of(t0 + i / QW);
+        if (lr < NM)
+            stg[stg_of(b / BPS) + (slot_q * QPW + (i % QW) * 16 + (l & 15)) * RQ_EPS + e] = r;
+    };
+    // entries of blocks past the chunk in its last super tile
+    auto fill_past = [&]() {
+        for (int b = n_blk; b % BPS != 0; ++b)
+#pragma unroll
+            for (int t = 0; t < TT; ++t)
+                if (RS == 1 || t == half)
+                    for (int q = lane; q < QPW; q += WAVE)
+                        stg[stg_of(b / BPS) + (slot_q * QPW + q) * RQ_EPS + (b % BPS) * TT + t] =
+                            __builtin_nanf("");
+    };
+    // super tile sl of the chunk from LDS to the workspace: 16 requests per
+    // instruction, four lanes of four entries each. The super tiles' maxima
+    // wait in LDS for HOLD of them (most chunks have no more) and go out
+    // request by request, because the selection reads all of a request's: a
+    // 16-byte piece every fourth super tile cost 24 us of 434 at 256 requests,
+    // the scattered stores holding up the loads behind them. RS = 1: each wave
+    // its own requests; else the waves share them out (the first NQS * QW).
+    constexpr int HOLD = rq_hold(QW, RS);
+    constexpr int GPW = RS == 1 ? QW : (NQS * QW + RQ_WAVES - 1) / RQ_WAVES;   // groups per wave
+    const bool flushes = RS == 1 ? active : wave * GPW < NQS * QW;
+    const int fq0 = RS == 1 ? qw0 : wave * GPW * 16;
+    const long sup0 = (long)c * A.sup_per_chunk;
+    int settle = 0;   // stages until this wave's last flush no longer counts
+    // maxima of super tiles s0 .. s1-1 (one HOLD) of this wave's requests;
+    // past the last one taken, no numbers
+    auto put_sup = [&](int s0, int s1) {
+        for (int i = fresh_lane(); i < GPW * 16 * HOLD; i += WAVE) {
+            const int q = fq0 + i / HOLD, j = i % HOLD;
+            if (q < A.B && s0 + j < A.sup_per_chunk)
+                A.m.sup[sup0 + s0 + j + q * A.m.sup_q] =
+                    s0 + j < s1 ? sst[q * HOLD + j] : __builtin_nanf("");
+        }
+    };
+    auto flush = [&](int sl) {
+        static_assert(RQ_EPS == 16, "four lanes of four entries");
+        const int l = fresh_lane(), part = l & 3, lq = l >> 2;
+        const float *src = stg + stg_of(sl) + (fq0 + lq) * RQ_EPS + part * 4;
+        float *const ent = A.m.ent + (sup0 + sl) * A.m.ent_s;
+        // (out-of-range lanes fall outside the resource, so that every flush
+        // is GPW stores at least)
+#pragma unroll
+        for (int i = 0; i < GPW; ++i) {
+            const int q = fq0 + 16 * i + lq;
+            const f32x4 v = *(const f32x4 *)(src + 16 * i * RQ_EPS);
+            float m = max4(v);
+            m = fmaxf(m, dpp<0xb1>(m));   // quad_perm [1,0,3,2]
+            m = fmaxf(m, dpp<0x4e>(m));   // quad_perm [2,3,0,1]
+            if (part == 0)
+                sst[q * HOLD + sl % HOLD] = m;
+            store16_nt(make_rsrc(ent + (long)(fq0 + 16 * i) * A.m.ent_q, 0x7fffffffu),
+                       q < A.B ? (uint32_t)(lq * A.m.ent_q + part * 4) * 4u : OFF_NONE, v);
+        }
+        settle = S - 1;
+        if (sl % HOLD == HOLD - 1)
+            put_sup(sl + 1 - HOLD, sl + 1);
     };
     // this wave's part of stage z has landed once at most FPW*(S-2) loads are
-    // outstanding (the fragment loads of the S-2 stages issued after it); the
-    // barrier then tells that every wave's part has and that every wave is
+    // outstanding, the fragment loads of the S-2 stages issued after it, and
+    // the stores of a flush where those came after it too (stores count like
+    // loads, in order; waiting as if they did not would wait for later loads);
+    // the barrier then tells that every wave's part has and that every wave is
     // done with stage z - 1, whose slot the next load reuses
     auto next_stage = [&](int z) {
         __builtin_amdgcn_sched_barrier(0);
-        wait_vmcnt<FPW * (S - 2)>();
+        if (settle > 0) {
+            wait_vmcnt<FPW * (S - 2) + GPW>();
+            --settle;
+        } else {
+            wait_vmcnt<FPW * (S - 2)>();
+        }
         stream_barrier();
         issue(z + S - 1);
         __builtin_amdgcn_sched_barrier(0);
@@ -311,8 +323,7 @@ __global__ __launch_bounds__(RQ_WAVES * WAVE, 1) void rq_scan_kernel(const ScanA
     int z = 0;   // the stage being consumed
     for (int b = 0; b < n_blk; ++b) {
         if constexpr (TSEQ) {
-            // one stage per block; its tiles one after the other, each with
-            // its candidate test
+            // one stage per block; its tiles one after the other
             next_stage(z);
             const int slot = z % S;
             if (active) {
@@ -320,131 +331,48 @@ __global__ __launch_bounds__(RQ_WAVES * WAVE, 1) void rq_scan_kernel(const ScanA
                     f32x4 acc[TA][QW];
                     init_acc(acc, slot, b, T.value);
                     mfma_tiles(Int<0>{}, acc, slot, T.value);
-                    test_tiles(acc, b, T.value);
+                    emit(acc, b, T.value);
                 });
             }
             ++z;
         } else {
-            f32x4 acc[TW][QW];
+            f32x4 acc[TA][QW];
             static_for<0, SPB>([&](auto ST) {
-                constexpr int st = decltype(ST)::value;
                 next_stage(z);
                 const int slot = z % S;
-                if constexpr (st == 0) {
-                    // the accumulators start from -|x|^2/2 of their rows (-inf
-                    // for rows past the chunk)
-#pragma unroll
-                    for (int t = 0; t < TW; ++t) {
-                        const int tt = RS == 2 ? half : t;
-                        const f32x4 xn =
-                            *(const f32x4 *)(nslot + slot * WAVE + tt * 16 + jg * 4);
-                        f32x4 h;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            h[e] = b * RQ_ROWS + tt * 16 + jg * 4 + e < nrows ? -0.5f * xn[e]
-                                                                             : -INFINITY;
-#pragma unroll
-                        for (int g = 0; g < QW; ++g)
-                            acc[t][g] = h;
-                    }
+                if constexpr (decltype(ST)::value == 0) {
+                    // two halves' entries of the super tile before are in LDS
+                    if (RS == 2 && flushes && b > 0 && b % BPS == 0)
+                        flush(b / BPS - 1);
+                    init_acc(acc, slot, b, 0);
                 }
-                if (active) {
-                    // the lane's A fragment of tile tt, k-step j of the stage:
-                    // row col of the tile, quarter jg, at load (j/2)*4 + rg
-                    const i32x4 *fr = ring + slot * F * WAVE;
-                    uint32_t fbase[TW][2];
-#pragma unroll
-                    for (int t = 0; t < TW; ++t) {
-                        const int tt = RS == 2 ? half : t;
-                        const int ri = col & 7, rg = tt * 2 + (col >> 3);
-#pragma unroll
-                        for (int h = 0; h < 2; ++h)
-                            fbase[t][h] = (uint32_t)rg * WAVE + rq_chunk(ri, rg, 4 * h + jg);
-                    }
-                    static_for<0, KSTG>([&](auto J) {
-                        constexpr int j = decltype(J)::value, s = st * KSTG + j;
-                        i32x4 a[TW];
-#pragma unroll
-                        for (int t = 0; t < TW; ++t)
-                            a[t] = fr[(j / 2) * 4 * WAVE + fbase[t][j & 1]];
-#pragma unroll
-                        for (int t = 0; t < TW; ++t)
-#pragma unroll
-                            for (int g = 0; g < QW; ++g)
-                                acc[t][g] = mfma_step<1>(a[t], qf[g][s], acc[t][g]);
-                    });
-                    // two k-steps of fragment reads in flight: the reads of
-                    // k-steps 0 and 1, then per k-step its MFMAs and the
-                    // reads two ahead
-                    __builtin_amdgcn_sched_group_barrier(0x100, 2 * TW, 0);
-                    static_for<0, KSTG>([&](auto J) {
-                        __builtin_amdgcn_sched_group_barrier(0x008, TW * QW, 0);
-                        if constexpr (decltype(J)::value + 2 < KSTG)
-                            __builtin_amdgcn_sched_group_barrier(0x100, TW, 0);
-                    });
-                }
+                if (active)
+                    mfma_tiles(ST, acc, slot, 0);
                 ++z;
             });
-            if (!active)
-                continue;
-            // ---- candidates of the block: acc = -|x|^2/2 + <q, x>, distance
-            // |q|^2 - 2*acc; a value passes if acc >= nu of its query
-            static_for<0, QW>([&](auto G) {
-                constexpr int g = decltype(G)::value;
-                float m = -INFINITY;
-#pragma unroll
-                for (int t = 0; t < TW; ++t)
-                    m = fmaxf(m, fmaxf(fmaxf(acc[t][g][0], acc[t][g][1]),
-                                       fmaxf(acc[t][g][2], acc[t][g][3])));
-                if (!ballot(m >= nu[g]))
-                    return;
-                const float qg = qn_w[g * 16 + col];
-#pragma unroll
-                for (int t = 0; t < TW; ++t) {
-                    const int tt = RS == 2 ? half : t;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float a = acc[t][g][e];
-                        uint64_t mk = ballot(a >= nu[g]);
-                        const uint32_t key = f2key(fmaf(-2.f, a, qg));
-                        const int32_t idx =
-                            (int32_t)(rbeg + b * RQ_ROWS + tt * 16 + jg * 4 + e);
-                        while (mk) {
-                            const int src = __builtin_ctzll(mk);
-                            mk &= mk - 1;
-                            insert(g, src & 15,
-                                   (uint32_t)__builtin_amdgcn_readlane((int)key, src),
-                                   __builtin_amdgcn_readlane(idx, src));
-                        }
-                    }
-                }
-            });
+            if (active)
+                emit(acc, b, 0);
         }
+        if (RS == 1 && flushes && b % BPS == BPS - 1)
+            flush(b / BPS);
     }
-
-    // ---- the wave's lists -> workspace [B][n_lists][k], list list_base +
-    // c*RS + half of each query, valid entries first (no global-to-LDS load
-    // may still be in flight when the workgroup ends)
+    // the last super tile, and those of the chunk's share that it has no rows for
+    fill_past();
+    if (RS == 2) {
+        stream_barrier();
+        if (flushes && n_blk > 0)
+            flush((n_blk - 1) / BPS);
+    } else if (flushes && n_blk % BPS != 0) {
+        flush(n_blk / BPS);
+    }
+    if (flushes) {
+        // maxima that still wait, and no numbers in the rest of the share
+        const int done = (n_blk + BPS - 1) / BPS;
+        for (int s0 = done / HOLD * HOLD; s0 < A.sup_per_chunk; s0 += HOLD)
+            put_sup(s0, done);
+    }
+    // (no global-to-LDS load may still be in flight when the workgroup ends)
     wait_vmcnt<0>();
-    if (!active)
-        return;
-    for (int i = 0; i < QPW; ++i) {
-        const int q = qw0 + i;
-        if (q >= A.B)
-            break;
-        const uint64_t v = lane < k ? wl[i * k + lane] : pack(KEY_NONE, 0);
-        const uint32_t key = (uint32_t)(v >> 32);
-        const bool valid = key != KEY_NONE;
-        const uint64_t m = ballot(valid);
-        const size_t o = (size_t)q * A.n_lists + A.list_base + c * RS + half;
-        if (valid) {
-            const int pos = mbcnt(m);
-            A.ckey[o * k + pos] = key;
-            A.cidx[o * k + pos] = (int32_t)(uint32_t)v;
-        }
-        if (lane == 0)
-            A.ccnt[o] = popc(m);
-    }
 }
 
 template <int NKS, int QW, int RS, int SPB, int S>
@@ -459,33 +387,16 @@ hipError_t launch_rq_scan(const ScanArgs &a, size_t lds, int grid, hipStream_t s
     return hipGetLastError();
 }
 
-// The instantiations of one row length: the (QW, RS) and (SPB, S) the plan
-// may choose for it (plan_knn's tables; QW * NKS * 4 registers of query
-// fragments stay within 192).
-template <int NKS, int QW, int RS>
-hipError_t launch_rq_stages(const KnnPlan &p, const ScanArgs &a, hipStream_t s)
-{
-    if constexpr (NKS == 12) {
-        if (p.spb == 1 && p.stages == 4)
-            return launch_rq_scan<NKS, QW, RS, 1, 4>(a, p.lds_bytes, p.grid, s);
-    } else {
-        if (p.spb == 2 && p.stages == 4)
-            return launch_rq_scan<NKS, QW, RS, 2, 4>(a, p.lds_bytes, p.grid, s);
-        if (p.spb == 2 && p.stages == 2)
-            return launch_rq_scan<NKS, QW, RS, 2, 2>(a, p.lds_bytes, p.grid, s);
-    }
-    if constexpr (NKS != 32)
-        if (p.spb == 1 && p.stages == 2)
-            return launch_rq_scan<NKS, QW, RS, 1, 2>(a, p.lds_bytes, p.grid, s);
-    return hipErrorInvalidValue;
-}
-
+// The instantiations of one row length: the (QW, RS) the plan may choose for
+// it (plan_knn's tables; QW * NKS * 4 registers of query fragments stay
+// within 192).
 template <int NKS>
 hipError_t launch_rq_nks(const KnnPlan &p, const ScanArgs &a, hipStream_t s)
 {
+    constexpr int SPB = rq_spb(NKS), S = RQ_SLOTS;
 #define RB_RQ(QW_, RS_)                                                                          \
-    if (p.qw == QW_ && p.rs == RS_)                                                             \
-        return launch_rq_stages<NKS, QW_, RS_>(p, a, s);
+    if (p.qw == QW_ && p.rs == RS_)                                                              \
+        return launch_rq_scan<NKS, QW_, RS_, SPB, S>(a, p.lds_bytes, p.grid, s);
     if constexpr (NKS == 12) {
         RB_RQ(1, 2)
         RB_RQ(2, 2)

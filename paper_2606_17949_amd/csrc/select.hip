@@ -102,8 +102,10 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int k = A.k;
     const uint32_t rowb = (uint32_t)A.d * ESZ;
-    const float *sup = A.sup + (size_t)b * A.n_sup;
-    const float *ent = A.ent + (size_t)b * A.n_sup * A.eps;
+    auto sup = [&](long i) -> float { return A.m.sup[i + b * A.m.sup_q]; };
+    auto ent = [&](int s, int e) -> float {
+        return A.m.ent[s * A.m.ent_s + e + b * A.m.ent_q];
+    };
 
     // the first super tiles stay in registers: their loads go out before
     // anything is waited for
@@ -115,7 +117,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
 #pragma unroll
     for (int u = 0; u < SV; ++u) {
         const long j = sup0 + lane + u * WAVE;
-        sv[u] = j < sup1 ? sup[j] : __builtin_nanf("");
+        sv[u] = j < sup1 ? sup(j) : __builtin_nanf("");
     }
     // |q|^2 (in every wave: the same sums in the same order), and the request
     // in LDS, zero past the row
@@ -147,7 +149,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
         for (int u = 0; u < SV; ++u)
             f(key_of(sv[u]), (int)sup0 + lane + u * WAVE);
         for (long j = sup0 + lane + SV * WAVE; j < sup1; j += WAVE)
-            f(key_of(sup[j]), (int)j);
+            f(key_of(sup(j)), (int)j);
     };
     each_sup([&](uint32_t key, int) { least = min(least, key); });
     const auto umin = [](uint32_t x, uint32_t y) { return x < y ? x : y; };
@@ -183,7 +185,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
         for (int r = 0; r < k; ++r) {
             uint64_t m = PAIR_NONE;
             for (long i = tid; i < A.n_sup; i += SEL_THREADS) {
-                const uint64_t v = pack(key_of(sup[i]), (int32_t)i);
+                const uint64_t v = pack(key_of(sup(i)), (int32_t)i);
                 if ((r == 0 || v > last) && v < m)
                     m = v;
             }
@@ -218,7 +220,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
         for (int i = tid; i < n_best * A.eps; i += SEL_THREADS) {
             const int j = i / A.eps, e = i - j * A.eps;
             const int s = (int)(uint32_t)S.best[j];
-            if (A.eps == 1 || key_of(ent[(size_t)s * A.eps + e]) <= bound)
+            if (A.eps == 1 || key_of(ent(s, e)) <= bound)
                 S.tiles[atomicAdd(&S.n_tiles, 1)] = s * A.eps + e;
         }
     }
@@ -243,8 +245,9 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
             for (int i = r0 + tid; i < r1; i += SEL_THREADS) {
                 const int per = A.eps * 16, j = i / per;
                 const long row = (long)S.sup[j] * per + (i - j * per);
-                const float v = row < A.rows ? A.acc[(size_t)b * A.ld_acc + row]
-                                             : __builtin_nanf("");
+                const float v = row < A.rows
+                                    ? A.acc[((size_t)(row >> 4) * A.B + b) * 16 + (row & 15)]
+                                    : __builtin_nanf("");
                 const uint32_t key = f2key(fmaf(-2.f, v, qn));
                 // (a distance that is not a number is no neighbour)
                 if (v == v && key <= bound)
@@ -253,14 +256,22 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
         }
         for (int ti = r0 / 16 + wave; !A.acc && ti < r1 / 16; ti += NW) {
             const int te = __builtin_amdgcn_readfirstlane(S.tiles[ti]);
-            const long row = A.row0 + (long)te * 16;      // first row of the tile
-            const long rend = A.row0 + A.rows;
+            // first row of the tile, and the end of its chunk
+            const long si = te / A.eps, ch = si / A.sup_per_chunk;
+            const int e0 = te % A.eps;
+            const long in_ch = (si - ch * A.sup_per_chunk) * A.eps * 16 +
+                               (A.split_tiles ? (e0 >> 1) * 32 + (e0 & 1) * 4 : e0 * 16);
+            const long row = A.row0 + ch * A.rows_per_chunk + in_ch;
+            const long rend = min(A.rows - ch * A.rows_per_chunk, A.rows_per_chunk);
             const int col = lane & 15, jg = lane >> 4;
-            const long n_in = min(16L, rend - row);
+            // (rows from `row` to the chunk's end, as far as a tile reaches)
+            const int n_in = (int)max(0L, min(32L, rend - in_ch));
+            // the tile's row of MFMA row i
+            auto row_of = [&](int i) { return A.split_tiles ? ((i & 12) << 1) + (i & 3) : i; };
             const __amdgpu_buffer_rsrc_t r =
                 make_rsrc(A.bank + (size_t)row * rowb, (uint32_t)n_in * rowb);
             const bool tail_ok = (A.nks - 1) * KS + jg * VEC < A.d;
-            const uint32_t vo = (uint32_t)col * rowb + jg * 16;
+            const uint32_t vo = (uint32_t)row_of(col) * rowb + jg * 16;
             auto load = [&](int s) -> i32x4 {
                 return buffer_load16(r, s >= A.nks || (s == A.nks - 1 && !tail_ok)
                                             ? OFF_NONE
@@ -272,10 +283,11 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
             for (int u = 0; u < 2 * LD; ++u)
                 a[u / LD][u % LD] = load(u);
             f32x4 acc = __builtin_bit_cast(
-                f32x4, buffer_load16(make_rsrc(A.bank_norms + row, (uint32_t)n_in * 4u), jg * 16));
+                f32x4, buffer_load16(make_rsrc(A.bank_norms + row, (uint32_t)n_in * 4u),
+                                       (uint32_t)row_of(jg * 4) * 4u));
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                acc[e] = jg * 4 + e < n_in ? -0.5f * acc[e] : -INFINITY;
+                acc[e] = row_of(jg * 4 + e) < n_in ? -0.5f * acc[e] : -INFINITY;
             for (int s0 = 0; s0 < A.nks; s0 += 2 * LD) {
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
@@ -297,8 +309,9 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
             if (col < 4) {
                 const float v = col == 0 ? acc[0] : col == 1 ? acc[1] : col == 2 ? acc[2] : acc[3];
                 const uint32_t key = f2key(fmaf(-2.f, v, qn));
-                if (v == v && jg * 4 + col < n_in && key <= bound)
-                    S.cand[atomicAdd(&S.n_cand, 1)] = pack(key, (int32_t)(row + jg * 4 + col));
+                const int i = row_of(jg * 4 + col);
+                if (v == v && i < n_in && key <= bound)
+                    S.cand[atomicAdd(&S.n_cand, 1)] = pack(key, (int32_t)(row + i));
             }
         }
         __syncthreads();

@@ -117,3 +117,35 @@ def test_bank_in_parts_matches_one_pass():
         assert torch.equal(out[0][f], out[1][f]), f
     ref_idx, ref_dist = reference(q, bank, k)
     assert torch.equal(out[0]["nbr_idx"], ref_idx) and torch.equal(out[0]["nbr_dist"], ref_dist)
+
+
+@pytest.mark.parametrize("B,N,d,k", [
+    (65, 4_099, 384, 64),       # query-resident, one group per wave, last chunk of 3 rows
+    (130, 70_001, 384, 10),     # two groups, row halves
+    (250, 33_000, 384, 10),     # four groups, row halves
+    (512, 66_007, 384, 10),     # four groups, tiles one after the other
+    (64, 600_011, 512, 10),     # a small batch over a long bank
+    (200, 50_021, 512, 33),
+    (256, 20_011, 768, 10),
+    (100, 9_000, 768, 1),
+    (128, 30_007, 1_024, 10),
+    (65, 5_000, 1_024, 10),
+    (129, 4_001, 1_024, 10),    # GEMM-structured: one request past the query-resident scan
+    (300, 20_003, 768, 20),     # second request tile nearly empty
+    (600, 10_000, 384, 10),
+    (70, 777, 8, 10),           # one 16-byte piece of a row: a stage of padding
+    (128, 5_000, 200, 64),      # tiles of 128 requests, ragged rows
+    (90, 3_000, 1_000, 10),
+    (1_025, 2_050, 136, 10),    # five request tiles
+])
+def test_bf16_scans_are_exact(B, N, d, k):
+    q, bank = draw(B, N, d, "bf16", -1, 1, 6)
+    check(q, bank, k, f"exact bf16 B={B} N={N} d={d} k={k}")
+
+
+@pytest.mark.parametrize("B,d", [(200, 768), (300, 768), (100, 136)])
+def test_bf16_equal_rows_come_in_index_order(B, d):
+    q, bank = draw(B, 33_000, d, "bf16", -1, 1, 7)
+    bank[:] = bank[5]
+    bank[12_345] = q[0]
+    check(q, bank, 20, f"equal rows bf16 B={B} d={d}")
