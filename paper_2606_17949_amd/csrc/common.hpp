@@ -84,6 +84,23 @@ __device__ __forceinline__ T wave_reduce(T v, F op)
     return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
+// Reduction over the wave's four rows of 16 lanes, column by column: every lane
+// ends with its column's result.
+template <typename T, typename F>
+__device__ __forceinline__ T rows_reduce(T v, F op)
+{
+    static_assert(sizeof(T) == 4, "32-bit values");
+    // (the results by value: a bit cast of an element in place reads the first)
+    auto both = [&](uint32_t x, uint32_t y) {
+        return op(__builtin_bit_cast(T, x), __builtin_bit_cast(T, y));
+    };
+    const uint32_t x = __builtin_bit_cast(uint32_t, v);
+    const auto p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    const uint32_t y = __builtin_bit_cast(uint32_t, both(p[0], p[1]));
+    const auto q = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+    return both(q[0], q[1]);
+}
+
 // Lexicographic maximum of (hi, lo) pairs: over each row of 16 lanes when
 // WIDTH is 16 (every lane ends with its row's pair), over the wave when it is
 // 64 (broadcast to every lane).
@@ -138,6 +155,16 @@ __device__ __forceinline__ float wave_max(float v)
 __device__ __forceinline__ float wave_sum(float v)
 {
     return wave_reduce_f(v, [](float a, float b) { return a + b; });
+}
+
+// Workgroup barrier once this wave's LDS accesses are done, with no release
+// fence (which would also wait for the wave's global-to-LDS loads still in
+// flight); the acquire fence keeps later LDS accesses below it.
+__device__ __forceinline__ void stream_barrier()
+{
+    __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 }  // namespace rb

@@ -242,16 +242,6 @@ __device__ __forceinline__ void static_for(F &&f)
     }
 }
 
-// Workgroup barrier once this wave's LDS reads have returned, with no release
-// fence (which would also wait for the wave's global-to-LDS loads still in
-// flight); the acquire fence keeps later LDS accesses below it.
-__device__ __forceinline__ void stream_barrier()
-{
-    __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 __device__ __forceinline__ uint64_t pack(uint32_t key, int32_t idx)
 {
     return ((uint64_t)key << 32) | (uint32_t)idx;

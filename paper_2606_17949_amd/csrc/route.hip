@@ -141,8 +141,8 @@ __global__ __launch_bounds__(LPT_THREADS) void lpt_order_kernel(const float *__r
 // predicted output length on the instance's model. Step t decides request
 // order[t] (arrival order when order is null). An instance outside the
 // request's candidate set (unavailable in mask, or over the request's budget
-// in the Eq. 2 cost) gets a NaN base score: it is left out of both maxima and
-// never picked. WIDTH = 16 (I <= 16):
+// in the Eq. 2 cost) gets a base score of -inf: it is left out of both maxima
+// and never picked. WIDTH = 16 (I <= 16):
 // instance i = lane % 16, replicated in the four rows of 16 lanes, so every
 // reduction stays inside a row and leaves its result in every lane. WIDTH = 64:
 // instance i = lane + 64*u in register slot u. Per request: the latency
@@ -150,23 +150,33 @@ __global__ __launch_bounds__(LPT_THREADS) void lpt_order_kernel(const float *__r
 // non-negative, prompts at least one token, rates positive), so the Eq. 1
 // score orders the candidates as S*Tmax = base*Tmax + w_lat*(Tmax - T) does,
 // which needs no division; both T and S*Tmax are non-negative (scores lie in
-// [0, 1]), so their float bits order as unsigned integers, and one more than
-// the bits of S*Tmax is never 0, which marks a non-candidate. One unsigned
+// [0, 1]), so their float bits order as integers. One integer
 // maximum, a ballot of the lanes that hold it and a find-first-set give the
 // largest score and, among equal scores, the lowest instance index;
-// the lanes holding that instance update its state. The pick's base score,
-// latency and Tmax are captured, one step per lane, and every 64 steps the
-// wave writes the picks and computes their Eq. 1 scores (with the division,
-// exactly as the dense score kernel does) in one vector pass. A request
-// without candidates gets -1 and changes no state.
-// 16 waves; 8 for 16 register slots per lane (more than 512 instances), whose
-// state and scores need the larger register share of a half-size workgroup
-template <int IPL>
-constexpr int assign_threads() { return IPL >= 16 ? 512 : 1024; }
+// the lanes holding that instance update its state.
+//
+// The loop is bound by its chain of dependent instructions, so everything but
+// the pick itself is taken off it: while step t's maximum is reduced, every
+// lane works out step t+1's latency both as the state stands and as it would
+// be had it been picked, and the former's maximum. A pick only adds to its
+// instance's queues, so the maximum of step t+1 is the larger of that maximum
+// and the picked lane's second latency: one lane read instead of a second
+// reduction. (ns a step with both reductions in the chain, and now: 231 / 150 on
+// 13 instances, 268 / 175 on 64, 330 / 267 on 128, 495 / 402 on 256.) The pick's latency and Tmax are captured, one step per lane,
+// and every 64 steps the wave writes the picks and computes their Eq. 1 scores
+// (with the division, exactly as the dense score kernel does) in one vector
+// pass. A request without candidates gets -1 and changes no state.
+constexpr int ASSIGN_THREADS = 1024;
 constexpr int ASSIGN_LDS_FLOATS = 8192;   // per buffer: chunk rows x instances x 2
 
-template <int IPL, int WIDTH>
-__global__ __launch_bounds__(assign_threads<IPL>()) void assign_kernel(
+// A request's base scores and predicted lengths over the instance set, as the
+// loop reads them: what does not depend on the state.
+struct Pair {
+    float base, lv;   // base -inf: not a candidate
+};
+
+template <int IPL, int WIDTH, bool DECIDED>
+__global__ __launch_bounds__(ASSIGN_THREADS) void assign_kernel(
     const float *__restrict__ q_hat, const float *__restrict__ l_hat,
     const int32_t *__restrict__ plen, int B, int M, const InstArgs in, int I, float wq, float wl,
     float wc, const AssignOpts opt, int32_t *__restrict__ assign, float *__restrict__ chosen,
@@ -175,11 +185,11 @@ __global__ __launch_bounds__(assign_threads<IPL>()) void assign_kernel(
     static_assert(WIDTH == 64 || IPL == 1, "a 16-lane row holds one slot");
     constexpr int IP = IPL * WIDTH;                       // instances per LDS row
     constexpr int CH = ASSIGN_LDS_FLOATS / (2 * IP);      // requests per chunk
-    __shared__ float base_s[2][CH][IP];
-    __shared__ float lv_s[2][CH][IP];
-    __shared__ float l_s[2][CH];
+    __shared__ Pair pair_s[2][CH + 2][IP];   // (two rows of slack: the loop reads ahead)
+    __shared__ float l_s[2][CH + 2];
     __shared__ int32_t r_s[2][CH];
-    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n_ch = (B + CH - 1) / CH;
     auto inst = [&](int u) { return WIDTH == 16 ? (lane & 15) : lane + WAVE * u; };
     // maximum over the instance set, as an unsigned maximum of order-preserving
@@ -195,7 +205,7 @@ __global__ __launch_bounds__(assign_threads<IPL>()) void assign_kernel(
     // producers: step t = c*CH + j into slot j of buffer c & 1, one wave per step
     auto produce = [&](int c) {
         const int buf = c & 1;
-        for (int j = wave - 1; j < CH; j += assign_threads<IPL>() / WAVE - 1) {
+        for (int j = wave - 1; j < CH; j += ASSIGN_THREADS / WAVE - 1) {
             const int t = c * CH + j;
             if (t >= B)
                 break;
@@ -224,9 +234,12 @@ __global__ __launch_bounds__(assign_threads<IPL>()) void assign_kernel(
             if (lane < (WIDTH == 16 ? 16 : WAVE)) {
 #pragma unroll
                 for (int u = 0; u < IPL; ++u) {
-                    base_s[buf][j][lane + WAVE * u] =
-                        cand[u] ? base_score(qv[u], C[u], cmax, wq, wc) : __builtin_nanf("");
-                    lv_s[buf][j][lane + WAVE * u] = lv[u];
+                    Pair v;
+                    v.base = base_score(qv[u], C[u], cmax, wq, wc);
+                    if (!(cand[u] && v.base == v.base))
+                        v.base = -INFINITY;
+                    v.lv = lv[u];
+                    pair_s[buf][j][lane + WAVE * u] = v;
                 }
             }
             if (lane == 0) {
@@ -262,134 +275,154 @@ __global__ __launch_bounds__(assign_threads<IPL>()) void assign_kernel(
         rP[u] = valid[u] ? 1.f / in.P[i] : 0.f;
         rD[u] = valid[u] ? 1.f / in.D[i] : 0.f;
     }
-    const auto umax = [](uint32_t x, uint32_t y) { return x > y ? x : y; };
-    // maximum over the instance set (every lane of the row, or of the wave)
-    auto umax_all = [&](uint32_t v) {
-        if constexpr (WIDTH == 16)
-            return row16_reduce(v, umax);
-        else
-            return wave_reduce(v, umax);
+    const auto imax = [](int x, int y) { return x > y ? x : y; };
+    // maximum over the instance set, in every lane
+    auto imax_all = [&](int v) {
+        v = row16_reduce(v, imax);
+        if constexpr (WIDTH == 64)
+            v = rows_reduce(v, imax);
+        return v;
     };
-    // Steps go in blocks of 64: lane s holds step (block + s)'s request index
-    // and prompt length, read from LDS once per block (a step takes its
-    // prompt length with a lane read, not an LDS round trip), and captures
-    // that step's pick.
+    auto lane_of = [](float v, int src) {
+        return __builtin_bit_cast(float,
+                                  __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), src));
+    };
+    // As signed integers, the bits of non-negative floats order as the floats
+    // and those of -inf lie below all of them. A step without candidates has
+    // Tmax TINY (no latency is that small), so that a base score of -inf makes
+    // S*Tmax -inf and not a NaN.
+    constexpr int TINY = 0x00800000;
+    // Lane NONE stands for "no instance" (WIDTH = 16: the rows past the first
+    // are copies, so one of the last may).
+    constexpr int NONE = 48;
+    // Steps go in blocks of 64: lane s captures the pick of step (block + s).
     int cap_i = -1;
-    float cap_b = 0.f, cap_t = 0.f, cap_m = 0.f;
+    float cap_t = 0.f, cap_m = 0.f;
     __syncthreads();   // chunk 0 is ready
     for (int c = 0; c < n_ch; ++c) {
         const int buf = c & 1;
         const int rows = min(CH, B - c * CH);
-        float bs[IPL], lv[IPL];
+        float bs[IPL], lv[IPL], T[IPL], l;      // this step
+        float bs1[IPL], lv1[IPL], l1;           // the next one
+        // (past the chunk: whatever lies there, for no step)
+        auto fetch = [&](int j, float(&bsx)[IPL], float(&lvx)[IPL], float &lx) {
+#pragma unroll
+            for (int u = 0; u < IPL; ++u) {
+                const Pair v = pair_s[buf][j][col + WAVE * u];
+                bsx[u] = v.base;
+                lvx[u] = v.lv;
+            }
+            lx = l_s[buf][j];
+        };
+        fetch(0, bs, lv, l);
+        fetch(1, bs1, lv1, l1);
+        int tb = TINY;
 #pragma unroll
         for (int u = 0; u < IPL; ++u) {
-            bs[u] = base_s[buf][0][col + WAVE * u];
-            lv[u] = lv_s[buf][0][col + WAVE * u];
+            T[u] = latency(p[u], a[u], rP[u], rD[u], l, lv[u]);
+            tb = imax(tb, bs[u] >= 0.f ? __float_as_int(T[u]) : 0);
         }
+        float tmax = __int_as_float(imax_all(tb));
         for (int jb = 0; jb < rows; jb += WAVE) {
-            const int nb = min(WAVE, rows - jb);   // steps of this block
-            const int jj = jb + min(lane, nb - 1);
-            const int rblk = r_s[buf][jj];
-            const float lblk = l_s[buf][jj];
+            const int nb = __builtin_amdgcn_readfirstlane(min(WAVE, rows - jb));
             for (int slot = 0; slot < nb; ++slot) {
-                const int j = jb + slot;
-                const float l = __builtin_bit_cast(
-                    float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lblk), slot));
-                // next step's values, in flight while this one is decided
-                const int jn = j + 1 < rows ? j + 1 : j;
-                float bsn[IPL], lvn[IPL];
+                float bs2[IPL], lv2[IPL], l2;   // the step after, in flight
+                fetch(jb + slot + 2, bs2, lv2, l2);
+                // S * Tmax; -inf for a non-candidate
+                int key[IPL], kb = 0;
 #pragma unroll
                 for (int u = 0; u < IPL; ++u) {
-                    bsn[u] = base_s[buf][jn][col + WAVE * u];
-                    lvn[u] = lv_s[buf][jn][col + WAVE * u];
+                    key[u] = __float_as_int(fmaf(bs[u], tmax, wl * (tmax - T[u])));
+                    kb = imax(kb, key[u]);
                 }
-                // latency maximum over the candidates (a non-candidate, NaN
-                // base score, contributes 0)
-                float T[IPL];
-                uint32_t tb = 0;
+                // the state after a pick of the lane's instance, and the next
+                // step's latencies without and with it (0 for its non-candidates)
+                float p1[IPL], a1[IPL], T0[IPL], T1[IPL], tn[IPL];
+                int t0 = TINY;
 #pragma unroll
                 for (int u = 0; u < IPL; ++u) {
-                    T[u] = latency(p[u], a[u], rP[u], rD[u], l, lv[u]);
-                    tb = umax(tb, bs[u] == bs[u] ? __float_as_uint(T[u]) : 0u);
+                    p1[u] = p[u] + l;
+                    a1[u] = a[u] + lv[u];
+                    T0[u] = latency(p[u], a[u], rP[u], rD[u], l1, lv1[u]);
+                    T1[u] = latency(p1[u], a1[u], rP[u], rD[u], l1, lv1[u]);
+                    const bool c1 = bs1[u] >= 0.f;
+                    t0 = imax(t0, c1 ? __float_as_int(T0[u]) : 0);
+                    tn[u] = c1 && (WIDTH == 64 || lane < NONE) ? T1[u] : 0.f;
                 }
-                const float tmax = __uint_as_float(umax_all(tb));
-                // keys of S * Tmax; 0 for a non-candidate
-                uint32_t key[IPL], kb = 0;
-#pragma unroll
-                for (int u = 0; u < IPL; ++u) {
-                    const float v = fmaf(bs[u], tmax, wl * (tmax - T[u]));
-                    key[u] = bs[u] == bs[u] ? __float_as_uint(v) + 1u : 0u;
-                    kb = umax(kb, key[u]);
-                }
-                const uint32_t kmax = umax_all(kb);
+                t0 = imax_all(t0);
+                const int kmax = imax_all(kb);   // (0, which no lane holds, without candidates)
                 // lowest instance holding the maximum (slots ascend in index)
-                int istar = -1, ustar = 0;
-                if (kmax != 0) {
+                int istar, src;
+                float tp = T[0], tx = tn[0];
+                if constexpr (WIDTH == 16) {
+                    // (the four rows hold the same instances)
+                    istar = src = (int)__builtin_ctzll((ballot(key[0] == kmax) & 0xffffull) |
+                                                       (1ull << NONE));
+                } else {
+                    istar = -1;
+                    int ustar = 0;
 #pragma unroll
                     for (int u = 0; u < IPL; ++u) {
-                        uint64_t mk = ballot(key[u] == kmax);
-                        if (WIDTH == 16)
-                            mk &= 0xffffull;   // the four rows hold the same instances
+                        const uint64_t mk = ballot(key[u] == kmax);
                         if (istar < 0 && mk != 0) {
                             istar = WAVE * u + (int)__builtin_ctzll(mk);
                             ustar = u;
                         }
                     }
-                }
-                // capture the pick in lane `slot`: the instance, Tmax and, for
-                // the scores, the pick's base score and latency from the lane
-                // and slot holding it
-                const bool mine = lane == slot;
-                cap_i = mine ? istar : cap_i;
-                cap_m = mine ? tmax : cap_m;
-                if (chosen && istar >= 0) {
-                    float vb = bs[0], vt = T[0];
 #pragma unroll
                     for (int u = 1; u < IPL; ++u) {
-                        vb = ustar == u ? bs[u] : vb;
-                        vt = ustar == u ? T[u] : vt;
+                        tp = ustar == u ? T[u] : tp;
+                        tx = ustar == u ? tn[u] : tx;
                     }
-                    const int src = istar & (WAVE - 1);
-                    vb = __builtin_bit_cast(
-                        float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, vb), src));
-                    vt = __builtin_bit_cast(
-                        float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, vt), src));
-                    cap_b = mine ? vb : cap_b;
-                    cap_t = mine ? vt : cap_t;
+                    src = istar & (WAVE - 1);
                 }
-                if (decided) {
+                const float tpick = lane_of(tp, src);
+                float tnext = lane_of(tx, src);
+                if (WIDTH == 64)
+                    tnext = istar >= 0 ? tnext : 0.f;
+                // capture the pick in lane `slot`: the instance, its latency, Tmax
+                const bool mine = lane == slot;
+                cap_i = mine ? istar : cap_i;
+                cap_t = mine ? tpick : cap_t;
+                cap_m = mine ? tmax : cap_m;
+                if (DECIDED) {
                     // the row of Eq. 1 scores this step saw, at the state
                     // before its update (NaN outside the candidate set), with
                     // the division of the dense score kernel
-                    const int rq = __builtin_amdgcn_readlane(rblk, slot);
+                    const int rq = r_s[buf][jb + slot];
                     float *drow = decided + (size_t)rq * I;
 #pragma unroll
                     for (int u = 0; u < IPL; ++u) {
                         const int i = inst(u);
                         if (lane < (WIDTH == 16 ? 16 : WAVE) && i < I)
-                            drow[i] = bs[u] == bs[u] ? full_score(bs[u], T[u], tmax, wl)
-                                                     : __builtin_nanf("");
+                            drow[i] = bs[u] >= 0.f ? full_score(bs[u], T[u], tmax, wl)
+                                                   : __builtin_nanf("");
                     }
                 }
+                tmax = __int_as_float(imax(t0, __float_as_int(tnext)));
 #pragma unroll
                 for (int u = 0; u < IPL; ++u) {
-                    if (inst(u) == istar) {
-                        p[u] += l;
-                        a[u] += lv[u];
-                    }
+                    const bool hit = inst(u) == istar;
+                    p[u] = hit ? p1[u] : p[u];
+                    a[u] = hit ? a1[u] : a[u];
+                    T[u] = hit ? T1[u] : T0[u];
+                    bs[u] = bs1[u];
+                    lv[u] = lv1[u];
+                    bs1[u] = bs2[u];
+                    lv1[u] = lv2[u];
                 }
-#pragma unroll
-                for (int u = 0; u < IPL; ++u) {
-                    bs[u] = bsn[u];
-                    lv[u] = lvn[u];
-                }
+                l = l1;
+                l1 = l2;
             }
             // write the block's picks and their Eq. 1 scores in one pass
             if (lane < nb) {
-                assign[rblk] = cap_i;
+                const int rblk = r_s[buf][jb + lane];
+                const int pick = WIDTH == 16 && cap_i == NONE ? -1 : cap_i;
+                assign[rblk] = pick;
                 if (chosen)
-                    chosen[rblk] = cap_i >= 0 ? full_score(cap_b, cap_t, cap_m, wl)
-                                              : __builtin_nanf("");
+                    chosen[rblk] = pick >= 0 ? full_score(pair_s[buf][jb + lane][pick].base, cap_t,
+                                                          cap_m, wl)
+                                             : __builtin_nanf("");
             }
         }
         __syncthreads();   // buffer c & 1 may now be refilled; chunk c + 1 is ready
@@ -398,6 +431,356 @@ __global__ __launch_bounds__(assign_threads<IPL>()) void assign_kernel(
     for (int u = 0; u < IPL; ++u) {
         const int i = inst(u);
         if (lane < (WIDTH == 16 ? 16 : WAVE) && i < I && valid[u]) {
+            in.p[i] = p[u];
+            in.a[i] = a[u];
+        }
+    }
+}
+
+// The same loop for more than 256 instances, which one wave would walk slot
+// by slot (512 instances: 0.77 us a step, bound by instruction issue). The
+// first CW waves hold SL slots of 64 instances each (instance wave*64*SL + 64*u
+// + lane) and every step take the pick of their own, with what the others need
+// to go on if it wins: its index, the next step's latency after the pick, and
+// the maximum of the wave's other latencies then. After one barrier every wave
+// reads all of them and finds the winner, so a step costs one exchange through
+// LDS. The other eight waves are the producers: a group of GR steps is decided while
+// the group after the next is made, a row of it (one request) per wave, cut
+// into GR pieces so that the producers meet every step's barrier too. Their
+// global loads run a group ahead (and the request's index two), so no barrier
+// waits for one.
+constexpr int WIDE_PRODUCERS = 8;
+
+template <int I> struct WideInt {
+    static constexpr int value = I;
+};
+// f(WideInt<K>) for K = B..E-1, unrolled at compile time.
+template <int B, int E, typename F>
+__device__ __forceinline__ void wide_for(F &&f)
+{
+    if constexpr (B < E) {
+        f(WideInt<B>{});
+        wide_for<B + 1, E>(f);
+    }
+}
+
+struct WidePick {
+    int key, inst;      // S*Tmax bits of the wave's pick (-1: none), its instance
+    int t0;             // the next step's largest latency bits with the state as it stands
+    float tn;           // the pick's, after the pick (0: not its candidate)
+};
+struct WideCap {
+    float T, base;      // of the pick, for its score
+};
+
+template <int CW, int SL>
+struct WideShared {
+    static constexpr int IP = CW * WAVE * SL;   // instances
+    static constexpr int GR = 4096 / IP;        // steps of a group
+    static_assert(GR >= 4 && GR <= WIDE_PRODUCERS && GR % 2 == 0, "a row per producer");
+    Pair pair[3][GR][IP];
+    float l[3][GR];
+    int r[3][GR];
+    WidePick pick[2][CW];
+    WideCap cap[2][CW];
+};
+
+template <int CW, int SL, bool DECIDED>
+__global__ __launch_bounds__((CW + WIDE_PRODUCERS) * WAVE) void assign_wide_kernel(
+    const float *__restrict__ q_hat, const float *__restrict__ l_hat,
+    const int32_t *__restrict__ plen, int B, int M, const InstArgs in, int I, float wq, float wl,
+    float wc, const AssignOpts opt, int32_t *__restrict__ assign, float *__restrict__ chosen,
+    float *__restrict__ decided)
+{
+    using Sh = WideShared<CW, SL>;
+    constexpr int GR = Sh::GR, NS = CW * SL;   // slots of 64 instances
+    constexpr int PS = NS / (GR / 2);                  // slots per piece of a row
+    extern __shared__ __align__(16) uint8_t wide_smem[];
+    Sh &S = *(Sh *)wide_smem;
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const auto imax = [](int x, int y) { return x > y ? x : y; };
+    const auto fmx = [](float x, float y) { return fmaxf(x, y); };
+    const int n_gr = (B + GR - 1) / GR;
+
+    if (wave >= CW) {
+        // ---- producers
+        const int w = wave - CW;
+        if (w >= GR) {
+            stream_barrier();
+            for (int t = 0; t < B; ++t)
+                stream_barrier();
+            return;
+        }
+        int model[NS];
+        float cin[NS], cout[NS];
+#pragma unroll
+        for (int u = 0; u < NS; ++u) {
+            const int i = u * WAVE + lane;
+            const int m = i < I ? in.model[i] : -1;
+            // -1: no candidate ever
+            model[u] = (unsigned)m < (unsigned)M && (!opt.mask || opt.mask[i] != 0) ? m : -1;
+            cin[u] = i < I ? in.cin[i] : 0.f;
+            cout[u] = i < I ? in.cout[i] : 0.f;
+        }
+        struct Req {
+            int r;
+            float l, budget;
+        };
+        auto request = [&](int g) {   // this wave's request of group g
+            const int t = g * GR + w;
+            Req q{-1, 0.f, 0.f};
+            if (t < B) {
+                q.r = opt.order ? opt.order[t] : t;
+                q.l = (float)plen[q.r];
+                q.budget = opt.budget ? opt.budget[q.r] : INFINITY;
+            }
+            return q;
+        };
+        float qv[NS], lv[NS];
+        auto labels = [&](const Req &q, float(&qx)[NS], float(&lx)[NS], int u0, int u1) {
+            const size_t o = (size_t)(q.r < 0 ? 0 : q.r) * M;
+#pragma unroll
+            for (int u = u0; u < u1; ++u) {
+                const int m = model[u] < 0 ? 0 : model[u];
+                qx[u] = q_hat[o + m];
+                lx[u] = l_hat[o + m];
+            }
+        };
+        float cmax = 0.f;
+        // piece k of the row of request q into group buffer g % 3: its costs
+        // and their maximum first, then the base scores
+        float C[NS];
+        auto piece = [&](auto K, const Req &q, int g) {
+            constexpr int k = decltype(K)::value;
+            if constexpr (k == 0)
+                cmax = -INFINITY;
+            if constexpr (k < GR / 2) {
+#pragma unroll
+                for (int u = k * PS; u < (k + 1) * PS; ++u) {
+                    C[u] = cost(q.l, lv[u], cin[u], cout[u]);
+                    // Alg. 1 budget filter on the Eq. 2 cost, and availability
+                    const bool cand = model[u] >= 0 && C[u] <= q.budget;
+                    cmax = fmaxf(cmax, cand ? C[u] : -INFINITY);
+                    C[u] = cand ? C[u] : __builtin_nanf("");
+                }
+            } else {
+                if constexpr (k == GR / 2)
+                    cmax = rows_reduce(row16_reduce(cmax, fmx), fmx);
+                Pair *row = S.pair[g % 3][w];
+#pragma unroll
+                for (int u = (k - GR / 2) * PS; u < (k - GR / 2 + 1) * PS; ++u) {
+                    Pair v;
+                    v.base = base_score(qv[u], C[u], cmax, wq, wc);
+                    if (!(C[u] == C[u] && v.base == v.base))
+                        v.base = -INFINITY;
+                    v.lv = model[u] >= 0 ? lv[u] : 0.f;
+                    row[u * WAVE + lane] = v;
+                }
+                if constexpr (k == GR - 1) {
+                    if (lane == 0) {
+                        S.l[g % 3][w] = q.l;
+                        S.r[g % 3][w] = q.r;
+                    }
+                }
+            }
+        };
+        // groups 0 and 1 before the first step
+        for (int g = 0; g < 2; ++g) {
+            const Req q = request(g);
+            labels(q, qv, lv, 0, NS);
+            wide_for<0, GR>([&](auto K) { piece(K, q, g); });
+        }
+        Req q = request(2), qn = request(3);
+        labels(q, qv, lv, 0, NS);
+        stream_barrier();
+        for (int g = 0; g < n_gr; ++g) {
+            // (with every piece a share of the loads of the next group's row; all
+            // with the first where sixteen slots leave no registers to spread them)
+            float qx[NS], lx[NS];
+            const Req qnn = request(g + 4);
+            wide_for<0, GR>([&](auto K) {
+                constexpr int k = decltype(K)::value;
+                if (g * GR + k < B) {
+                    labels(qn, qx, lx, SL == 1 ? k * (NS / GR) : k == 0 ? 0 : NS,
+                           SL == 1 ? (k + 1) * (NS / GR) : NS);
+                    piece(K, q, g + 2);
+                    stream_barrier();
+                }
+            });
+            q = qn;
+            qn = qnn;
+#pragma unroll
+            for (int u = 0; u < NS; ++u) {
+                qv[u] = qx[u];
+                lv[u] = lx[u];
+            }
+        }
+        return;
+    }
+
+    // ---- consumers: instance state in registers
+    const int i0 = wave * WAVE * SL + lane;   // instance of slot u: i0 + 64*u
+    float p[SL], a[SL], rP[SL], rD[SL];
+    bool valid[SL];
+#pragma unroll
+    for (int u = 0; u < SL; ++u) {
+        const int i = i0 + u * WAVE;
+        const int m = i < I ? in.model[i] : -1;
+        valid[u] = (unsigned)m < (unsigned)M;
+        p[u] = valid[u] ? in.p[i] : 0.f;
+        a[u] = valid[u] ? in.a[i] : 0.f;
+        rP[u] = valid[u] ? 1.f / in.P[i] : 0.f;
+        rD[u] = valid[u] ? 1.f / in.D[i] : 0.f;
+    }
+    auto wave_imax = [&](int v) { return rows_reduce(row16_reduce(v, imax), imax); };
+    // over the waves' packets, one per lane of every CW
+    static_assert(CW == 4 || CW == 8, "quads or half rows of lanes");
+    auto imax_waves = [&](int v) {
+        v = imax(v, dpp<0xb1>(v));
+        v = imax(v, dpp<0x4e>(v));
+        if constexpr (CW == 8)
+            v = imax(v, dpp<0x141>(v));
+        return v;
+    };
+    auto lane_of = [](float v, int src) {
+        return __builtin_bit_cast(float,
+                                  __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), src));
+    };
+    constexpr int TINY = 0x00800000;   // as in the narrow loop
+    // (the instance state is written at the very end only)
+    int cap_i = -1, cap_r = 0;
+    float cap_t = 0.f, cap_m = 0.f, cap_b = 0.f;
+    float bs[SL], lv[SL], T[SL], l, bs1[SL], lv1[SL], l1;
+    auto fetch = [&](int t, float(&bsx)[SL], float(&lvx)[SL], float &lx) {
+        const int g = (unsigned)t / GR, k = t - g * GR, buf = g % 3;
+#pragma unroll
+        for (int u = 0; u < SL; ++u) {
+            const Pair v = S.pair[buf][k][i0 + u * WAVE];
+            bsx[u] = v.base;
+            lvx[u] = v.lv;
+        }
+        lx = S.l[buf][k];
+    };
+    stream_barrier();   // groups 0 and 1 are ready
+    fetch(0, bs, lv, l);
+    fetch(1, bs1, lv1, l1);
+#pragma unroll
+    for (int u = 0; u < SL; ++u)
+        T[u] = latency(p[u], a[u], rP[u], rD[u], l, lv[u]);
+    // the first step's largest latency: every wave over the whole table
+    float tmax;
+    {
+        int tt = TINY;
+        for (int i = lane; i < Sh::IP; i += WAVE) {
+            const int m = i < I ? in.model[i] : -1;
+            const Pair v = S.pair[0][0][i];
+            if ((unsigned)m < (unsigned)M && v.base >= 0.f)
+                tt = imax(tt, __float_as_int(latency(in.p[i], in.a[i], 1.f / in.P[i],
+                                                     1.f / in.D[i], l, v.lv)));
+        }
+        tmax = __int_as_float(wave_imax(tt));
+    }
+    for (int t = 0; t < B; ++t) {
+        float bs2[SL], lv2[SL], l2;   // the step after the next, in flight
+        fetch(t + 2, bs2, lv2, l2);
+        int key[SL], kb = -1;
+        float p1[SL], a1[SL], T0[SL], T1[SL], tn[SL];
+        int tz = 0;
+#pragma unroll
+        for (int u = 0; u < SL; ++u) {
+            key[u] = __float_as_int(fmaf(bs[u], tmax, wl * (tmax - T[u])));
+            kb = imax(kb, key[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < SL; ++u) {
+            p1[u] = p[u] + l;
+            a1[u] = a[u] + lv[u];
+            T0[u] = latency(p[u], a[u], rP[u], rD[u], l1, lv1[u]);
+            T1[u] = latency(p1[u], a1[u], rP[u], rD[u], l1, lv1[u]);
+            const bool c1 = bs1[u] >= 0.f;
+            tz = imax(tz, c1 ? __float_as_int(T0[u]) : 0);
+            tn[u] = c1 ? T1[u] : 0.f;
+        }
+        kb = wave_imax(kb);
+        tz = wave_imax(tz);
+        // the wave's lowest instance holding its maximum
+        float tp = T[0], tx = tn[0], bp = bs[0];
+        uint64_t mk = ballot(key[0] == kb);
+        int us = 0;
+#pragma unroll
+        for (int u = 1; u < SL; ++u) {
+            const uint64_t m2 = ballot(key[u] == kb);
+            if (mk == 0) {
+                mk = m2;
+                us = u;
+                tp = T[u];
+                tx = tn[u];
+                bp = bs[u];
+            }
+        }
+        if (mk == 0 || kb < 0)
+            mk = 1;
+        const int src = (int)__builtin_ctzll(mk);
+        if (lane == src) {
+            S.pick[t & 1][wave] =
+                WidePick{kb, kb < 0 ? -1 : i0 + us * WAVE, tz, kb < 0 ? 0.f : tx};
+            S.cap[t & 1][wave] = WideCap{tp, bp};
+        }
+        stream_barrier();
+        const WidePick pk = S.pick[t & 1][lane & (CW - 1)];
+        const int kmax = imax_waves(pk.key);
+        const int tm = imax_waves(pk.t0);
+        const int ws = (int)__builtin_ctzll(ballot(pk.key == kmax));   // (below CW)
+        const int istar = __builtin_amdgcn_readlane(pk.inst, ws);
+        const float tnext = lane_of(pk.tn, ws);
+        if (wave == 0) {
+            // capture the pick in lane t % 64
+            const WideCap cp = S.cap[t & 1][ws];
+            const int rt = S.r[(unsigned)t / GR % 3][t % GR];
+            const bool mine = lane == (t & 63);
+            cap_i = mine ? istar : cap_i;
+            cap_r = mine ? rt : cap_r;
+            cap_t = mine ? cp.T : cap_t;
+            cap_b = mine ? cp.base : cap_b;
+            cap_m = mine ? tmax : cap_m;
+            if ((t & 63) == 63 || t == B - 1) {
+                if (lane <= (t & 63)) {
+                    assign[cap_r] = cap_i;
+                    if (chosen)
+                        chosen[cap_r] = cap_i >= 0 ? full_score(cap_b, cap_t, cap_m, wl)
+                                                   : __builtin_nanf("");
+                }
+            }
+        }
+        if (DECIDED) {
+            const int rq = S.r[(unsigned)t / GR % 3][t % GR];
+            float *drow = decided + (size_t)rq * I;
+#pragma unroll
+            for (int u = 0; u < SL; ++u)
+                if (i0 + u * WAVE < I)
+                    drow[i0 + u * WAVE] = bs[u] >= 0.f ? full_score(bs[u], T[u], tmax, wl)
+                                                       : __builtin_nanf("");
+        }
+        tmax = __int_as_float(imax(imax(tm, __float_as_int(tnext)), TINY));
+#pragma unroll
+        for (int u = 0; u < SL; ++u) {
+            const bool hit = i0 + u * WAVE == istar;
+            p[u] = hit ? p1[u] : p[u];
+            a[u] = hit ? a1[u] : a[u];
+            T[u] = hit ? T1[u] : T0[u];
+            bs[u] = bs1[u];
+            lv[u] = lv1[u];
+            bs1[u] = bs2[u];
+            lv1[u] = lv2[u];
+        }
+        l = l1;
+        l1 = l2;
+    }
+#pragma unroll
+    for (int u = 0; u < SL; ++u) {
+        const int i = i0 + u * WAVE;
+        if (i < I && valid[u]) {
             in.p[i] = p[u];
             in.a[i] = a[u];
         }
@@ -443,17 +826,49 @@ hipError_t launch_assign(const float *q_hat, const float *l_hat, const int32_t *
                          const AssignOpts &opt, int32_t *assign, float *chosen, float *decided,
                          hipStream_t s)
 {
-    const int ipl = (I + WAVE - 1) / WAVE;
-#define RB_ASSIGN(N, W)                                                                          \
-    hipLaunchKernelGGL((assign_kernel<N, W>), dim3(1), dim3(assign_threads<N>()), 0, s, q_hat,   \
-                       l_hat, plen, B, M, in, I, wq, wl, wc, opt, assign, chosen, decided)
-    if (I <= 16) RB_ASSIGN(1, 16);
-    else if (ipl <= 1) RB_ASSIGN(1, 64);
-    else if (ipl <= 2) RB_ASSIGN(2, 64);
-    else if (ipl <= 4) RB_ASSIGN(4, 64);
-    else if (ipl <= 8) RB_ASSIGN(8, 64);
-    else if (ipl <= 16) RB_ASSIGN(16, 64);
-    else return hipErrorInvalidValue;
+#define RB_ASSIGN(KERN, THREADS, LDS)                                                            \
+    hipLaunchKernelGGL((KERN), dim3(1), dim3(THREADS), LDS, s, q_hat, l_hat, plen, B, M, in, I,  \
+                       wq, wl, wc, opt, assign, chosen, decided)
+#define RB_NARROW(N, W)                                                                          \
+    do {                                                                                         \
+        if (decided)                                                                             \
+            RB_ASSIGN((assign_kernel<N, W, true>), ASSIGN_THREADS, 0);                           \
+        else                                                                                     \
+            RB_ASSIGN((assign_kernel<N, W, false>), ASSIGN_THREADS, 0);                          \
+    } while (0)
+#define RB_WIDE(CW, SL)                                                                              \
+    do {                                                                                         \
+        const size_t lds = sizeof(WideShared<CW, SL>);                                           \
+        const void *f = decided ? (const void *)assign_wide_kernel<CW, SL, true>                 \
+                                : (const void *)assign_wide_kernel<CW, SL, false>;               \
+        const hipError_t e = hipFuncSetAttribute(                                                \
+            f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                            \
+        if (e != hipSuccess)                                                                     \
+            return e;                                                                            \
+        if (decided)                                                                             \
+            RB_ASSIGN((assign_wide_kernel<CW, SL, true>), (CW + WIDE_PRODUCERS) * WAVE, lds);    \
+        else                                                                                     \
+            RB_ASSIGN((assign_wide_kernel<CW, SL, false>), (CW + WIDE_PRODUCERS) * WAVE, lds);   \
+    } while (0)
+    // one wave walks up to four slots of 64 instances faster than several
+    // exchange theirs (256 instances: 402 against 523 ns a step; 512: 800
+    // against 526)
+    if (I <= 16)
+        RB_NARROW(1, 16);
+    else if (I <= WAVE)
+        RB_NARROW(1, 64);
+    else if (I <= 2 * WAVE)
+        RB_NARROW(2, 64);
+    else if (I <= 4 * WAVE)
+        RB_NARROW(4, 64);
+    else if (I <= 8 * WAVE)
+        RB_WIDE(8, 1);
+    else if (I <= 16 * WAVE)
+        RB_WIDE(8, 2);
+    else
+        return hipErrorInvalidValue;
+#undef RB_WIDE
+#undef RB_NARROW
 #undef RB_ASSIGN
     return hipGetLastError();
 }
