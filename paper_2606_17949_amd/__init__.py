@@ -97,6 +97,9 @@ def _load():
 
 
 _lib = _load()
+# the raw stream handle without building a torch.cuda.Stream object
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream",
+                              lambda d: torch.cuda.current_stream(d).cuda_stream)
 
 
 def rb_status_string(status: int) -> str:
@@ -109,18 +112,21 @@ def _check(status: int, where: str):
 
 
 def _ptr(t: Optional[torch.Tensor]):
+    """Device address of a contiguous GPU tensor (None for no or an empty one)."""
     if t is None:
         return None
     if not t.is_cuda:
         raise ValueError("tensor must live on the GPU")
     if not t.is_contiguous():
         raise ValueError("tensor must be contiguous")
-    return ctypes.c_void_p(t.data_ptr()) if t.numel() else None
+    return t.data_ptr() if t.numel() else None
 
 
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    """hipStream_t of ``stream``, or of the current device's current one."""
+    if stream is not None:
+        return stream.cuda_stream
+    return _current_raw_stream(torch.cuda.current_device())
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -135,12 +141,13 @@ def _expect(t: torch.Tensor, dtype, shape, name):
     """dtype and shape of a tensor argument, checked before anything reaches
     the library (a short or mistyped buffer would be read or written out of
     bounds on the GPU)."""
+    if isinstance(t, torch.Tensor) and t.dtype is dtype and t.shape == shape:
+        return   # (torch.Size compares with a tuple as a tuple)
     if not isinstance(t, torch.Tensor):
         raise ValueError(f"{name}: expected a torch tensor, got {type(t).__name__}")
     if t.dtype != dtype:
         raise ValueError(f"{name}: expected {dtype}, got {t.dtype}")
-    if tuple(t.shape) != tuple(shape):
-        raise ValueError(f"{name}: expected shape {tuple(shape)}, got {tuple(t.shape)}")
+    raise ValueError(f"{name}: expected shape {tuple(shape)}, got {tuple(t.shape)}")
 
 
 def _expect_opt(t: Optional[torch.Tensor], dtype, shape, name):
@@ -219,11 +226,14 @@ class DeviceInstances:
         return DeviceInstances(*[getattr(self, f).clone() for f in self.FIELDS])
 
     def struct(self) -> rb_instances:
-        I = self.I
-        for f in self.FIELDS:
-            t = getattr(self, f)
-            _expect(t, torch.int32 if f == "model" else torch.float32, (I,), f)
-        return rb_instances(*[_ptr(getattr(self, f)) for f in self.FIELDS])
+        shape = (self.I,)
+        model, f32 = self.model, torch.float32
+        _expect(model, torch.int32, shape, "model")
+        for f in self.FIELDS[1:]:
+            _expect(getattr(self, f), f32, shape, f)
+        return rb_instances(_ptr(model), _ptr(self.prefill_q), _ptr(self.decode_q),
+                            _ptr(self.prefill_rate), _ptr(self.decode_rate),
+                            _ptr(self.price_in), _ptr(self.price_out))
 
 
 def rb_workspace_size(B: int, N: int, d: int, dtype: int, k: int, M: int) -> int:
@@ -258,7 +268,8 @@ def rb_knn_topk(queries: torch.Tensor, bank: torch.Tensor, bank_norms: torch.Ten
     _expect(bank_norms, torch.float32, (N,), "bank_norms")
     _expect_opt(nbr_idx, torch.int32, (B, k), "nbr_idx")
     _expect_opt(nbr_dist, torch.float32, (B, k), "nbr_dist")
-    _expect_opt(ws, torch.uint8, (ws.numel(),) if ws is not None else (), "ws")
+    if ws is not None:
+        _expect(ws, torch.uint8, (ws.numel(),), "ws")
     dev = queries.device
     if nbr_idx is None:
         nbr_idx = torch.empty(B, k, dtype=torch.int32, device=dev)
@@ -299,7 +310,7 @@ def rb_predict(nbr_idx: torch.Tensor, bank_qual: torch.Tensor, bank_len: torch.T
 
 
 def _w(weights) -> rb_weights:
-    return rb_weights(*[float(x) for x in weights])
+    return rb_weights(*map(float, weights))
 
 
 def _request_args(q_hat, l_hat, prompt_len):
@@ -360,7 +371,8 @@ def _route_args(queries, bank, bank_norms, k, bank_qual, bank_len, prompt_len, i
     _expect_opt(score0, torch.float32, (B, inst.I), "score0")
     _expect_opt(chosen, torch.float32, (B,), "chosen")
     _expect_opt(assign, torch.int32, (B,), "assign")
-    _expect_opt(ws, torch.uint8, (ws.numel(),) if ws is not None else (), "ws")
+    if ws is not None:
+        _expect(ws, torch.uint8, (ws.numel(),), "ws")
     return B, N, d, M
 
 
@@ -474,7 +486,8 @@ def rb_knn_predict(queries, bank, bank_norms, k: int, bank_qual, bank_len,
     _expect_opt(l_hat, torch.float32, (B, M), "l_hat")
     _expect_opt(nbr_idx, torch.int32, (B, k), "nbr_idx")
     _expect_opt(nbr_dist, torch.float32, (B, k), "nbr_dist")
-    _expect_opt(ws, torch.uint8, (ws.numel(),) if ws is not None else (), "ws")
+    if ws is not None:
+        _expect(ws, torch.uint8, (ws.numel(),), "ws")
     dev = queries.device
     lists_only = opts is not None and (opts.flags & RB_FLAG_LISTS_ONLY)
     if q_hat is None and not lists_only:
