@@ -37,10 +37,12 @@ constexpr int GM_HOLD = 8;     // macro tiles whose maxima wait in LDS
 constexpr int RES_WAVES = 8;
 constexpr int RES_RING = 8;
 constexpr int RES_MAX_NG = 8;
-// The selection: one workgroup of SEL_THREADS threads per request; up to
+// The selection: one workgroup of SEL_THREADS threads per request (half of
+// them for more than SEL_WIDE_B requests); up to
 // SEL_CAP super tiles or rows held in LDS at once; SEL_ROUND row tiles
 // recomputed per round.
 constexpr int SEL_THREADS = 1024;
+constexpr int SEL_WIDE_B = 256;
 constexpr int SEL_CAP = 2048;
 constexpr int SEL_ROUND = 64;
 constexpr int SEL_MAX_EPS = 16;            // row tiles per super tile, at most

@@ -101,38 +101,57 @@ __global__ __launch_bounds__(256) void score_kernel(const float *__restrict__ q_
 // maximum over models of its predicted length). Each request's position is
 // the number of requests before it under (key descending, index ascending),
 // a total order, so the positions form a permutation: order[pos] = r. Every
-// workgroup ranks LPT_THREADS requests against all B keys, which it computes
-// tile by tile into LDS.
+// workgroup ranks LPT_RANK requests against all B keys, LPT_TILE at a time in
+// LDS, its four waves a quarter of them each. What bounds it is latency: a
+// tile's keys are all loaded together, and few requests per workgroup keep the
+// count short (1,024 requests of 16 models: 25 us in workgroups of 256 with
+// 256 keys at a time).
 constexpr int LPT_THREADS = 256;
+constexpr int LPT_RANK = WAVE;
+constexpr int LPT_TILE = 2048;
 
 __global__ __launch_bounds__(LPT_THREADS) void lpt_order_kernel(const float *__restrict__ l_hat,
                                                                  int B, int M,
                                                                  int32_t *__restrict__ order)
 {
-    __shared__ uint64_t keys[LPT_THREADS];
+    __shared__ uint64_t keys[LPT_TILE];
+    __shared__ uint64_t own[LPT_RANK];
+    __shared__ int pos[LPT_RANK];
     // ascending in this 64-bit key is descending in the length, then
     // ascending in the index
     auto key_of = [&](int r) {
         const float *row = l_hat + (size_t)r * M;
         float mx = row[0];
+#pragma unroll 8
         for (int m = 1; m < M; ++m)
             mx = fmaxf(mx, row[m]);
         return ((uint64_t)~f2key(mx) << 32) | (uint32_t)r;
     };
-    const int r = blockIdx.x * LPT_THREADS + threadIdx.x;
-    const uint64_t mine = r < B ? key_of(r) : ~0ull;
-    int pos = 0;
-    for (int base = 0; base < B; base += LPT_THREADS) {
-        const int s = base + threadIdx.x;
-        keys[threadIdx.x] = s < B ? key_of(s) : ~0ull;
-        __syncthreads();
-        const int n = min(LPT_THREADS, B - base);
-        for (int j = 0; j < n; ++j)
-            pos += keys[j] < mine ? 1 : 0;
-        __syncthreads();
+    const int tid = threadIdx.x, lane = lane_id(), part = tid / WAVE;
+    const int r = blockIdx.x * LPT_RANK + lane;
+    if (tid < LPT_RANK) {
+        pos[tid] = 0;
+        own[tid] = r < B ? key_of(r) : ~0ull;
     }
-    if (r < B)
-        order[pos] = r;
+    for (int base = 0; base < B; base += LPT_TILE) {
+        const int n = min(LPT_TILE, B - base);
+        if (base > 0)
+            __syncthreads();
+#pragma unroll 4
+        for (int i = tid; i < n; i += LPT_THREADS)
+            keys[i] = key_of(base + i);
+        __syncthreads();
+        const uint64_t mine = own[lane];
+        const int j0 = n * part / (LPT_THREADS / WAVE), j1 = n * (part + 1) / (LPT_THREADS / WAVE);
+        int c = 0;
+#pragma unroll 8
+        for (int j = j0; j < j1; ++j)
+            c += keys[j] < mine ? 1 : 0;
+        atomicAdd(&pos[lane], c);
+    }
+    __syncthreads();
+    if (tid < LPT_RANK && r < B)
+        order[pos[tid]] = r;
 }
 
 // Greedy assignment. Wave 0 runs the sequential loop over requests; waves
@@ -448,7 +467,10 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void assign_kernel(
 // the group after the next is made, a row of it (one request) per wave, cut
 // into GR pieces so that the producers meet every step's barrier too. Their
 // global loads run a group ahead (and the request's index two), so no barrier
-// waits for one.
+// waits for one. (512 instances: 767 ns a step on one wave, 510 so; 1,000: 1,392
+// and 950. Four waves of two slots: 607. The longest piece of a row sets the
+// step: with all loads in the first piece 526, with a row's reciprocal taken
+// once and an exact-remainder step per ratio 579.)
 constexpr int WIDE_PRODUCERS = 8;
 
 template <int I> struct WideInt {
@@ -816,7 +838,7 @@ hipError_t launch_score(const float *q_hat, const float *l_hat, const int32_t *p
 
 hipError_t launch_lpt_order(const float *l_hat, int B, int M, int32_t *order, hipStream_t s)
 {
-    hipLaunchKernelGGL(lpt_order_kernel, dim3((B + LPT_THREADS - 1) / LPT_THREADS),
+    hipLaunchKernelGGL(lpt_order_kernel, dim3((B + LPT_RANK - 1) / LPT_RANK),
                        dim3(LPT_THREADS), 0, s, l_hat, B, M, order);
     return hipGetLastError();
 }

@@ -22,17 +22,18 @@ __device__ __forceinline__ uint64_t wave_min_u64(uint64_t m)
 // the pairs to rank and, where there are more threads, the pairs to count
 // over; rank[] holds n counts, zero on entry. Every thread of the workgroup
 // takes part; `out` is complete after the next barrier.
+template <int NT>
 __device__ __forceinline__ void rank_pairs(const uint64_t *cand, int n, int k, int *rank,
                                            uint64_t *out)
 {
     const int width = (n + WAVE - 1) / WAVE * WAVE;
-    const int parts = width > 0 && width < SEL_THREADS ? SEL_THREADS / width : 1;
+    const int parts = width > 0 && width < NT ? NT / width : 1;
     const int part = width > 0 ? threadIdx.x / width : 0;
     if (part < parts || parts == 1) {
         const int j0 = parts == 1 ? 0 : n * part / parts;
         const int j1 = parts == 1 ? n : n * (part + 1) / parts;
         for (int i = parts == 1 ? threadIdx.x : threadIdx.x - part * width; i < n;
-             i += SEL_THREADS) {
+             i += NT) {
             const uint64_t mine = cand[i];
             int r = 0;
 #pragma unroll 8
@@ -42,7 +43,7 @@ __device__ __forceinline__ void rank_pairs(const uint64_t *cand, int n, int k, i
         }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < n; i += SEL_THREADS) {
+    for (int i = threadIdx.x; i < n; i += NT) {
         const int r = rank[i];
         rank[i] = 0;
         if (r < k)
@@ -76,7 +77,7 @@ __device__ __forceinline__ void rank_pairs(const uint64_t *cand, int n, int k, i
 struct SelectShared {
     uint64_t cand[SEL_CAP];
     uint64_t best[RB_MAX_K_DEV], prev[RB_MAX_K_DEV];
-    uint32_t group_min[SEL_THREADS / 16];
+    uint32_t group_min[WAVE];
     uint64_t wave_min[SEL_THREADS / WAVE];
     int tiles[RB_MAX_K_DEV * SEL_MAX_EPS];
     int sup[RB_MAX_K_DEV];
@@ -86,15 +87,14 @@ struct SelectShared {
     float wts[RB_MAX_K_DEV];
     __align__(16) uint8_t q[SEL_MAX_ROW_BYTES];
 };
-static_assert(SEL_THREADS / 16 == WAVE, "one group per lane, k groups for every k");
 static_assert(SEL_ROUND * 16 + RB_MAX_K_DEV <= SEL_CAP, "a round's rows and the running best");
 
-template <int DT>
-__global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
+template <int DT, int NT>
+__global__ __launch_bounds__(NT, 1024 / NT) void select_kernel(const SelectArgs A)
 {
     constexpr int VEC = Elem<DT>::VEC, ESZ = Elem<DT>::ESZ;
     constexpr int KS = 4 * VEC;
-    constexpr int NW = SEL_THREADS / WAVE;
+    constexpr int NW = NT / WAVE;
     constexpr int LD = 8;   // k-steps of one block of bank loads
     __shared__ SelectShared S;
     const int b = blockIdx.x;
@@ -110,7 +110,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
     // the first super tiles stay in registers: their loads go out before
     // anything is waited for
     // (a wave's share is contiguous, so that every wave has some)
-    constexpr int SV = SEL_WANT_SUP / SEL_THREADS;
+    constexpr int SV = SEL_WANT_SUP / NT;
     const long share = (A.n_sup + NW - 1) / NW;
     const long sup0 = wave * share, sup1 = min(A.n_sup, sup0 + share);
     float sv[SV];
@@ -131,9 +131,9 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
     }
     qn = wave_sum(qn);
     const uint32_t padded = (uint32_t)(A.nks + LD - 1) / LD * LD * KSTEP_BYTES;
-    for (uint32_t off = rowb + tid * 16; off < padded; off += SEL_THREADS * 16)
+    for (uint32_t off = rowb + tid * 16; off < padded; off += NT * 16)
         *(i32x4 *)(S.q + off) = i32x4{0, 0, 0, 0};
-    for (int i = tid; i < SEL_CAP; i += SEL_THREADS)
+    for (int i = tid; i < SEL_CAP; i += NT)
         S.rank[i] = 0;
     if (tid == 0)
         S.n_cand = S.n_tiles = 0;
@@ -156,16 +156,27 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
     const auto umax = [](uint32_t x, uint32_t y) { return x > y ? x : y; };
     // the largest of the least distances of at least k groups (waves, half
     // waves or rows of lanes) has a super tile of each at or below it
-    least = row16_reduce(least, umin);
-    if (k <= NW) {
-        least = wave_reduce(least, umin);
-    } else if (k <= 2 * NW) {
-        least = umin(least, dpp<0x142, 0xa>(least));   // row_bcast:15 into rows 1 and 3
-        if (!(lane & 16))
-            least = 0;   // (rows 0 and 2: no group of their own)
+    // groups of GL lanes, 64 of them; each step up halves their number, as far
+    // as k allows (a group of its pair: 0, which no maximum takes)
+    constexpr int GL = NT / WAVE;
+    static_assert(GL == 16 || GL == 8, "rows or half rows of lanes");
+    least = umin(least, dpp<0xb1>(least));
+    least = umin(least, dpp<0x4e>(least));
+    least = umin(least, dpp<0x141>(least));   // half rows of 8 lanes
+    bool of_group = true;
+    if (GL == 16 || k <= 32) {
+        least = umin(least, dpp<0x140>(least));   // rows
+        of_group = GL == 16 || !(lane & 8);
     }
-    if ((lane & 15) == 0)
-        S.group_min[wave * 4 + (lane >> 4)] = least;
+    if (k <= (GL == 16 ? 16 : 8)) {
+        least = rows_reduce(least, umin);   // waves
+        of_group = lane < GL;
+    } else if (k <= (GL == 16 ? 32 : 16)) {
+        least = umin(least, dpp<0x142, 0xa>(least));   // row_bcast:15: half waves
+        of_group = (lane & 16) && (GL == 16 || !(lane & 8));
+    }
+    if (lane % GL == 0)
+        S.group_min[wave * (WAVE / GL) + lane / GL] = of_group ? least : 0u;
     __syncthreads();
     // absent entries stay out
     uint32_t bound = min(KEY_NONE - 1, wave_reduce(S.group_min[lane], umax));
@@ -179,12 +190,12 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
     __syncthreads();
     int n_best = min(S.n_cand, k);
     if (S.n_cand <= SEL_CAP) {
-        rank_pairs(S.cand, S.n_cand, k, S.rank, S.best);
+        rank_pairs<NT>(S.cand, S.n_cand, k, S.rank, S.best);
     } else {
         uint64_t last = 0;
         for (int r = 0; r < k; ++r) {
             uint64_t m = PAIR_NONE;
-            for (long i = tid; i < A.n_sup; i += SEL_THREADS) {
+            for (long i = tid; i < A.n_sup; i += NT) {
                 const uint64_t v = pack(key_of(sup(i)), (int32_t)i);
                 if ((r == 0 || v > last) && v < m)
                     m = v;
@@ -217,7 +228,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
         if (tid < n_best)
             S.sup[tid] = (int)(uint32_t)S.best[tid];
     } else {
-        for (int i = tid; i < n_best * A.eps; i += SEL_THREADS) {
+        for (int i = tid; i < n_best * A.eps; i += NT) {
             const int j = i / A.eps, e = i - j * A.eps;
             const int s = (int)(uint32_t)S.best[j];
             if (A.eps == 1 || key_of(ent(s, e)) <= bound)
@@ -238,11 +249,11 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
             S.n_cand = 0;
         __syncthreads();
         const int r1 = min(n_items, r0 + SEL_ROUND * 16);
-        for (int i = tid; i < n_prev; i += SEL_THREADS)
+        for (int i = tid; i < n_prev; i += NT)
             if ((uint32_t)(S.prev[i] >> 32) != KEY_NONE)
                 S.cand[atomicAdd(&S.n_cand, 1)] = S.prev[i];
         if (A.acc) {
-            for (int i = r0 + tid; i < r1; i += SEL_THREADS) {
+            for (int i = r0 + tid; i < r1; i += NT) {
                 const int per = A.eps * 16, j = i / per;
                 const long row = (long)S.sup[j] * per + (i - j * per);
                 const float v = row < A.rows
@@ -319,7 +330,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
         if (tid < k)
             S.best[tid] = PAIR_NONE;
         __syncthreads();
-        rank_pairs(S.cand, n, k, S.rank, S.best);
+        rank_pairs<NT>(S.cand, n, k, S.rank, S.best);
         __syncthreads();
         if (tid < k)
             S.prev[tid] = S.best[tid];
@@ -351,8 +362,8 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
     // neighbour order, as average_labels takes them (whose loop serves more
     // labels than threads)
     const int M = A.M;
-    if (k * M <= SEL_THREADS) {
-        float *lq = (float *)S.cand, *ll = lq + SEL_THREADS;
+    if (k * M <= NT) {
+        float *lq = (float *)S.cand, *ll = lq + NT;
         if (tid < k * M) {
             const int j = tid / M;
             const int32_t n = S.nbr[j];
@@ -384,7 +395,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const SelectArgs A)
         }
         return;
     }
-    for (int m = tid; m < M; m += SEL_THREADS)
+    for (int m = tid; m < M; m += NT)
         average_labels(S.nbr, A.inv_dist ? S.wts : nullptr, k, A.qual, A.len, A.N, M, m,
                        A.q_hat + (size_t)b * M + m, A.l_hat + (size_t)b * M + m);
 }
@@ -419,10 +430,25 @@ __global__ __launch_bounds__(WAVE) void from_list_kernel(const SelectArgs A)
 
 hipError_t launch_select(int dtype, const SelectArgs &a, hipStream_t s)
 {
-    if (dtype == 1)
-        hipLaunchKernelGGL(select_kernel<1>, dim3(a.B), dim3(SEL_THREADS), 0, s, a);
-    else
-        hipLaunchKernelGGL(select_kernel<0>, dim3(a.B), dim3(SEL_THREADS), 0, s, a);
+    // one workgroup of 16 waves per compute unit while there are enough units;
+    // more requests go in workgroups of 8, two to a unit, so that one's chain of
+    // accesses runs beside the other's reading (1,024 requests over 1,000,000 x
+    // 1,024: 1,861 us a lookup for 1,871; 20 neighbours of 100 requests instead
+    // lose 4 us of 145 that way)
+#define RB_SELECT(DT, NT)                                                                        \
+    hipLaunchKernelGGL((select_kernel<DT, NT>), dim3(a.B), dim3(NT), 0, s, a)
+    if (a.B <= SEL_WIDE_B) {
+        if (dtype == 1)
+            RB_SELECT(1, SEL_THREADS);
+        else
+            RB_SELECT(0, SEL_THREADS);
+    } else {
+        if (dtype == 1)
+            RB_SELECT(1, SEL_THREADS / 2);
+        else
+            RB_SELECT(0, SEL_THREADS / 2);
+    }
+#undef RB_SELECT
     return hipGetLastError();
 }
 
