@@ -73,7 +73,8 @@ thread_local hipEvent_t t_scan_begin = nullptr, t_scan_end = nullptr;
 // what decides which sizes rb_route_batch_noalloc takes (those whose
 // workspace fits its static array), so the figure stays where callers found
 // it when the scans kept candidate lists: a request's bounds and lists over
-// the chunks of the scan that took it, and the overflow of its candidates.
+// the chunks of the scan that took it, and the overflow of its candidates. 0:
+// refused (more lists than the merge took: banks of over 2 TB).
 size_t contract_bytes(int B, int N, int d, int dtype, int k, int num_cu, int reserve)
 {
     const int vec = dtype == 1 ? 8 : 4;
@@ -135,6 +136,8 @@ size_t contract_bytes(int B, int N, int d, int dtype, int k, int num_cu, int res
     const long G = S / 16 < k ? 0 : S / 16;
     const bool two = rs && B > 128 && (long)N / 32 > 32768 && rpc >= 1024;
     const size_t W = (size_t)n_chunks * (rs ? rs : 1) * (two ? 2 : 1), b = (size_t)B;
+    if (W > 4096)
+        return 0;
     const long pairs = 512L * ng;
     const size_t cap = rs ? 1 : gemm ? 64 * 128 - 64 : pairs > 128 ? pairs - 128 : 1;
     const size_t wgs = rs ? n_chunks : (n_chunks + 7) / 8 * 8 * n_qt;
@@ -286,6 +289,8 @@ int plan_knn(int B, int N, int d, int dtype, int k, int num_cu, KnnPlan *p, int 
     p->k = k;
     p->nks = (d + 4 * vec - 1) / (4 * vec);
     p->contract = contract_bytes(B, N, d, dtype, k, num_cu, reserve);
+    if (p->contract == 0)
+        return -1;
     // bf16 rows of 384, 512, 768 or 1,024 elements go to the query-resident
     // scan when the batch fits one workgroup's registers; a batch of at most
     // 64 requests only over a bank of at least RQ_SMALL_B_MIN_ROWS rows per
