@@ -96,8 +96,8 @@ def parse():
     ap.add_argument("--options", default="",
                     help="comma list of lpt, inv_dist, budget, mask (rb_route_batch_ex)")
     ap.add_argument("--schedule", choices=("pipelined", "sequential"), default="pipelined",
-                    help="pipelined: the seed and bank scan of batch t+1 run on a second stream "
-                         "while batch t is merged, averaged and assigned; sequential: one "
+                    help="pipelined: the bank scan and selection of batch t+1 run on a second "
+                         "stream while batch t is averaged and assigned; sequential: one "
                          "rb_route_batch call per batch")
     ap.add_argument("--cpu-sample", type=int, default=0,
                     help="requests in the CPU oracle sample (0: 8 per host thread)")
@@ -302,16 +302,16 @@ def main():
                                  cfg.weights, opts[t], ws=ws, assign=out, stream=stream)
         rb.rb_advance_state(state, carry_dt, stream=stream)
 
-    # pipelined schedule: the first half of each lookup (seed and bank scan,
-    # RB_FLAG_LISTS_ONLY) on s_knn; the second half (merge of the chunk lists
-    # and label average, RB_FLAG_FROM_LISTS), the greedy pass and the carry in
-    # batch order on s_asg, after an event on the first half. A ring of
-    # WS_RING workspaces: a lookup waits for the merge WS_RING batches back,
-    # which last read its workspace. The greedy stream keeps a few hundred
-    # microseconds of slack per batch, but a merge that finds every compute
-    # unit taken by the next scan waits for the few units the scan leaves
-    # free, so the ring is deep enough that such a late merge never holds up
-    # a lookup.
+    # pipelined schedule: the first half of each lookup (bank scan and
+    # selection, RB_FLAG_LISTS_ONLY) on s_knn; the second half (label average
+    # over the neighbours it left, RB_FLAG_FROM_LISTS), the greedy pass and the
+    # carry in batch order on s_asg, after an event on the first half. A ring
+    # of WS_RING workspaces: a lookup waits for the average WS_RING batches
+    # back, which last read its workspace. The greedy stream keeps a few
+    # hundred microseconds of slack per batch, but an average that finds every
+    # compute unit taken by the next scan waits for the few units the scan
+    # leaves free, so the ring is deep enough that such a late one never holds
+    # up a lookup.
     s_knn = torch.cuda.Stream(device=dev)
     s_asg = torch.cuda.Stream(device=dev) if args.schedule == "pipelined" else stream
     n_ws = WS_RING if args.schedule == "pipelined" else 1
@@ -526,8 +526,8 @@ def main():
         tf = flops / (scan_avg / 1e3) / 1e12
         roof = {"bound": "mfma", "achieved": round(tf, 1), "peak": peak_tf, "unit": "TFLOP/s",
                 "frac": round(tf / peak_tf, 4), "traffic": measured_traffic(cfg.name)}
-    roof["kernel"] = ("bank scan, scan_kernel or rq_scan_kernel (distance contraction + fused "
-                      "per-chunk top-k)")
+    roof["kernel"] = ("bank scan: res_scan_kernel, rq_scan_kernel or gemm_scan_kernel (distance "
+                      "contraction + the maxima of row tiles)")
     roof["per_launch"] = {"bytes": bank_bytes, "flops": flops, "launches_timed": len(scan_ms),
                           "avg_us": round(scan_avg * 1e3, 2),
                           "p10_us": round(float(np.percentile(scan_ms, 10)) * 1e3, 2),
@@ -560,8 +560,8 @@ def main():
                    "parallelism": "single GPU"},
         "options": opt_names,
         "schedule": args.schedule if args.schedule == "sequential" else
-        "pipelined: the seed and bank scan of batch t+1 (second stream) overlap the merge, "
-        "greedy pass and carry of batch t; every batch's lookup, greedy pass and carry are "
+        "pipelined: the bank scan and selection of batch t+1 (second stream) overlap the label "
+        "average, greedy pass and carry of batch t; every batch's lookup, greedy pass and carry are "
         "inside the timed region",
         "bank_scan_gbps": round(scan_gbs, 1),
         "arith_intensity_flop_per_byte": round(ai, 1),

@@ -210,11 +210,11 @@ rb_status rb_assign(const float *q_hat, const float *l_hat, const int32_t *promp
 #define RB_FLAG_OVERLAP 1u
 /*   RB_FLAG_LISTS_ONLY, RB_FLAG_FROM_LISTS (rb_knn_predict only, not both):
  *     the lookup in two calls, so that its two halves can go on different
- *     streams. With RB_FLAG_LISTS_ONLY the call runs the seed and the bank
- *     scan and leaves the per-chunk candidate lists in the workspace; it
+ *     streams. With RB_FLAG_LISTS_ONLY the call runs the bank scan and the
+ *     selection and leaves every request's neighbours in the workspace; it
  *     writes none of nbr_idx, nbr_dist, q_hat, l_hat (q_hat and l_hat may
- *     then be NULL). With RB_FLAG_FROM_LISTS it runs only the merge of those
- *     lists and the label average, from the lists that the last
+ *     then be NULL). With RB_FLAG_FROM_LISTS it runs only the label average
+ *     (and the copy of the neighbours out), from the lists that the last
  *     RB_FLAG_LISTS_ONLY call on this workspace left there; that call must
  *     have had the same dtype, B, N, d, k and RB_FLAG_OVERLAP bit, on the same
  *     device, and have completed (same stream, or ordered before this call by

@@ -475,10 +475,11 @@ def rb_knn_predict(queries, bank, bank_norms, k: int, bank_qual, bank_len,
                    stream=None):
     """KNN lookup and label average in one call: returns (q_hat, l_hat).
 
-    With RB_FLAG_LISTS_ONLY in ``opts.flags`` only the seed and the bank scan
-    run (their lists stay in ``ws``; returns (None, None) unless buffers are
-    given); with RB_FLAG_FROM_LISTS only the merge and average of the lists a
-    LISTS_ONLY call left in ``ws`` (the same shapes and overlap flag)."""
+    With RB_FLAG_LISTS_ONLY in ``opts.flags`` only the bank scan and the
+    selection run (the neighbours stay in ``ws``; returns (None, None) unless
+    buffers are given); with RB_FLAG_FROM_LISTS only the average over the
+    neighbours a LISTS_ONLY call left in ``ws`` (the same shapes and overlap
+    flag)."""
     B, N, d = _embeddings(queries, bank)
     _expect(bank_norms, torch.float32, (N,), "bank_norms")
     M = _labels(bank_qual, bank_len, N)

@@ -454,7 +454,7 @@ rb_status rb_knn_predict(const void *queries, const void *bank, const float *ban
         return s;
     if (B == 0)
         return RB_OK;
-    // the halves of the lookup: seed and scan to the lists, then merge and average
+    // the halves of the lookup: scan and selection to the lists, then the average
     const bool lists_only = (o->flags & RB_FLAG_LISTS_ONLY) != 0;
     const bool from_lists = (o->flags & RB_FLAG_FROM_LISTS) != 0;
     if (!from_lists && (!queries || !bank || !bank_norms))

@@ -91,10 +91,10 @@ void set_scan_events(hipEvent_t begin, hipEvent_t end);
 
 hipError_t launch_bank_norms(const void *bank, int dtype, int N, int d, float *norms,
                              hipStream_t s);
-// The halves of launch_knn: the seed and the bank scan (which leave the
-// per-chunk lists in the workspace), and the merge of those lists.
+// The halves of launch_knn: the bank scan and the selection (which leave the
+// neighbours in the workspace), and the outputs from those lists.
 enum KnnPhases { KNN_LISTS = 1, KNN_MERGE = 2, KNN_ALL = 3 };
-// With q_hat non-null, the merge also averages the labels (inv_dist: with
+// With q_hat non-null, the second half also averages the labels (inv_dist: with
 // inverse-distance weights instead of the plain mean).
 hipError_t launch_knn(const KnnPlan &p, const void *queries, const void *bank,
                       const float *bank_norms, void *ws, int32_t *nbr_idx, float *nbr_dist,
