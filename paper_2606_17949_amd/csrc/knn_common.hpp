@@ -56,6 +56,15 @@ struct SelectArgs {
 hipError_t launch_select(int dtype, const SelectArgs &a, hipStream_t s);
 hipError_t launch_from_list(const SelectArgs &a, hipStream_t s);
 
+// Floats between two entries of the maxima staged in LDS (entry by entry,
+// n_req requests each, a multiple of 32): a wave writes one entry of
+// consecutive requests and reads back four entries of 16 requests in four lane
+// groups, 4 * pitch = 16 (mod 64) apart, both over distinct banks. (Request by
+// request, 16 entries each, a write took sixteen lanes to one bank: 61 M
+// conflict cycles a launch of 512 x 4,000,000 x 384, 31 M of 1,024 x 1,000,000
+// x 1,024.)
+__host__ __device__ constexpr int stage_pitch(int n_req) { return (n_req + 63) / 64 * 64 + 4; }
+
 // Byte offsets of the query-resident scan's LDS regions.
 struct RqLayout {
     uint32_t ring, norms, stage, sup, bytes;
@@ -69,9 +78,9 @@ __host__ __device__ inline RqLayout rq_layout(int qw, int rs, int kstg, int stag
     o += (uint32_t)stages * kstg * (RQ_ROWS / 16) * WAVE * 16;
     L.norms = o;   // [stages][64] |x|^2 of the rows of a block (with its first stage)
     o += (uint32_t)stages * WAVE * 4;
-    L.stage = o;   // [rs][RQ_WAVES / rs * 16 * qw][RQ_EPS] maxima of a super tile (two
-    // buffers where two waves share a request)
-    o += (uint32_t)RQ_WAVES * qw * 16 * RQ_EPS * 4;
+    L.stage = o;   // [rs][RQ_EPS][stage_pitch(RQ_WAVES / rs * 16 * qw)] maxima of a super
+    // tile (two buffers where two waves share a request)
+    o += (uint32_t)rs * RQ_EPS * stage_pitch(RQ_WAVES / rs * 16 * qw) * 4;
     L.sup = o;     // [RQ_WAVES / rs * 16 * qw][rq_hold] maxima of the last super tiles
     o += (uint32_t)RQ_WAVES / rs * qw * 16 * rq_hold(qw, rs) * 4;
     L.bytes = o;
@@ -91,8 +100,8 @@ __host__ __device__ inline GemmLayout gemm_layout(int tpq)
     o += (uint32_t)GM_SLOTS * GM_SLOT_LOADS * WAVE * 16;
     L.norms = o;   // [2][GM_ROWS] |x|^2 of a macro tile's rows
     o += 2u * GM_ROWS * 4;
-    L.stage = o;   // [64 * tpq][GM_EPS] a macro tile's maxima
-    o += 64u * tpq * GM_EPS * 4;
+    L.stage = o;   // [GM_EPS][stage_pitch(64 * tpq)] a macro tile's maxima
+    o += (uint32_t)GM_EPS * stage_pitch(64 * tpq) * 4;
     L.sup = o;     // [64 * tpq][GM_HOLD] maxima of the last macro tiles
     o += 64u * tpq * GM_HOLD * 4;
     L.bytes = o;

@@ -59,7 +59,8 @@ __global__ __launch_bounds__(GM_WAVES * WAVE, 1) void gemm_scan_kernel(const Sca
     extern __shared__ __align__(16) uint8_t smem[];
     const GemmLayout L = gemm_layout(TPQ);
     float *nslot = (float *)(smem + L.norms);        // [2][GM_ROWS] |x|^2 of macro tiles rt & 1
-    float *stg = (float *)(smem + L.stage);          // [QRY][GM_EPS] a macro tile's maxima
+    constexpr int PITCH = stage_pitch(QRY);
+    float *stg = (float *)(smem + L.stage);          // [GM_EPS][PITCH] a macro tile's maxima
 
     // Workgroup -> (chunk c, request tile t): workgroups go to the eight
     // XCDs round robin, so every request tile of one of the first
@@ -246,12 +247,15 @@ __global__ __launch_bounds__(GM_WAVES * WAVE, 1) void gemm_scan_kernel(const Sca
     };
     auto flush = [&](int rt) {
         const int part = lane & 3;
-        const float *src = stg + (fq0 + (lane >> 2)) * GM_EPS + part * 4;
+        const float *src = stg + part * 4 * PITCH + fq0 + (lane >> 2);
         float *const ent = A.m.ent + (sup0 + rt) * A.m.ent_s + (q0 + fq0) * A.m.ent_q;
 #pragma unroll
         for (int i = 0; i < GPW; ++i) {
             const int q = fq0 + 16 * i + (lane >> 2);
-            const f32x4 v = *(const f32x4 *)(src + 16 * i * GM_EPS);
+            f32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                v[e] = src[16 * i + e * PITCH];
             float m = max4(v);
             m = fmaxf(m, dpp<0xb1>(m));   // quad_perm [1,0,3,2]
             m = fmaxf(m, dpp<0x4e>(m));   // quad_perm [2,3,0,1]
@@ -352,7 +356,7 @@ __global__ __launch_bounds__(GM_WAVES * WAVE, 1) void gemm_scan_kernel(const Sca
 #pragma unroll
                 for (int r = 1; r < 16; ++r)
                     m = fmaxf(m, v[r]);
-                stg[(32 * TPQ * wq + 32 * u + (lane & 31)) * GM_EPS + 2 * (2 * wr + i) + hl] = m;
+                stg[(2 * (2 * wr + i) + hl) * PITCH + 32 * TPQ * wq + 32 * u + (lane & 31)] = m;
                 __builtin_amdgcn_sched_barrier(0);
             });
         });

@@ -86,7 +86,7 @@ __global__ __launch_bounds__(RQ_WAVES * WAVE, 1) void rq_scan_kernel(const ScanA
     const RqLayout L = rq_layout(QW, RS, KSTG, S);
     i32x4 *ring = (i32x4 *)(smem + L.ring);              // [S][F][64] fragments
     float *nslot = (float *)(smem + L.norms);            // [S][64] |x|^2 of a block's rows
-    float *stg = (float *)(smem + L.stage);              // [RS][NQS * QPW][RQ_EPS] maxima
+    float *stg = (float *)(smem + L.stage);              // [RS][RQ_EPS][PITCH] maxima
     float *sst = (float *)(smem + L.sup);                // [NQS * QPW][rq_hold] super tiles' maxima
 
     const int c = blockIdx.x;
@@ -228,7 +228,7 @@ __global__ __launch_bounds__(RQ_WAVES * WAVE, 1) void rq_scan_kernel(const ScanA
         asm volatile("" : "+v"(l));
         return l;
     };
-    constexpr int STG_BUF = NQS * QPW * RQ_EPS;   // floats of one staging buffer
+    constexpr int PITCH = stage_pitch(NQS * QPW), STG_BUF = RQ_EPS * PITCH;   // of one buffer
     auto stg_of = [&](int sl) { return RS == 2 ? (sl & 1) * STG_BUF : 0; };
     auto emit = [&](f32x4(&ac)[TA][QW], int b, int t0) {
         float m[4];
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(RQ_WAVES * WAVE, 1) void rq_scan_kernel(const ScanA
         const int i = NM == 4 ? (lr >> 1) | ((lr & 1) << 1) : lr % NM;
         const int e = (b % BPS) * TT + tile_of(t0 + i / QW);
         if (lr < NM)
-            stg[stg_of(b / BPS) + (slot_q * QPW + (i % QW) * 16 + (l & 15)) * RQ_EPS + e] = r;
+            stg[stg_of(b / BPS) + e * PITCH + slot_q * QPW + (i % QW) * 16 + (l & 15)] = r;
     };
     // entries of blocks past the chunk in its last super tile
     auto fill_past = [&]() {
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(RQ_WAVES * WAVE, 1) void rq_scan_kernel(const ScanA
             for (int t = 0; t < TT; ++t)
                 if (RS == 1 || t == half)
                     for (int q = lane; q < QPW; q += WAVE)
-                        stg[stg_of(b / BPS) + (slot_q * QPW + q) * RQ_EPS + (b % BPS) * TT + t] =
+                        stg[stg_of(b / BPS) + ((b % BPS) * TT + t) * PITCH + slot_q * QPW + q] =
                             __builtin_nanf("");
     };
     // super tile sl of the chunk from LDS to the workspace: 16 requests per
@@ -281,14 +281,17 @@ __global__ __launch_bounds__(RQ_WAVES * WAVE, 1) void rq_scan_kernel(const ScanA
     auto flush = [&](int sl) {
         static_assert(RQ_EPS == 16, "four lanes of four entries");
         const int l = fresh_lane(), part = l & 3, lq = l >> 2;
-        const float *src = stg + stg_of(sl) + (fq0 + lq) * RQ_EPS + part * 4;
+        const float *src = stg + stg_of(sl) + part * 4 * PITCH + fq0 + lq;
         float *const ent = A.m.ent + (sup0 + sl) * A.m.ent_s;
         // (out-of-range lanes fall outside the resource, so that every flush
         // is GPW stores at least)
 #pragma unroll
         for (int i = 0; i < GPW; ++i) {
             const int q = fq0 + 16 * i + lq;
-            const f32x4 v = *(const f32x4 *)(src + 16 * i * RQ_EPS);
+            f32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                v[e] = src[16 * i + e * PITCH];
             float m = max4(v);
             m = fmaxf(m, dpp<0xb1>(m));   // quad_perm [1,0,3,2]
             m = fmaxf(m, dpp<0x4e>(m));   // quad_perm [2,3,0,1]
