@@ -87,6 +87,33 @@ __host__ __device__ inline RqLayout rq_layout(int qw, int rs, int kstg, int stag
     return L;
 }
 
+// Workgroup -> (chunk c, request tile t) of a scan with request tiles (c =
+// n_chunks: nothing to do): workgroups go to the eight XCDs round robin, so
+// every request tile of one of the first 8 * (n_chunks / 8) chunks lands on one
+// XCD, where a bank line fetched for one is an L2 hit for the others. The last
+// n_chunks % 8 chunks take the remaining workgroups in order of XCD (x) and
+// then of dispatch (s): rank L among them, chunk base + L / n_qt, tile L % n_qt,
+// so that a chunk's tiles sit on as few XCDs as the counts allow, and no XCD
+// gets more workgroups than its share of them (three tiles of 85 chunks, whole
+// chunks to an XCD, left five XCDs of 32 units with 33: one more round of the
+// whole scan).
+__device__ __forceinline__ void chunk_and_tile(int n_chunks, int n_qt, int *c, int *t)
+{
+    const int per8 = 8 * n_qt;
+    const int full = (n_chunks / 8) * per8;
+    if ((int)blockIdx.x < full) {
+        const int rem = blockIdx.x % per8;
+        *t = rem / 8;
+        *c = (blockIdx.x / per8) * 8 + rem % 8;
+    } else {
+        const int j = blockIdx.x - full, x = j % 8, s = j / 8;
+        const int tail = (n_chunks % 8) * n_qt, q = tail / 8, r = tail % 8;
+        const int L = x * q + min(x, r) + s;
+        *t = L % n_qt;
+        *c = s < q + (x < r) ? (n_chunks / 8) * 8 + L / n_qt : n_chunks;
+    }
+}
+
 // Byte offsets of the GEMM-structured scan's LDS regions.
 struct GemmLayout {
     uint32_t ring, norms, stage, sup, bytes;

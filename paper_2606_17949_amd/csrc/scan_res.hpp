@@ -34,12 +34,8 @@ __global__ __launch_bounds__(RES_WAVES * WAVE, 1) void res_scan_kernel(const Sca
     extern __shared__ __align__(16) uint8_t smem[];
     i32x4 *qs = (i32x4 *)smem;               // [nks][NG][64] request fragments
 
-    // Workgroup -> (chunk c, request tile t): workgroups go to the XCDs round
-    // robin, so this map puts the request tiles of one chunk on one XCD.
-    const int per8 = 8 * A.n_qt;
-    const int rem = blockIdx.x % per8;
-    const int t = rem / 8;
-    const int c = (blockIdx.x / per8) * 8 + rem % 8;
+    int t, c;
+    chunk_and_tile(A.n_chunks, A.n_qt, &c, &t);
     if (c >= A.n_chunks)
         return;
     const int tid = threadIdx.x, lane = tid & 63;

@@ -55,6 +55,8 @@ def check(q, bank, k, label):
     ("f32", 130, 40_001, 12, 64),     # two request tiles, k at its maximum
     ("f32", 33, 300_017, 16, 10),     # super tiles of two row tiles, the last partial
     ("f32", 3, 70, 2_048, 5),         # the longest rows
+    ("f32", 92, 9_001, 1_024, 10),    # three request tiles of 85 chunks, five of them spread out
+    ("f32", 640, 3_001, 2_048, 4),    # forty request tiles, fewer chunks than XCDs
     ("bf16", 1, 1_000, 8, 10),
     ("bf16", 64, 100_003, 64, 10),
     ("bf16", 49, 33_333, 1_000, 7),   # ragged bf16 rows, four groups
