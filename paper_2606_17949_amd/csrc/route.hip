@@ -160,8 +160,9 @@ __global__ __launch_bounds__(LPT_THREADS) void lpt_order_kernel(const float *__r
 // predicted output length on the instance's model. Step t decides request
 // order[t] (arrival order when order is null). An instance outside the
 // request's candidate set (unavailable in mask, or over the request's budget
-// in the Eq. 2 cost) gets a base score of -inf: it is left out of both maxima
-// and never picked. WIDTH = 16 (I <= 16):
+// in the Eq. 2 cost) gets a NaN base score: it is left out of both maxima and
+// its key is NO_KEY whatever its queues and predictions hold, so that it is
+// never picked. WIDTH = 16 (I <= 16):
 // instance i = lane % 16, replicated in the four rows of 16 lanes, so every
 // reduction stays inside a row and leaves its result in every lane. WIDTH = 64:
 // instance i = lane + 64*u in register slot u. Per request: the latency
@@ -191,8 +192,12 @@ constexpr int ASSIGN_LDS_FLOATS = 8192;   // per buffer: chunk rows x instances 
 // A request's base scores and predicted lengths over the instance set, as the
 // loop reads them: what does not depend on the state.
 struct Pair {
-    float base, lv;   // base -inf: not a candidate
+    float base, lv;   // base NaN: not a candidate
 };
+
+// Keys of the pick as signed integers: S*Tmax bits, those of a non-candidate,
+// and what the maximum starts from (no candidate holds it).
+constexpr int NO_KEY = (int)0x80000000, LEAST_KEY = (int)0x80000001;
 
 template <int IPL, int WIDTH, bool DECIDED>
 __global__ __launch_bounds__(ASSIGN_THREADS) void assign_kernel(
@@ -255,8 +260,8 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void assign_kernel(
                 for (int u = 0; u < IPL; ++u) {
                     Pair v;
                     v.base = base_score(qv[u], C[u], cmax, wq, wc);
-                    if (!(cand[u] && v.base == v.base))
-                        v.base = -INFINITY;
+                    if (!cand[u])
+                        v.base = __builtin_nanf("");
                     v.lv = lv[u];
                     pair_s[buf][j][lane + WAVE * u] = v;
                 }
@@ -306,10 +311,8 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void assign_kernel(
         return __builtin_bit_cast(float,
                                   __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), src));
     };
-    // As signed integers, the bits of non-negative floats order as the floats
-    // and those of -inf lie below all of them. A step without candidates has
-    // Tmax TINY (no latency is that small), so that a base score of -inf makes
-    // S*Tmax -inf and not a NaN.
+    // As signed integers, the bits of non-negative floats order as the floats.
+    // Tmax is at least TINY (no latency is that small).
     constexpr int TINY = 0x00800000;
     // Lane NONE stands for "no instance" (WIDTH = 16: the rows past the first
     // are copies, so one of the last may).
@@ -336,10 +339,12 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void assign_kernel(
         fetch(0, bs, lv, l);
         fetch(1, bs1, lv1, l1);
         int tb = TINY;
+        bool cand[IPL];
 #pragma unroll
         for (int u = 0; u < IPL; ++u) {
             T[u] = latency(p[u], a[u], rP[u], rD[u], l, lv[u]);
-            tb = imax(tb, bs[u] >= 0.f ? __float_as_int(T[u]) : 0);
+            cand[u] = bs[u] >= 0.f;
+            tb = imax(tb, cand[u] ? __float_as_int(T[u]) : 0);
         }
         float tmax = __int_as_float(imax_all(tb));
         for (int jb = 0; jb < rows; jb += WAVE) {
@@ -347,29 +352,34 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void assign_kernel(
             for (int slot = 0; slot < nb; ++slot) {
                 float bs2[IPL], lv2[IPL], l2;   // the step after, in flight
                 fetch(jb + slot + 2, bs2, lv2, l2);
-                // S * Tmax; -inf for a non-candidate
-                int key[IPL], kb = 0;
+                // S * Tmax; the candidates by a test kept from the step before
+                // or, one slot, made again (256 instances: 397 ns a step for
+                // 421; 13 instances: 138 for 154)
+                int key[IPL], kb = LEAST_KEY;
 #pragma unroll
                 for (int u = 0; u < IPL; ++u) {
-                    key[u] = __float_as_int(fmaf(bs[u], tmax, wl * (tmax - T[u])));
+                    const float v = fmaf(bs[u], tmax, wl * (tmax - T[u]));
+                    const bool c = WIDTH == 64 ? cand[u] : bs[u] == bs[u];
+                    key[u] = c ? __float_as_int(v) : NO_KEY;
                     kb = imax(kb, key[u]);
                 }
                 // the state after a pick of the lane's instance, and the next
                 // step's latencies without and with it (0 for its non-candidates)
                 float p1[IPL], a1[IPL], T0[IPL], T1[IPL], tn[IPL];
                 int t0 = TINY;
+                bool cand1[IPL];
 #pragma unroll
                 for (int u = 0; u < IPL; ++u) {
                     p1[u] = p[u] + l;
                     a1[u] = a[u] + lv[u];
                     T0[u] = latency(p[u], a[u], rP[u], rD[u], l1, lv1[u]);
                     T1[u] = latency(p1[u], a1[u], rP[u], rD[u], l1, lv1[u]);
-                    const bool c1 = bs1[u] >= 0.f;
-                    t0 = imax(t0, c1 ? __float_as_int(T0[u]) : 0);
-                    tn[u] = c1 && (WIDTH == 64 || lane < NONE) ? T1[u] : 0.f;
+                    cand1[u] = bs1[u] >= 0.f;
+                    t0 = imax(t0, cand1[u] ? __float_as_int(T0[u]) : 0);
+                    tn[u] = cand1[u] && (WIDTH == 64 || lane < NONE) ? T1[u] : 0.f;
                 }
                 t0 = imax_all(t0);
-                const int kmax = imax_all(kb);   // (0, which no lane holds, without candidates)
+                const int kmax = imax_all(kb);   // (LEAST_KEY, which no lane holds, without candidates)
                 // lowest instance holding the maximum (slots ascend in index)
                 int istar, src;
                 float tp = T[0], tx = tn[0];
@@ -427,6 +437,7 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void assign_kernel(
                     T[u] = hit ? T1[u] : T0[u];
                     bs[u] = bs1[u];
                     lv[u] = lv1[u];
+                    cand[u] = cand1[u];
                     bs1[u] = bs2[u];
                     lv1[u] = lv2[u];
                 }
@@ -487,7 +498,7 @@ __device__ __forceinline__ void wide_for(F &&f)
 }
 
 struct WidePick {
-    int key, inst;      // S*Tmax bits of the wave's pick (-1: none), its instance
+    int key, inst;      // key of the wave's pick (LEAST_KEY: none), its instance
     int t0;             // the next step's largest latency bits with the state as it stands
     float tn;           // the pick's, after the pick (0: not its candidate)
 };
@@ -594,8 +605,8 @@ __global__ __launch_bounds__((CW + WIDE_PRODUCERS) * WAVE) void assign_wide_kern
                 for (int u = (k - GR / 2) * PS; u < (k - GR / 2 + 1) * PS; ++u) {
                     Pair v;
                     v.base = base_score(qv[u], C[u], cmax, wq, wc);
-                    if (!(C[u] == C[u] && v.base == v.base))
-                        v.base = -INFINITY;
+                    if (C[u] != C[u])
+                        v.base = __builtin_nanf("");
                     v.lv = model[u] >= 0 ? lv[u] : 0.f;
                     row[u * WAVE + lane] = v;
                 }
@@ -706,12 +717,13 @@ __global__ __launch_bounds__((CW + WIDE_PRODUCERS) * WAVE) void assign_wide_kern
     for (int t = 0; t < B; ++t) {
         float bs2[SL], lv2[SL], l2;   // the step after the next, in flight
         fetch(t + 2, bs2, lv2, l2);
-        int key[SL], kb = -1;
+        int key[SL], kb = LEAST_KEY;
         float p1[SL], a1[SL], T0[SL], T1[SL], tn[SL];
         int tz = 0;
 #pragma unroll
         for (int u = 0; u < SL; ++u) {
-            key[u] = __float_as_int(fmaf(bs[u], tmax, wl * (tmax - T[u])));
+            const float v = fmaf(bs[u], tmax, wl * (tmax - T[u]));
+            key[u] = bs[u] == bs[u] ? __float_as_int(v) : NO_KEY;
             kb = imax(kb, key[u]);
         }
 #pragma unroll
@@ -741,12 +753,11 @@ __global__ __launch_bounds__((CW + WIDE_PRODUCERS) * WAVE) void assign_wide_kern
                 bp = bs[u];
             }
         }
-        if (mk == 0 || kb < 0)
-            mk = 1;
-        const int src = (int)__builtin_ctzll(mk);
+        const bool none = kb == LEAST_KEY;
+        const int src = none ? 0 : (int)__builtin_ctzll(mk);
         if (lane == src) {
             S.pick[t & 1][wave] =
-                WidePick{kb, kb < 0 ? -1 : i0 + us * WAVE, tz, kb < 0 ? 0.f : tx};
+                WidePick{kb, none ? -1 : i0 + us * WAVE, tz, none ? 0.f : tx};
             S.cap[t & 1][wave] = WideCap{tp, bp};
         }
         stream_barrier();
