@@ -311,7 +311,10 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void assign_kernel(
         return __builtin_bit_cast(float,
                                   __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), src));
     };
-    // As signed integers, the bits of non-negative floats order as the floats.
+    // As signed integers, the bits of non-negative floats order as the floats,
+    // above those of any negative one (a negative quality may give some
+    // instances scores below zero; qualities lie in [0, 1], so the best one's
+    // is not).
     // Tmax is at least TINY (no latency is that small).
     constexpr int TINY = 0x00800000;
     // Lane NONE stands for "no instance" (WIDTH = 16: the rows past the first
@@ -343,7 +346,7 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void assign_kernel(
 #pragma unroll
         for (int u = 0; u < IPL; ++u) {
             T[u] = latency(p[u], a[u], rP[u], rD[u], l, lv[u]);
-            cand[u] = bs[u] >= 0.f;
+            cand[u] = bs[u] == bs[u];
             tb = imax(tb, cand[u] ? __float_as_int(T[u]) : 0);
         }
         float tmax = __int_as_float(imax_all(tb));
@@ -374,7 +377,7 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void assign_kernel(
                     a1[u] = a[u] + lv[u];
                     T0[u] = latency(p[u], a[u], rP[u], rD[u], l1, lv1[u]);
                     T1[u] = latency(p1[u], a1[u], rP[u], rD[u], l1, lv1[u]);
-                    cand1[u] = bs1[u] >= 0.f;
+                    cand1[u] = bs1[u] == bs1[u];
                     t0 = imax(t0, cand1[u] ? __float_as_int(T0[u]) : 0);
                     tn[u] = cand1[u] && (WIDTH == 64 || lane < NONE) ? T1[u] : 0.f;
                 }
@@ -424,8 +427,8 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void assign_kernel(
                     for (int u = 0; u < IPL; ++u) {
                         const int i = inst(u);
                         if (lane < (WIDTH == 16 ? 16 : WAVE) && i < I)
-                            drow[i] = bs[u] >= 0.f ? full_score(bs[u], T[u], tmax, wl)
-                                                   : __builtin_nanf("");
+                            drow[i] = bs[u] == bs[u] ? full_score(bs[u], T[u], tmax, wl)
+                                                     : __builtin_nanf("");
                     }
                 }
                 tmax = __int_as_float(imax(t0, __float_as_int(tnext)));
@@ -708,7 +711,7 @@ __global__ __launch_bounds__((CW + WIDE_PRODUCERS) * WAVE) void assign_wide_kern
         for (int i = lane; i < Sh::IP; i += WAVE) {
             const int m = i < I ? in.model[i] : -1;
             const Pair v = S.pair[0][0][i];
-            if ((unsigned)m < (unsigned)M && v.base >= 0.f)
+            if ((unsigned)m < (unsigned)M && v.base == v.base)
                 tt = imax(tt, __float_as_int(latency(in.p[i], in.a[i], 1.f / in.P[i],
                                                      1.f / in.D[i], l, v.lv)));
         }
@@ -732,7 +735,7 @@ __global__ __launch_bounds__((CW + WIDE_PRODUCERS) * WAVE) void assign_wide_kern
             a1[u] = a[u] + lv[u];
             T0[u] = latency(p[u], a[u], rP[u], rD[u], l1, lv1[u]);
             T1[u] = latency(p1[u], a1[u], rP[u], rD[u], l1, lv1[u]);
-            const bool c1 = bs1[u] >= 0.f;
+            const bool c1 = bs1[u] == bs1[u];
             tz = imax(tz, c1 ? __float_as_int(T0[u]) : 0);
             tn[u] = c1 ? T1[u] : 0.f;
         }
@@ -792,8 +795,8 @@ __global__ __launch_bounds__((CW + WIDE_PRODUCERS) * WAVE) void assign_wide_kern
 #pragma unroll
             for (int u = 0; u < SL; ++u)
                 if (i0 + u * WAVE < I)
-                    drow[i0 + u * WAVE] = bs[u] >= 0.f ? full_score(bs[u], T[u], tmax, wl)
-                                                       : __builtin_nanf("");
+                    drow[i0 + u * WAVE] = bs[u] == bs[u] ? full_score(bs[u], T[u], tmax, wl)
+                                                         : __builtin_nanf("");
         }
         tmax = __int_as_float(imax(imax(tm, __float_as_int(tnext)), TINY));
 #pragma unroll

@@ -1,6 +1,6 @@
 """The greedy pass where values that the ordinary inputs do not hold meet the
 candidate set (GPU): predictions and queues that are no numbers or infinite on
-instances that are no candidates.
+instances that are no candidates, and qualities below zero on some that are.
 
 The reference is the loop itself in float64, step by step from the GPU's own
 picks: a pick must be a candidate whose score is within 1e-5 of the best one
@@ -92,3 +92,16 @@ def test_queues_of_masked_instances(I, value):
         r[mask == 0] = 0.0                # (a lost instance that decodes nothing)
         run(qh, lh, pl, dataclasses.replace(inst, decode_rate=r), w, mask,
             f"decode rate 0 I={I} w={w}")
+
+
+@pytest.mark.parametrize("I", COUNTS)
+def test_negative_qualities(I):
+    """A candidate whose quality is below zero is one all the same, in the
+    maxima and for the pick (the best score is not below zero here)."""
+    B, M = 70, 5
+    for w in ((0.3, 0.4, 0.3), (0.6, 0.4, 0.0), (0.8, 0.1, 0.1)):
+        qh, lh, pl, inst = opt.random_case(B, M, I, seed=I + 2)
+        qh -= np.float32(0.6)
+        qh[:, 0] = np.float32(0.05)       # one model's is not
+        qh[::4, 0] = -np.float32(0.01)    # (or hardly below)
+        run(qh, lh, pl, inst, w, label=f"negative qualities I={I} w={w}")
