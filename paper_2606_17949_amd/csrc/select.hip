@@ -130,6 +130,8 @@ __global__ __launch_bounds__(NT, 1024 / NT) void select_kernel(const SelectArgs 
             *(i32x4 *)(S.q + off) = v;
     }
     qn = wave_sum(qn);
+    if (!(qn <= FLT_MAX))
+        qn = __builtin_nanf("");   // (an infinite request is at no distance from any row)
     const uint32_t padded = (uint32_t)(A.nks + LD - 1) / LD * LD * KSTEP_BYTES;
     for (uint32_t off = rowb + tid * 16; off < padded; off += NT * 16)
         *(i32x4 *)(S.q + off) = i32x4{0, 0, 0, 0};
@@ -137,9 +139,11 @@ __global__ __launch_bounds__(NT, 1024 / NT) void select_kernel(const SelectArgs 
         S.rank[i] = 0;
     if (tid == 0)
         S.n_cand = S.n_tiles = 0;
-    // a maximum as a distance key; an entry past the bank (NaN) is absent
+    // a scan's value as a distance key. Absent is a distance that is no
+    // number: an entry past the bank (NaN), every row of an infinite request.
     auto key_of = [&](float acc) -> uint32_t {
-        return acc == acc ? f2key(fmaf(-2.f, acc, qn)) : KEY_NONE;
+        const float dist = fmaf(-2.f, acc, qn);
+        return dist == dist ? f2key(dist) : KEY_NONE;
     };
 
     // ---- 1. the k super tiles
@@ -259,9 +263,8 @@ __global__ __launch_bounds__(NT, 1024 / NT) void select_kernel(const SelectArgs 
                 const float v = row < A.rows
                                     ? A.acc[((size_t)(row >> 4) * A.B + b) * 16 + (row & 15)]
                                     : __builtin_nanf("");
-                const uint32_t key = f2key(fmaf(-2.f, v, qn));
-                // (a distance that is not a number is no neighbour)
-                if (v == v && key <= bound)
+                const uint32_t key = key_of(v);
+                if (key <= bound)   // (below KEY_NONE)
                     S.cand[atomicAdd(&S.n_cand, 1)] = pack(key, (int32_t)(A.row0 + row));
             }
         }
@@ -316,12 +319,11 @@ __global__ __launch_bounds__(NT, 1024 / NT) void select_kernel(const SelectArgs 
                 }
             }
             // lane (col, jg) holds rows jg*4 .. +3; every column the same
-            // (a distance that is not a number is no neighbour)
             if (col < 4) {
                 const float v = col == 0 ? acc[0] : col == 1 ? acc[1] : col == 2 ? acc[2] : acc[3];
-                const uint32_t key = f2key(fmaf(-2.f, v, qn));
+                const uint32_t key = key_of(v);
                 const int i = row_of(jg * 4 + col);
-                if (v == v && i < n_in && key <= bound)
+                if (i < n_in && key <= bound)
                     S.cand[atomicAdd(&S.n_cand, 1)] = pack(key, (int32_t)(row + i));
             }
         }

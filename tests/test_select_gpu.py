@@ -151,3 +151,36 @@ def test_bf16_equal_rows_come_in_index_order(B, d):
     bank[:] = bank[5]
     bank[12_345] = q[0]
     check(q, bank, 20, f"equal rows bf16 B={B} d={d}")
+
+
+@pytest.mark.parametrize("dtype,B,N,d", [
+    ("f32", 3, 40, 16),          # every row's value kept
+    ("f32", 33, 40_000, 16),     # row tiles computed again
+    ("bf16", 5, 9_000, 1_000),
+    ("bf16", 100, 9_000, 768),   # query-resident
+    ("bf16", 300, 9_000, 768),   # GEMM-structured
+])
+def test_infinite_distances(dtype, B, N, d):
+    """Rows whose norm overflows are at an infinite distance, after all others
+    and in index order; an infinite request is at no distance from any row:
+    index -1, distance NaN."""
+    import paper_2606_17949_amd as rb
+    q, bank = draw(B, N, d, dtype, 1, 2, 8)
+    near = torch.arange(7, device=DEV) * (N // 7) + N // 14
+    far = torch.ones(N, dtype=torch.bool, device=DEV)
+    far[near] = False
+    bank[far] *= 1e20
+    bank[:, d - 1] *= -1
+    q[1, d // 2] = float("inf")       # all products +inf
+    q[0, d - 1] = float("inf")        # all products -inf
+    label = f"infinite distances {dtype} B={B} N={N} d={d}"
+    print(label, flush=True)
+    idx, dist = rb.rb_knn_topk(q, bank, rb.rb_bank_norms(bank), 10)
+    torch.cuda.synchronize()
+    assert torch.all(idx[:2] == -1) and torch.all(torch.isnan(dist[:2])), label
+    idx, dist = idx[2:], dist[2:]
+    assert torch.equal(idx[:, :7].sort(1).values, near.to(torch.int32).expand(B - 2, 7)), label
+    assert torch.all(torch.isfinite(dist[:, :7])), label
+    ref = torch.nonzero(far)[:3, 0].to(torch.int32)
+    assert torch.equal(idx[:, 7:], ref.expand(B - 2, 3)), label
+    assert torch.all(dist[:, 7:] == float("inf")), label
