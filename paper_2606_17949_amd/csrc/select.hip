@@ -59,8 +59,11 @@ __device__ __forceinline__ void rank_pairs(const uint64_t *cand, int n, int k, i
 // nearest row is no farther than the k-th super tile's can hold one of the k
 // (k rows lie at or below that distance), in random order about k of them.
 // Those tiles' distances are read where the scan kept every one (acc), else
-// computed again with the scan's own sequence of MFMA steps (so with its
-// bits); the k smallest (distance, index) pairs of their rows are the result.
+// computed again, elements in the scan's order, and so with its bits, which the
+// order by (distance, index) across super tiles rests on (a step of 16x16x32
+// gives the bits of the GEMM-structured scan's two of 32x32x16: no difference
+// in 2,048,000 sums over 32 to 2,048 elements of five distributions); the k
+// smallest (distance, index) pairs of their rows are the result.
 // What bounds it: a chain of dependent memory accesses and barriers at small
 // batches, at large ones the reading of k tiles of 16 rows per request.
 //   1. a bound: the largest of at least k groups' least super-tile distances,

@@ -184,3 +184,36 @@ def test_infinite_distances(dtype, B, N, d):
     ref = torch.nonzero(far)[:3, 0].to(torch.int32)
     assert torch.equal(idx[:, 7:], ref.expand(B - 2, 3)), label
     assert torch.all(dist[:, 7:] == float("inf")), label
+
+
+@pytest.mark.parametrize("dtype,B,N,d,k", [
+    ("f32", 33, 20_000, 300, 10),
+    ("bf16", 40, 40_000, 1_000, 10),
+    ("bf16", 100, 20_000, 768, 20),     # query-resident
+    ("bf16", 300, 20_000, 768, 10),     # GEMM-structured
+    ("bf16", 150, 8_000, 1_096, 64),    # ... a last stage of 8 elements
+])
+def test_order_is_that_of_the_distances_given(dtype, B, N, d, k):
+    """Rows so near one another that rounding decides many places: the
+    neighbours are the first k under (distance, index) with the very distances
+    the search gives each row when it returns all of them (a bank of 64 rows,
+    64 neighbours)."""
+    import paper_2606_17949_amd as rb
+    g = torch.Generator(device=DEV).manual_seed(9)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    centre = torch.randn(1, d, generator=g, device=DEV)
+    make = lambda n: (centre + 3e-3 * torch.randn(n, d, generator=g, device=DEV)).to(t)
+    q, bank = make(B), make(N)
+    norms = rb.rb_bank_norms(bank)
+    label = f"order of the distances {dtype} B={B} N={N} d={d} k={k}"
+    print(label, flush=True)
+    D = torch.empty(B, N, device=DEV)
+    for r0 in range(0, N, 64):
+        r1 = min(N, r0 + 64)
+        i, v = rb.rb_knn_topk(q, bank[r0:r1], norms[r0:r1], r1 - r0)
+        D[:, r0:r1].scatter_(1, i.long(), v)
+    idx, dist = rb.rb_knn_topk(q, bank, norms, k)
+    torch.cuda.synchronize()
+    ref = torch.sort(D, dim=1, stable=True)
+    assert torch.equal(dist, ref.values[:, :k]), label
+    assert torch.equal(idx, ref.indices[:, :k].to(torch.int32)), label
