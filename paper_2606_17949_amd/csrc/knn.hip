@@ -362,11 +362,11 @@ hipError_t launch_knn(const KnnPlan &p, const void *queries, const void *bank,
     sa.split_tiles = p.kind == 2;
     sa.m.sup = (float *)(w + p.off_sup);
     sa.m.ent = (float *)(w + p.off_ent);
-    // super tiles request by request; the entries of the scans with chunks
-    // super tile by super tile, as their workgroups write them
+    // super tiles request by request; the entries super tile by super tile, as
+    // the scans write them
     sa.m.sup_q = p.n_sup;
-    sa.m.ent_s = p.kind == 0 ? p.eps : (long)p.B * p.eps;
-    sa.m.ent_q = p.kind == 0 ? p.n_sup * p.eps : p.eps;
+    sa.m.ent_s = (long)p.B * p.eps;
+    sa.m.ent_q = p.eps;
     sa.acc = p.keep_acc ? sa.m.ent : nullptr;
     sa.list_key = (uint32_t *)(w + p.off_lkey);
     sa.list_idx = (int32_t *)(w + p.off_lidx);
@@ -406,7 +406,6 @@ hipError_t launch_knn(const KnnPlan &p, const void *queries, const void *bank,
             a.n_tiles = (a.rows + 15) / 16;
             a.n_sup = (a.n_tiles + p.eps - 1) / p.eps;
             a.m.sup_q = sa.m.sup_q = a.n_sup;
-            a.m.ent_q = sa.m.ent_q = a.n_sup * p.eps;
         }
         if (timed && seg == 0 && (e = hipEventRecord(t_scan_begin, s)) != hipSuccess)
             return e;

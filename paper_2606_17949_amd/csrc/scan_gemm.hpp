@@ -10,8 +10,6 @@ namespace rb {
 
 namespace {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
 // One v_mfma_f32_32x32x16_bf16: D = A*B + C over 16 elements of K, A 32 bank
 // rows, B 32 requests. Lane l holds, of both operands, row (or request) l % 32
 // at K positions 8*(l/32) .. 8*(l/32)+7; of D, request l % 32 of rows

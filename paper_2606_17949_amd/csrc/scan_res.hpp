@@ -116,15 +116,69 @@ __global__ __launch_bounds__(RES_WAVES * WAVE, 1) void res_scan_kernel(const Sca
         const int g = 4 * v + gsw, q = q0 + g * 16 + col;
         own[v] = g < NG && q < A.B;
         sup[v] = A.m.sup + s0 + (own[v] ? q : 0) * A.m.sup_q;
-        ent[v] = A.m.ent + t0 + (own[v] ? q : 0) * A.m.ent_q;
+        ent[v] = A.m.ent + s0 * A.m.ent_s + (own[v] ? q : 0) * A.m.ent_q;
     }
+    // They wait in registers, entries until their super tile is complete,
+    // super tiles until there are RES_HOLD, and go out as whole lines (one
+    // value at a time, a line left the cache with a piece of it between two
+    // stores: 64 requests over 4,000,000 x 128 bf16 took 386 us for 250, 16
+    // over 2,000,000 x 384 fp32 678 for 578).
+    static_assert(RES_HOLD == 16 && SEL_MAX_EPS <= 16, "what a lane holds");
+    f32x16 ehold[NQ], shold[NQ];
+    const float nan = __builtin_nanf("");
+    auto clear = [&](f32x16(&h)[NQ]) {
+#pragma unroll
+        for (int v = 0; v < NQ; ++v)
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                h[v][e] = nan;
+    };
+    // the super tile's entries (those past the bank hold no number)
+    auto put_ent = [&]() {
+#pragma unroll
+        for (int v = 0; v < NQ; ++v) {
+            if (own[v]) {
+                if (A.eps == 2)
+                    *(f32x2 *)ent[v] = f32x2{ehold[v][0], ehold[v][1]};
+#pragma unroll
+                for (int e = 0; e < 16; e += 4)
+                    if (e + 4 <= A.eps)
+                        *(f32x4 *)(ent[v] + e) = f32x4{ehold[v][e], ehold[v][e + 1],
+                                                       ehold[v][e + 2], ehold[v][e + 3]};
+            }
+            ent[v] += A.m.ent_s;
+        }
+        clear(ehold);
+    };
+    auto put_sup = [&](int n) {   // the first n held
+#pragma unroll
+        for (int v = 0; v < NQ; ++v) {
+            if (own[v]) {
+#pragma unroll
+                for (int e = 0; e < RES_HOLD; e += 4) {
+                    if (e + 4 <= n)
+                        *(f32x4_any *)(sup[v] + e) = f32x4{shold[v][e], shold[v][e + 1],
+                                                           shold[v][e + 2], shold[v][e + 3]};
+                    else
+#pragma unroll
+                        for (int i = e; i < e + 4; ++i)
+                            if (i < n)
+                                sup[v][i] = shold[v][i];
+                }
+            }
+            sup[v] += n;
+        }
+    };
+    clear(ehold);
+    clear(shold);
 
     f32x4 acc[NG];
     float smax[NQ];
 #pragma unroll
     for (int v = 0; v < NQ; ++v)
-        smax[v] = __builtin_nanf("");
-    int tile = 0, s = 0, es = 0;   // tile of the share, its k-step, its place in the super tile
+        smax[v] = nan;
+    // tile of the share, its k-step, its place in the super tile, that one's among those held
+    int tile = 0, s = 0, es = 0, ss = 0;
     auto start_tile = [&]() {
         // the accumulators start from -|x|^2/2 of their rows (-inf past the bank)
         const f32x4 xn = *(const f32x4 *)(norms + (tile & 31) * 16 + jg * 4);
@@ -155,20 +209,19 @@ __global__ __launch_bounds__(RES_WAVES * WAVE, 1) void res_scan_kernel(const Sca
 #pragma unroll
         for (int v = 0; v < NQ; ++v) {
             const float r = rows_max4(m[4 * v], m[4 * v + 1], m[4 * v + 2], m[4 * v + 3]);
-            if (A.eps > 1) {
-                smax[v] = fmaxf(smax[v], r);
-                if (own[v] && !A.acc)
-                    ent[v][tile] = r;
-                if (last) {
-                    if (own[v])
-                        *sup[v] = smax[v];
-                    smax[v] = __builtin_nanf("");
-                }
-            } else if (own[v]) {
-                *sup[v] = r;
-            }
+            ehold[v][es] = r;
+            smax[v] = fmaxf(smax[v], r);
+            shold[v][ss] = smax[v];
             if (last)
-                ++sup[v];
+                smax[v] = nan;
+        }
+        if (last) {
+            if (A.eps > 1 && !A.acc)
+                put_ent();
+            if (++ss == RES_HOLD) {
+                put_sup(RES_HOLD);
+                ss = 0;
+            }
         }
         es = last ? 0 : es + 1;
         ++tile;
@@ -204,14 +257,7 @@ __global__ __launch_bounds__(RES_WAVES * WAVE, 1) void res_scan_kernel(const Sca
             }
         });
     }
-    // entries of the last super tile past the bank
-    if (A.eps > 1 && !A.acc && s1 > s0 && s1 * A.eps > t0 + n_tiles) {
-#pragma unroll
-        for (int v = 0; v < NQ; ++v)
-            if (own[v])
-                for (long e = n_tiles; e < s1 * A.eps - t0; ++e)
-                    ent[v][e] = __builtin_nanf("");
-    }
+    put_sup(ss);
     // (no global-to-LDS load may still be in flight when the workgroup ends)
     wait_vmcnt<0>();
 }

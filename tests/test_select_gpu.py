@@ -54,6 +54,10 @@ def check(q, bank, k, label):
     ("f32", 100, 5_003, 300, 20),     # seven groups, rows of 18.75 k-steps
     ("f32", 130, 40_001, 12, 64),     # two request tiles, k at its maximum
     ("f32", 33, 300_017, 16, 10),     # super tiles of two row tiles, the last partial
+    ("f32", 5, 1_000_003, 8, 10),     # super tiles of four row tiles
+    ("f32", 20, 1_200_007, 8, 20),    # ... of eight
+    ("bf16", 64, 2_200_021, 8, 10),   # ... of sixteen
+    ("f32", 300, 150_003, 512, 10),   # more super tiles to a wave than it holds
     ("f32", 3, 70, 2_048, 5),         # the longest rows
     ("f32", 92, 9_001, 1_024, 10),    # three request tiles of 85 chunks, five of them spread out
     ("f32", 640, 3_001, 2_048, 4),    # forty request tiles, fewer chunks than XCDs
