@@ -194,8 +194,17 @@ long plan_chunks(const KnnPlan *p, int num_cu, int reserve)
     return chunks < 1 ? 1 : chunks;
 }
 
+// Groups of 16 requests that fit LDS for every k-step of the LDS-resident
+// scan, beside the norms of every wave's tiles; at most RES_MAX_NG.
+constexpr size_t RES_NORM_BYTES = RES_WAVES * 2 * 256 * sizeof(float);
+int res_groups(int nks)
+{
+    const int ng = (int)((LDS_LIMIT - RES_NORM_BYTES) / ((size_t)nks * WAVE * 16));
+    return ng < RES_MAX_NG ? ng : RES_MAX_NG;
+}
+
 // The LDS-resident scan. Request tiles: as many groups of 16 requests as fit
-// LDS for every k-step, at most RES_MAX_NG, evenly over the tiles. Waves:
+// (res_groups), evenly over the tiles. Waves:
 // eight per workgroup, fewer when there are not enough super tiles to go
 // round (a bank of 2,048 rows is 128 row tiles: one wave on each of 128
 // compute units).
@@ -204,13 +213,10 @@ void plan_res(KnnPlan *p, int num_cu, int reserve, size_t limit)
     const int B = p->B;
     const long rowb = (long)p->d * (p->dtype == 1 ? 2 : 4);
     const int groups = B > 0 ? (B + 15) / 16 : 1;
-    const size_t norms = RES_WAVES * 2 * 256 * sizeof(float);   // of every wave's tiles
-    int ng = (int)((LDS_LIMIT - norms) / ((size_t)p->nks * WAVE * 16));
-    if (ng > RES_MAX_NG)
-        ng = RES_MAX_NG;
+    const int ng = res_groups(p->nks);
     p->n_qt = (groups + ng - 1) / ng;
     p->ng = (groups + p->n_qt - 1) / p->n_qt;
-    p->lds_bytes = (size_t)p->nks * p->ng * WAVE * 16 + norms;
+    p->lds_bytes = (size_t)p->nks * p->ng * WAVE * 16 + RES_NORM_BYTES;
     // super tiles: single row tiles up to SEL_WANT_SUP of them
     const long all_tiles = ((long)p->N + 15) / 16;
     p->eps = 1;
@@ -289,8 +295,12 @@ int plan_knn(int B, int N, int d, int dtype, int k, int num_cu, KnnPlan *p, int 
     // compute unit (below, its start, every wave loading its queries, costs
     // more than that of the LDS-resident scan). Other bf16 batches of more
     // than 64 requests go to the GEMM-structured scan, in tiles of 128
-    // requests if one tile holds them, else of 256. Everything else, all fp32
-    // batches among it, goes to the LDS-resident scan.
+    // requests if one tile holds them, else of 256; so do smaller ones that do
+    // not fit LDS as one tile (33 to 64 requests of 1,536 or 2,048 elements:
+    // the LDS-resident scan reads the bank for two), over at least a macro
+    // tile of rows per compute unit (64 requests, 1,536 elements: 490 us for
+    // 577 over 700,000 rows, 61 for 64 over 48,001, but 57 for 40 over 32,001).
+    // Everything else, all fp32 batches among it, goes to the LDS-resident scan.
     const bool rq_rows = B > 64 || (long)N >= (long)RQ_SMALL_B_MIN_ROWS * num_cu;
     if (dtype == 1 && d % (4 * vec) == 0 && rq_rows && rq_shape(p->nks, B, &p->qw, &p->rs)) {
         p->kind = 1;
@@ -298,7 +308,8 @@ int plan_knn(int B, int N, int d, int dtype, int k, int num_cu, KnnPlan *p, int 
         p->lds_bytes =
             rq_layout(p->qw, p->rs, p->nks / rq_spb(p->nks), RQ_SLOTS).bytes;
         plan_chunked(p, num_cu, reserve, limit);
-    } else if (dtype == 1 && B > 64) {
+    } else if (dtype == 1 && (B > 64 || ((B + 15) / 16 > res_groups(p->nks) &&
+                                         (long)N >= (long)GM_ROWS * num_cu))) {
         p->kind = 2;
         p->qw = B > 128 ? 4 : 2;
         p->n_qt = (B + 64 * p->qw - 1) / (64 * p->qw);

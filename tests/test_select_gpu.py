@@ -143,6 +143,9 @@ def test_bank_in_parts_matches_one_pass():
     (128, 5_000, 200, 64),      # tiles of 128 requests, ragged rows
     (90, 3_000, 1_000, 10),
     (1_025, 2_050, 136, 10),    # five request tiles
+    (64, 70_001, 1_536, 10),    # a small batch too long for LDS as one tile
+    (33, 65_536, 2_048, 10),    # ... at the fewest requests and rows
+    (33, 65_535, 2_048, 10),    # ... and one row below
 ])
 def test_bf16_scans_are_exact(B, N, d, k):
     q, bank = draw(B, N, d, "bf16", -1, 1, 6)
