@@ -111,16 +111,23 @@ __global__ __launch_bounds__(NT, 1024 / NT) void select_kernel(const SelectArgs 
     };
 
     // the first super tiles stay in registers: their loads go out before
-    // anything is waited for
-    // (a wave's share is contiguous, so that every wave has some)
+    // anything is waited for. The waves take them in turn, 16 at a time (4 of
+    // a few), so that near rows that follow one another in the bank are not
+    // all one wave's and every wave's least distance is as near as another's (a
+    // bank in the order of its clusters, contiguous shares / in turn: 64 x
+    // 100,000 x 768 178 / 57 us, 256 x 1,000,000 x 768 in 32 clusters 479 / 385;
+    // rows in random order the same).
     constexpr int SV = SEL_WANT_SUP / NT;
-    const long share = (A.n_sup + NW - 1) / NW;
-    const long sup0 = wave * share, sup1 = min(A.n_sup, sup0 + share);
+    const int deal = A.n_sup >= 16 * 16 * NW ? 4 : 2;   // log2 of a turn
+    auto sup_at = [&](int u) -> long {
+        const int i = u * WAVE + lane;
+        return (((long)(i >> deal) * NW + wave) << deal) + (i & ((1 << deal) - 1));
+    };
     float sv[SV];
 #pragma unroll
     for (int u = 0; u < SV; ++u) {
-        const long j = sup0 + lane + u * WAVE;
-        sv[u] = j < sup1 ? sup(j) : __builtin_nanf("");
+        const long j = sup_at(u);
+        sv[u] = j < A.n_sup ? sup(j) : __builtin_nanf("");
     }
     // |q|^2 (in every wave: the same sums in the same order), and the request
     // in LDS, zero past the row
@@ -154,9 +161,19 @@ __global__ __launch_bounds__(NT, 1024 / NT) void select_kernel(const SelectArgs 
     auto each_sup = [&](auto f) {   // f(key, index) of this thread's super tiles
 #pragma unroll
         for (int u = 0; u < SV; ++u)
-            f(key_of(sv[u]), (int)sup0 + lane + u * WAVE);
-        for (long j = sup0 + lane + SV * WAVE; j < sup1; j += WAVE)
-            f(key_of(sup(j)), (int)j);
+            f(key_of(sv[u]), (int)sup_at(u));
+        for (int u = SV; ((long)u * NT) < A.n_sup; ++u) {
+            const long j = sup_at(u);
+            if (j < A.n_sup)
+                f(key_of(sup(j)), (int)j);
+        }
+    };
+    // a distance key and a margin far above any fp32 rounding difference, so
+    // that it also bounds if a row's two evaluations should ever differ in
+    // their last bits
+    auto widen = [&](uint32_t key) -> uint32_t {
+        const float t = key2f(key);
+        return min(KEY_NONE - 1, f2key(t + ldexpf(qn + fabsf(t) + 1.f, -18)));
     };
     each_sup([&](uint32_t key, int) { least = min(least, key); });
     const auto umin = [](uint32_t x, uint32_t y) { return x < y ? x : y; };
@@ -222,13 +239,9 @@ __global__ __launch_bounds__(NT, 1024 / NT) void select_kernel(const SelectArgs 
     }
     __syncthreads();
 
-    // ---- 2. their row tiles (the bound widened by a margin far above any
-    // fp32 rounding difference, so that it also holds if a row's two
-    // evaluations should ever differ in their last bits)
-    if (n_best == k) {
-        const float t = key2f((uint32_t)(S.best[k - 1] >> 32));
-        bound = min(KEY_NONE - 1, f2key(t + ldexpf(qn + fabsf(t) + 1.f, -18)));
-    }
+    // ---- 2. their row tiles
+    if (n_best == k)
+        bound = widen((uint32_t)(S.best[k - 1] >> 32));
     int n_items;   // what a round takes SEL_ROUND * 16 rows of
     if (A.acc) {
         n_items = n_best * A.eps * 16;
@@ -238,16 +251,42 @@ __global__ __launch_bounds__(NT, 1024 / NT) void select_kernel(const SelectArgs 
         for (int i = tid; i < n_best * A.eps; i += NT) {
             const int j = i / A.eps, e = i - j * A.eps;
             const int s = (int)(uint32_t)S.best[j];
-            if (A.eps == 1 || key_of(ent(s, e)) <= bound)
-                S.tiles[atomicAdd(&S.n_tiles, 1)] = s * A.eps + e;
+            const uint32_t key = A.eps == 1 ? (uint32_t)(S.best[j] >> 32) : key_of(ent(s, e));
+            if (key <= bound) {
+                const int at = atomicAdd(&S.n_tiles, 1);
+                S.tiles[at] = s * A.eps + e;
+                S.cand[at] = pack(key, s * A.eps + e);
+            }
         }
     }
     // the rows found in earlier launches over other parts of the bank
     if (tid < k && A.carry_in)
         S.prev[tid] = pack(A.list_key[(size_t)b * k + tid], A.list_idx[(size_t)b * k + tid]);
     __syncthreads();
-    if (!A.acc)
+    if (!A.acc) {
         n_items = S.n_tiles * 16;
+        // Many more than k row tiles: near rows follow one another in the
+        // bank, the k-th super tile lies outside them and its distance is a
+        // loose bound. The k-th of the row tiles' own distances is one too (a
+        // row each), and leaves about k of them in any order of the bank
+        // (1,000 clusters one after the other: 256 x 1,000,000 x 768 481 / 390
+        // us, 1,024 x 1,000,000 x 1,024 2,285 / 1,825).
+        if (n_items > (k + NW) * 16) {
+            rank_pairs<NT>(S.cand, S.n_tiles, k, S.rank, S.best);
+            __syncthreads();
+            bound = min(bound, widen((uint32_t)(S.best[k - 1] >> 32)));
+            const int n = S.n_tiles;
+            __syncthreads();
+            if (tid == 0)
+                S.n_tiles = 0;
+            __syncthreads();
+            for (int i = tid; i < n; i += NT)
+                if ((uint32_t)(S.cand[i] >> 32) <= bound)
+                    S.tiles[atomicAdd(&S.n_tiles, 1)] = (int)(uint32_t)S.cand[i];
+            __syncthreads();
+            n_items = S.n_tiles * 16;
+        }
+    }
 
     // ---- 3. their rows
     int n_prev = A.carry_in ? k : 0;

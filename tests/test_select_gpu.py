@@ -82,6 +82,27 @@ def test_equal_rows_come_in_index_order(dtype, B, d):
     check(q, bank, 64, f"equal rows but one {dtype}")
 
 
+@pytest.mark.parametrize("dtype,B,N,d,k", [
+    ("f32", 33, 40_000, 16, 10),       # single row tiles
+    ("f32", 9, 300_017, 16, 10),       # super tiles of two
+    ("bf16", 64, 2_200_021, 8, 20),    # ... of sixteen
+    ("bf16", 200, 33_000, 768, 10),    # query-resident
+    ("bf16", 100, 150_001, 768, 64),
+    ("bf16", 300, 33_000, 768, 10),    # GEMM-structured, half-size workgroups
+    ("bf16", 150, 40_003, 136, 33),
+])
+def test_banks_in_the_order_of_their_clusters(dtype, B, N, d, k):
+    """Near rows that follow one another: most row tiles of the k super tiles
+    are near, and the super tiles are one another's neighbours."""
+    q, bank = draw(B, N, d, dtype, -1, 1, 10)
+    g = torch.Generator(device=DEV).manual_seed(11)
+    n_c = max(4, N // 2_500)
+    centre = torch.randint(-2, 3, (n_c, d), generator=g, device=DEV).to(bank.dtype)
+    bank += centre[torch.arange(N, device=DEV) * n_c // N]
+    q += centre[torch.randint(0, n_c, (B,), generator=g, device=DEV)]
+    check(q, bank, k, f"clusters in order {dtype} B={B} N={N} d={d} k={k}")
+
+
 def test_rows_that_are_no_numbers_are_no_neighbours():
     """Fewer rows with a distance than neighbours: index -1, distance NaN."""
     import paper_2606_17949_amd as rb
