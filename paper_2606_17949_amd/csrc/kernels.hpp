@@ -52,6 +52,10 @@ constexpr long SEL_WANT_SUP = 16384;       // super tiles per request worth read
 // Bytes of maxima a call's workspace takes at most: a bank that would leave
 // more goes by in parts, each with its own scan and selection.
 constexpr size_t MAXIMA_LIMIT = (size_t)1 << 30;
+// Row tiles of one entry where the bank would otherwise go by in parts: the
+// selection then computes up to FOLD times the row tiles again, and the maxima
+// take 20 bytes for 68.
+constexpr int FOLD = 4;
 
 // Bytes of single values a scan keeps at most: then the selection takes 10 us
 // for 19 (it computes no row tile again), while 26 MB of them made a scan of
@@ -60,7 +64,8 @@ constexpr size_t KEEP_LIMIT = (size_t)8 << 20;
 
 // How one rb_knn_topk call is split.
 //  * the bank in n_seg parts of seg_rows rows (one, unless the maxima would
-//    pass the limit), each scanned and selected from by itself;
+//    pass the limit), each scanned and selected from by itself, the selection
+//    under the k-th distance of the parts before;
 //  * scan: the part in n_chunks row ranges, the requests in n_qt tiles, one
 //    workgroup per (chunk, tile), `grid` of them; per request it leaves n_sup
 //    super tiles of eps row tiles;
@@ -76,6 +81,7 @@ struct KnnPlan {
     int qw, rs;         // query-resident scan: query groups per wave, row halves; GEMM-structured
                         //   scan: 32-request tiles per wave (qw)
     int n_seg, n_qt, n_chunks, eps, grid;
+    bool folded;        // an entry is of FOLD row tiles (not by the LDS-resident scan)
     long seg_rows, n_sup, rows_per_chunk, sup_per_chunk;
     size_t lds_bytes;
     size_t off_sup, off_ent, off_lkey, off_lidx, bytes;

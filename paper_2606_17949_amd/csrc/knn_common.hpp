@@ -12,12 +12,14 @@ namespace rb {
 // <q, x> - |x|^2/2 of the tile's rows (the nearest row's distance is |q|^2 - 2
 // times that), and the maximum over every eps such entries (a super tile, of
 // eps * 16 consecutive rows). The rows go by in chunks, each with super tiles
-// of its own; entries and super tiles without a row hold NaN.
+// of its own; entries and super tiles without a row hold NaN. The entries of
+// FOLD consecutive row tiles go out as one where the plan says so.
 struct Maxima {
     float *sup;          // of request q: super tile s at s + q*sup_q
     float *ent;          // its entry e at s*ent_s + e + q*ent_q (unused when eps is 1 or when
     long sup_q;          //   every row's value is kept)
     long ent_s, ent_q;
+    bool folded;         // an entry is of FOLD row tiles
 };
 
 struct ScanArgs {
@@ -240,6 +242,21 @@ __device__ __forceinline__ void store16_nt(__amdgpu_buffer_rsrc_t r, uint32_t vo
                                            const f32x4 &v)
 {
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, v), r, (int)voffset, 0, 2);
+}
+
+// Lane l's four entries of a request (entries 4*(l % 4) .. +3 of its super
+// tile) to its place `at` (in floats, of the first entry, in resource r), as
+// they are or folded into one: one store either way. `in`: whether the lane
+// has anything to store.
+static_assert(FOLD == 4, "a lane's four entries are one folded entry");
+__device__ __forceinline__ void put_entries(__amdgpu_buffer_rsrc_t r, bool in, uint32_t at, int l,
+                                            const f32x4 &v, bool folded)
+{
+    if (folded)
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(max4(v)), r,
+                                              (int)(in ? (at + (l & 3)) * 4u : OFF_NONE), 0, 2);
+    else
+        store16_nt(r, in ? (at + (l & 3) * 4) * 4u : OFF_NONE, v);
 }
 
 // Global -> LDS load of 16 bytes per lane through the buffer resource: lane l's

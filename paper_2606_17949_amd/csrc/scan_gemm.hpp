@@ -241,8 +241,8 @@ __global__ __launch_bounds__(GM_WAVES * WAVE, 1) void gemm_scan_kernel(const Sca
             m = fmaxf(m, dpp<0x4e>(m));   // quad_perm [2,3,0,1]
             if (part == 0)
                 sst[q * GM_HOLD + rt % GM_HOLD] = m;
-            store16_nt(make_rsrc(ent + 16L * i * A.m.ent_q, 0x7fffffffu),
-                       q < nq ? (uint32_t)((lane >> 2) * A.m.ent_q + part * 4) * 4u : OFF_NONE, v);
+            put_entries(make_rsrc(ent + 16L * i * A.m.ent_q, 0x7fffffffu), q < nq,
+                        (uint32_t)((lane >> 2) * A.m.ent_q), lane, v, A.m.folded);
         }
         if (rt % GM_HOLD == GM_HOLD - 1)
             put_sup(rt + 1 - GM_HOLD, rt + 1);

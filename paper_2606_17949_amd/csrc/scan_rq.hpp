@@ -297,8 +297,8 @@ __global__ __launch_bounds__(RQ_WAVES * WAVE, 1) void rq_scan_kernel(const ScanA
             m = fmaxf(m, dpp<0x4e>(m));   // quad_perm [2,3,0,1]
             if (part == 0)
                 sst[q * HOLD + sl % HOLD] = m;
-            store16_nt(make_rsrc(ent + (long)(fq0 + 16 * i) * A.m.ent_q, 0x7fffffffu),
-                       q < A.B ? (uint32_t)(lq * A.m.ent_q + part * 4) * 4u : OFF_NONE, v);
+            put_entries(make_rsrc(ent + (long)(fq0 + 16 * i) * A.m.ent_q, 0x7fffffffu), q < A.B,
+                        (uint32_t)(lq * A.m.ent_q), l, v, A.m.folded);
         }
         settle = S - 1;
         if (sl % HOLD == HOLD - 1)

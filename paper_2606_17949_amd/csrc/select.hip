@@ -176,6 +176,13 @@ __global__ __launch_bounds__(NT, 1024 / NT) void select_kernel(const SelectArgs 
         return min(KEY_NONE - 1, f2key(t + ldexpf(qn + fabsf(t) + 1.f, -18)));
     };
     each_sup([&](uint32_t key, int) { least = min(least, key); });
+    // nothing past the k-th row of the earlier parts of the bank
+    uint32_t cap = KEY_NONE - 1;
+    if (A.carry_in) {
+        const uint32_t kth = A.list_key[(size_t)b * k + k - 1];
+        if (kth != KEY_NONE)
+            cap = widen(kth);
+    }
     const auto umin = [](uint32_t x, uint32_t y) { return x < y ? x : y; };
     const auto umax = [](uint32_t x, uint32_t y) { return x > y ? x : y; };
     // the largest of the least distances of at least k groups (waves, half
@@ -203,7 +210,7 @@ __global__ __launch_bounds__(NT, 1024 / NT) void select_kernel(const SelectArgs 
         S.group_min[wave * (WAVE / GL) + lane / GL] = of_group ? least : 0u;
     __syncthreads();
     // absent entries stay out
-    uint32_t bound = min(KEY_NONE - 1, wave_reduce(S.group_min[lane], umax));
+    uint32_t bound = min(cap, wave_reduce(S.group_min[lane], umax));
     each_sup([&](uint32_t key, int j) {
         if (key <= bound) {
             const int pos = atomicAdd(&S.n_cand, 1);
@@ -240,22 +247,24 @@ __global__ __launch_bounds__(NT, 1024 / NT) void select_kernel(const SelectArgs 
     __syncthreads();
 
     // ---- 2. their row tiles
-    if (n_best == k)
-        bound = widen((uint32_t)(S.best[k - 1] >> 32));
+    bound = n_best == k ? min(cap, widen((uint32_t)(S.best[k - 1] >> 32))) : cap;
+    const int fold = A.m.folded ? FOLD : 1;   // row tiles of an entry
     int n_items;   // what a round takes SEL_ROUND * 16 rows of
     if (A.acc) {
         n_items = n_best * A.eps * 16;
         if (tid < n_best)
             S.sup[tid] = (int)(uint32_t)S.best[tid];
     } else {
-        for (int i = tid; i < n_best * A.eps; i += NT) {
-            const int j = i / A.eps, e = i - j * A.eps;
+        const int per = A.eps / fold;
+        for (int i = tid; i < n_best * per; i += NT) {
+            const int j = i / per, e = i - j * per;
             const int s = (int)(uint32_t)S.best[j];
             const uint32_t key = A.eps == 1 ? (uint32_t)(S.best[j] >> 32) : key_of(ent(s, e));
             if (key <= bound) {
                 const int at = atomicAdd(&S.n_tiles, 1);
-                S.tiles[at] = s * A.eps + e;
-                S.cand[at] = pack(key, s * A.eps + e);
+                for (int f = 0; f < fold; ++f)
+                    S.tiles[at * fold + f] = s * A.eps + e * fold + f;
+                S.cand[at] = pack(key, s * A.eps + e * fold);
             }
         }
     }
@@ -264,14 +273,14 @@ __global__ __launch_bounds__(NT, 1024 / NT) void select_kernel(const SelectArgs 
         S.prev[tid] = pack(A.list_key[(size_t)b * k + tid], A.list_idx[(size_t)b * k + tid]);
     __syncthreads();
     if (!A.acc) {
-        n_items = S.n_tiles * 16;
-        // Many more than k row tiles: near rows follow one another in the
+        n_items = S.n_tiles * fold * 16;
+        // Many more than k entries: near rows follow one another in the
         // bank, the k-th super tile lies outside them and its distance is a
-        // loose bound. The k-th of the row tiles' own distances is one too (a
+        // loose bound. The k-th of the entries' own distances is one too (a
         // row each), and leaves about k of them in any order of the bank
         // (1,000 clusters one after the other: 256 x 1,000,000 x 768 481 / 390
         // us, 1,024 x 1,000,000 x 1,024 2,285 / 1,825).
-        if (n_items > (k + NW) * 16) {
+        if (n_items > (k * fold + NW) * 16) {
             rank_pairs<NT>(S.cand, S.n_tiles, k, S.rank, S.best);
             __syncthreads();
             bound = min(bound, widen((uint32_t)(S.best[k - 1] >> 32)));
@@ -281,10 +290,13 @@ __global__ __launch_bounds__(NT, 1024 / NT) void select_kernel(const SelectArgs 
                 S.n_tiles = 0;
             __syncthreads();
             for (int i = tid; i < n; i += NT)
-                if ((uint32_t)(S.cand[i] >> 32) <= bound)
-                    S.tiles[atomicAdd(&S.n_tiles, 1)] = (int)(uint32_t)S.cand[i];
+                if ((uint32_t)(S.cand[i] >> 32) <= bound) {
+                    const int at = atomicAdd(&S.n_tiles, 1);
+                    for (int f = 0; f < fold; ++f)
+                        S.tiles[at * fold + f] = (int)(uint32_t)S.cand[i] + f;
+                }
             __syncthreads();
-            n_items = S.n_tiles * 16;
+            n_items = S.n_tiles * fold * 16;
         }
     }
 

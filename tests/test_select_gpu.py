@@ -146,6 +146,64 @@ def test_bank_in_parts_matches_one_pass():
     assert torch.equal(out[0]["nbr_idx"], ref_idx) and torch.equal(out[0]["nbr_dist"], ref_dist)
 
 
+@pytest.mark.parametrize("B,N,parts", [
+    (256, 1_000_003, 1),        # folded entries, one part
+    (512, 1_700_013, 2),        # two parts of folded entries, the last one shorter
+])
+def test_bank_in_parts_query_resident(B, N, parts):
+    """The no-allocation call over banks whose maxima would not fit its array:
+    the results of one pass, and the integer neighbours of some requests."""
+    import paper_2606_17949_amd as rb
+    d, k, M, I = 384, 10, 2, 3
+    q, bank = draw(B, N, d, "bf16", -1, 1, 12)
+    # exact ties across the parts
+    bank[N - 40:] = bank[:40]
+    q[:20] = bank[:20]
+    norms = rb.rb_bank_norms(bank)
+    g = torch.Generator(device=DEV).manual_seed(13)
+    qual = torch.rand(N, M, generator=g, device=DEV)
+    length = 100.0 + qual
+    plen = torch.full((B,), 50, dtype=torch.int32, device=DEV)
+    out = []
+    for fn in (rb.rb_route_batch, rb.rb_route_batch_noalloc):
+        inst = rb.DeviceInstances(torch.tensor([0, 1, 1], dtype=torch.int32, device=DEV),
+                                  *[torch.ones(I, device=DEV) for _ in range(6)])
+        r = dict(assign=torch.empty(B, dtype=torch.int32, device=DEV),
+                 nbr_idx=torch.empty(B, k, dtype=torch.int32, device=DEV),
+                 nbr_dist=torch.empty(B, k, device=DEV), q_hat=torch.empty(B, M, device=DEV),
+                 l_hat=torch.empty(B, M, device=DEV))
+        print(f"query-resident, {parts} parts, B={B} N={N}", fn.__name__, flush=True)
+        fn(q, bank, norms, k, qual, length, plen, inst, (0.4, 0.3, 0.3), **r)
+        torch.cuda.synchronize()
+        out.append(r)
+    for f in out[0]:
+        assert torch.equal(out[0][f], out[1][f]), f
+    some = torch.arange(0, B, B // 32, device=DEV)
+    ref_idx, ref_dist = reference(q[some], bank, k)
+    assert torch.equal(out[0]["nbr_idx"][some], ref_idx)
+    assert torch.equal(out[0]["nbr_dist"][some], ref_dist)
+
+
+@pytest.mark.parametrize("B,N,k", [
+    (1_024, 4_300_013, 10),     # folded entries, one part
+    (4_096, 3_500_017, 20),     # two parts of them
+])
+def test_bank_in_parts_gemm(B, N, k):
+    """More than 1 GiB of maxima after the GEMM-structured scan: the integer
+    neighbours of some requests of every request tile."""
+    import paper_2606_17949_amd as rb
+    q, bank = draw(B, N, 8, "bf16", -3, 3, 14)
+    need = rb.rb_workspace_size(B, N, 8, rb.RB_BF16, k, 1)
+    print(f"GEMM-structured, parts, B={B} N={N}: workspace {need / 2**20:.0f} MiB", flush=True)
+    assert need < B * (N // 256) * 68
+    idx, dist = rb.rb_knn_topk(q, bank, rb.rb_bank_norms(bank), k)
+    torch.cuda.synchronize()
+    some = torch.arange(5, B, B // 32, device=DEV)
+    ref_idx, ref_dist = reference(q[some], bank, k)
+    assert torch.equal(dist[some], ref_dist)
+    assert torch.equal(idx[some], ref_idx)
+
+
 @pytest.mark.parametrize("B,N,d,k", [
     (65, 4_099, 384, 64),       # query-resident, one group per wave, last chunk of 3 rows
     (130, 70_001, 384, 10),     # two groups, row halves
