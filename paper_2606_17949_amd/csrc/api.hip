@@ -148,7 +148,11 @@ RouteExtra route_extra(size_t base, int B, int k, int M)
 }
 
 // Workspace bytes of a plan: its layout, and at least what its sizes ask for.
-size_t plan_bytes(const rb::KnnPlan &p) { return p.bytes > p.contract ? p.bytes : p.contract; }
+size_t plan_bytes(const rb::KnnPlan &p)
+{
+    const size_t ask = p.ordered > p.contract ? p.ordered : p.contract;
+    return p.bytes > ask ? p.bytes : ask;
+}
 
 const rb_options k_default_opts = {RB_ORDER_ARRIVAL, RB_KNN_UNIFORM, nullptr, nullptr, nullptr,
                                    0u};

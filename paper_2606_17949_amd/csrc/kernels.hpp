@@ -85,7 +85,7 @@ struct KnnPlan {
     long seg_rows, n_sup, rows_per_chunk, sup_per_chunk;
     size_t lds_bytes;
     size_t off_sup, off_ent, off_lkey, off_lidx, bytes;
-    size_t contract;    // bytes of workspace a call asks for at least
+    size_t contract, ordered;   // bytes of workspace a call asks for at least
 };
 
 // limit: bytes the maxima may take (they are cut to it by taking the bank in

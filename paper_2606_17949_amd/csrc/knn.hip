@@ -192,6 +192,17 @@ void plan_parts(KnnPlan *p, size_t limit)
     p->seg_rows = (all + p->n_seg - 1) / p->n_seg * rows;
 }
 
+// Super tiles up to SEL_WANT_SUP per request: row tiles of one of the
+// LDS-resident scan's.
+int res_eps(int N)
+{
+    const long all_tiles = ((long)N + 15) / 16;
+    int eps = 1;
+    while (eps < SEL_MAX_EPS && all_tiles > SEL_WANT_SUP * eps)
+        eps *= 2;
+    return eps;
+}
+
 // Chunks for n_qt request tiles: one workgroup per compute unit (the LDS use
 // allows no more). With `reserve`, that many units of each XCD stay free. The
 // tiles of a chunk share an XCD but for those of the last n_chunks % 8 chunks,
@@ -228,11 +239,7 @@ void plan_res(KnnPlan *p, int num_cu, int reserve, size_t limit)
     p->n_qt = (groups + ng - 1) / ng;
     p->ng = (groups + p->n_qt - 1) / p->n_qt;
     p->lds_bytes = (size_t)p->nks * p->ng * WAVE * 16 + RES_NORM_BYTES;
-    // super tiles: single row tiles up to SEL_WANT_SUP of them
-    const long all_tiles = ((long)p->N + 15) / 16;
-    p->eps = 1;
-    while (p->eps < SEL_MAX_EPS && all_tiles > SEL_WANT_SUP * p->eps)
-        p->eps *= 2;
+    p->eps = res_eps(p->N);
     plan_parts(p, limit);
     p->n_sup = p->seg_rows / (p->eps * 16);
     long chunks = plan_chunks(p, num_cu, reserve);
@@ -257,10 +264,12 @@ void plan_chunked(KnnPlan *p, int num_cu, int reserve, size_t limit)
 {
     const long rowb = (long)p->d * 2;
     p->eps = p->kind == 1 ? RQ_EPS : GM_EPS;
-    p->n_chunks = (int)plan_chunks(p, num_cu, reserve);
+    long chunks = plan_chunks(p, num_cu, reserve), most = chunks;
+    while ((p->N / most + 32) * rowb >= (1L << 31) - (1L << 20))   // (as below)
+        most *= 2;
+    p->n_chunks = (int)most;
     plan_parts(p, limit);
     const long rows = p->seg_rows < p->N ? p->seg_rows : p->N;
-    long chunks = p->n_chunks;
     if (chunks > (rows + 15) / 16)
         chunks = (rows + 15) / 16;
     long rpc = ((rows + chunks - 1) / chunks + 15) / 16 * 16;
@@ -273,6 +282,38 @@ void plan_chunked(KnnPlan *p, int num_cu, int reserve, size_t limit)
     p->sup_per_chunk = (rpc + p->eps * 16 - 1) / (p->eps * 16);
     p->n_sup = p->n_chunks * p->sup_per_chunk;
     p->grid = p->kind == 1 ? p->n_chunks : ((p->n_chunks + 7) / 8) * 8 * p->n_qt;
+}
+
+// What the layout of any batch of up to B requests takes at most, whatever scan
+// and how many parts it goes by. It is asked for, so that a workspace sized
+// for a program's largest batch holds the smaller ones too (folded entries and
+// parts make the layouts themselves go up and down with B: 1,006 requests over
+// 4,000,000 x 384 take 1,073 MB, 1,024 of them 321).
+size_t ordered_bytes(int B, int N, int d, int dtype, int k, int num_cu)
+{
+    const size_t b = B > 0 ? B : 1;
+    const long rowb = (long)d * (dtype == 1 ? 2 : 4);
+    // LDS-resident scan: bf16 batches of at most 64
+    const size_t b0 = dtype == 1 && b > 64 ? 64 : b;
+    const size_t eps = res_eps(N), n0 = ((size_t)N + 16 * eps - 1) / (16 * eps);
+    const size_t all = b0 * n0 * eps * 64, keep = all < KEEP_LIMIT ? all : KEEP_LIMIT;
+    size_t ent = eps > 1 ? b0 * n0 * eps * 4 : 0;
+    ent = ent > keep ? ent : keep;
+    const size_t res = b0 * n0 * 4 + ent;
+    // the others: every chunk may end in a partial super tile, and its rows
+    // are rounded up to a whole tile
+    size_t chunked = 0;
+    if (dtype == 1 && (b > 32 || (long)N >= (long)GM_ROWS * num_cu)) {
+        size_t chunks = (size_t)num_cu, split = 2 * (size_t)((long)N * rowb >> 30) + 2;
+        chunks = chunks > split ? chunks : split;
+        chunked = b * ((size_t)N / (RQ_EPS * 16) + chunks + chunks / 16 + 2) * 4 * (1 + RQ_EPS);
+    }
+    static_assert(RQ_EPS == GM_EPS, "one size of super tile");
+    size_t maxima = res > chunked ? res : chunked;
+    // (a part takes at least one super tile)
+    const size_t most = MAXIMA_LIMIT > b * 4 * (1 + RQ_EPS) ? MAXIMA_LIMIT : b * 4 * (1 + RQ_EPS);
+    maxima = maxima < most ? maxima : most;
+    return 2 * align256(b * k * 4) + maxima + 3 * 256;
 }
 
 }  // namespace
@@ -298,6 +339,8 @@ int plan_knn(int B, int N, int d, int dtype, int k, int num_cu, KnnPlan *p, int 
     p->k = k;
     p->nks = (d + 4 * vec - 1) / (4 * vec);
     p->contract = contract_bytes(B, N, d, dtype, k, num_cu, reserve);
+    // (a lower limit is one workspace's, not a size that is asked for)
+    p->ordered = limit == MAXIMA_LIMIT ? ordered_bytes(B, N, d, dtype, k, num_cu) : 0;
     if (p->contract == 0)
         return -1;
     // bf16 rows of 384, 512, 768 or 1,024 elements go to the query-resident
