@@ -247,12 +247,14 @@ __device__ __forceinline__ void store16_nt(__amdgpu_buffer_rsrc_t r, uint32_t vo
 // Lane l's four entries of a request (entries 4*(l % 4) .. +3 of its super
 // tile) to its place `at` (in floats, of the first entry, in resource r), as
 // they are or folded into one: one store either way. `in`: whether the lane
-// has anything to store.
+// has anything to store. (The choice at run time, in the flush, cost the scan
+// of 512 x 4,000,000 x 384 0.6 %.)
 static_assert(FOLD == 4, "a lane's four entries are one folded entry");
+template <bool FOLDED>
 __device__ __forceinline__ void put_entries(__amdgpu_buffer_rsrc_t r, bool in, uint32_t at, int l,
-                                            const f32x4 &v, bool folded)
+                                            const f32x4 &v)
 {
-    if (folded)
+    if (FOLDED)
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(max4(v)), r,
                                               (int)(in ? (at + (l & 3)) * 4u : OFF_NONE), 0, 2);
     else

@@ -8,7 +8,7 @@ namespace {
 template <int TPQ>
 hipError_t launch_gemm(const KnnPlan &p, const ScanArgs &a, hipStream_t s)
 {
-    auto kern = gemm_scan_kernel<TPQ>;
+    auto kern = a.m.folded ? gemm_scan_kernel<TPQ, true> : gemm_scan_kernel<TPQ, false>;
     hipError_t e = hipFuncSetAttribute((const void *)kern,
                                        hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)p.lds_bytes);

@@ -41,7 +41,7 @@ __device__ __forceinline__ f32x16 mfma32(const i32x4 &a, const i32x4 &b, const f
 // maxima of its accumulators (a lane's 16 rows of a 32 x 32 tile are one
 // entry, a macro tile's 16 entries one super tile) into LDS; they go out after
 // the next barrier, 64 bytes per request.
-template <int TPQ>
+template <int TPQ, bool FOLDED>
 __global__ __launch_bounds__(GM_WAVES * WAVE, 1) void gemm_scan_kernel(const ScanArgs A)
 {
     constexpr int QRY = 64 * TPQ;                 // requests of a tile
@@ -241,8 +241,8 @@ __global__ __launch_bounds__(GM_WAVES * WAVE, 1) void gemm_scan_kernel(const Sca
             m = fmaxf(m, dpp<0x4e>(m));   // quad_perm [2,3,0,1]
             if (part == 0)
                 sst[q * GM_HOLD + rt % GM_HOLD] = m;
-            put_entries(make_rsrc(ent + 16L * i * A.m.ent_q, 0x7fffffffu), q < nq,
-                        (uint32_t)((lane >> 2) * A.m.ent_q), lane, v, A.m.folded);
+            put_entries<FOLDED>(make_rsrc(ent + 16L * i * A.m.ent_q, 0x7fffffffu), q < nq,
+                                (uint32_t)((lane >> 2) * A.m.ent_q), lane, v);
         }
         if (rt % GM_HOLD == GM_HOLD - 1)
             put_sup(rt + 1 - GM_HOLD, rt + 1);

@@ -58,7 +58,7 @@ __device__ __forceinline__ uint32_t rq_chunk(int ri, int rg, int c)
 // over 1,000,000 x 768 took 305 us for 286), with the super tile's maximum. No
 // bound, list or candidate test holds a wave up between two blocks (one at a
 // time, the candidates of the bounded scan took about a tenth of it).
-template <int NKS, int QW, int RS, int SPB, int S>
+template <int NKS, int QW, int RS, int SPB, int S, bool FOLDED>
 __global__ __launch_bounds__(RQ_WAVES * WAVE, 1) void rq_scan_kernel(const ScanArgs A)
 {
     constexpr int TT = RQ_ROWS / 16;
@@ -297,8 +297,8 @@ __global__ __launch_bounds__(RQ_WAVES * WAVE, 1) void rq_scan_kernel(const ScanA
             m = fmaxf(m, dpp<0x4e>(m));   // quad_perm [2,3,0,1]
             if (part == 0)
                 sst[q * HOLD + sl % HOLD] = m;
-            put_entries(make_rsrc(ent + (long)(fq0 + 16 * i) * A.m.ent_q, 0x7fffffffu), q < A.B,
-                        (uint32_t)(lq * A.m.ent_q), l, v, A.m.folded);
+            put_entries<FOLDED>(make_rsrc(ent + (long)(fq0 + 16 * i) * A.m.ent_q, 0x7fffffffu),
+                                q < A.B, (uint32_t)(lq * A.m.ent_q), l, v);
         }
         settle = S - 1;
         if (sl % HOLD == HOLD - 1)
@@ -381,7 +381,8 @@ __global__ __launch_bounds__(RQ_WAVES * WAVE, 1) void rq_scan_kernel(const ScanA
 template <int NKS, int QW, int RS, int SPB, int S>
 hipError_t launch_rq_scan(const ScanArgs &a, size_t lds, int grid, hipStream_t s)
 {
-    auto kern = rq_scan_kernel<NKS, QW, RS, SPB, S>;
+    auto kern = a.m.folded ? rq_scan_kernel<NKS, QW, RS, SPB, S, true>
+                           : rq_scan_kernel<NKS, QW, RS, SPB, S, false>;
     hipError_t e = hipFuncSetAttribute((const void *)kern,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess)
