@@ -203,6 +203,18 @@ int res_eps(int N)
     return eps;
 }
 
+// Bytes of single values the LDS-resident scan keeps at most. Else the
+// selection computes k row tiles again for every request by itself, a
+// sixteenth of each MFMA's columns used: fp32 batches keep them, as far as the
+// workspace may, where that is more work than a sixteenth of the scan's
+// (2,022 x 2,312 x 512, 64 neighbours: 547 us computed again, 127 kept; 1,000 x
+// 48,000 x 384, 10 neighbours: 365 and 341). bf16 scans, sixteen times as fast,
+// lose more to the stores.
+size_t keep_limit(int dtype, int N, int d, int k)
+{
+    return dtype == 0 && (long)N <= 16L * k * d ? MAXIMA_LIMIT : KEEP_LIMIT;
+}
+
 // Chunks for n_qt request tiles: one workgroup per compute unit (the LDS use
 // allows no more). With `reserve`, that many units of each XCD stay free. The
 // tiles of a chunk share an XCD but for those of the last n_chunks % 8 chunks,
@@ -296,7 +308,8 @@ size_t ordered_bytes(int B, int N, int d, int dtype, int k, int num_cu)
     // LDS-resident scan: bf16 batches of at most 64
     const size_t b0 = dtype == 1 && b > 64 ? 64 : b;
     const size_t eps = res_eps(N), n0 = ((size_t)N + 16 * eps - 1) / (16 * eps);
-    const size_t all = b0 * n0 * eps * 64, keep = all < KEEP_LIMIT ? all : KEEP_LIMIT;
+    const size_t all = b0 * n0 * eps * 64, kl = keep_limit(dtype, N, d, k);
+    const size_t keep = all < kl ? all : kl;
     size_t ent = eps > 1 ? b0 * n0 * eps * 4 : 0;
     ent = ent > keep ? ent : keep;
     const size_t res = b0 * n0 * 4 + ent;
@@ -383,7 +396,7 @@ int plan_knn(int B, int N, int d, int dtype, int k, int num_cu, KnnPlan *p, int 
     off += align256(b * p->n_sup * 4);
     p->off_ent = off;
     const size_t keep = align256(b * p->n_sup * p->eps * 16 * 4);
-    p->keep_acc = p->kind == 0 && p->n_seg == 1 && keep <= KEEP_LIMIT && off + keep <= limit;
+    p->keep_acc = p->kind == 0 && p->n_seg == 1 && keep <= keep_limit(dtype, N, d, k) && off + keep <= limit;
     off += p->keep_acc ? keep : p->eps > 1 ? align256(b * p->n_sup * entries_of(*p) * 4) : 0;
     p->bytes = off;
     return 0;
