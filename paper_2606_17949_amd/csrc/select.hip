@@ -119,10 +119,8 @@ __global__ __launch_bounds__(NT, 1024 / NT) void select_kernel(const SelectArgs 
     // rows in random order the same).
     constexpr int SV = SEL_WANT_SUP / NT;
     const int deal = A.n_sup >= 16 * 16 * NW ? 4 : 2;   // log2 of a turn
-    auto sup_at = [&](int u) -> long {
-        const int i = u * WAVE + lane;
-        return (((long)(i >> deal) * NW + wave) << deal) + (i & ((1 << deal) - 1));
-    };
+    const int first = (((lane >> deal) * NW + wave) << deal) + (lane & ((1 << deal) - 1));
+    auto sup_at = [&](int u) -> long { return first + (long)u * NT; };
     float sv[SV];
 #pragma unroll
     for (int u = 0; u < SV; ++u) {
