@@ -38,10 +38,9 @@ constexpr int RES_WAVES = 8;
 constexpr int RES_RING = 8;
 constexpr int RES_MAX_NG = 8;
 constexpr int RES_HOLD = 16;   // super tiles whose maxima a wave holds
-// The selection: one workgroup of SEL_THREADS threads per request (half of
-// them for more than SEL_WIDE_B requests); up to
-// SEL_CAP super tiles or rows held in LDS at once; SEL_ROUND row tiles
-// recomputed per round.
+// The selection: one workgroup of SEL_THREADS threads per request (a quarter
+// of them for more than SEL_WIDE_B requests); up to SEL_CAP super tiles or rows
+// held in LDS at once; SEL_ROUND row tiles recomputed per round.
 constexpr int SEL_THREADS = 1024;
 constexpr int SEL_WIDE_B = 256;
 constexpr int SEL_CAP = 2048;

@@ -117,7 +117,7 @@ __global__ __launch_bounds__(NT, 1024 / NT) void select_kernel(const SelectArgs 
     // bank in the order of its clusters, contiguous shares / in turn: 64 x
     // 100,000 x 768 178 / 57 us, 256 x 1,000,000 x 768 in 32 clusters 479 / 385;
     // rows in random order the same).
-    constexpr int SV = SEL_WANT_SUP / NT;
+    constexpr int SV = SEL_WANT_SUP / NT < 32 ? SEL_WANT_SUP / NT : 32;
     const int deal = A.n_sup >= 16 * 16 * NW ? 4 : 2;   // log2 of a turn
     const int first = (((lane >> deal) * NW + wave) << deal) + (lane & ((1 << deal) - 1));
     auto sup_at = [&](int u) -> long { return first + (long)u * NT; };
@@ -188,21 +188,24 @@ __global__ __launch_bounds__(NT, 1024 / NT) void select_kernel(const SelectArgs 
     // groups of GL lanes, 64 of them; each step up halves their number, as far
     // as k allows (a group of its pair: 0, which no maximum takes)
     constexpr int GL = NT / WAVE;
-    static_assert(GL == 16 || GL == 8, "rows or half rows of lanes");
+    static_assert(GL == 16 || GL == 4, "rows or quads of lanes");
     least = umin(least, dpp<0xb1>(least));
     least = umin(least, dpp<0x4e>(least));
-    least = umin(least, dpp<0x141>(least));   // half rows of 8 lanes
     bool of_group = true;
-    if (GL == 16 || k <= 32) {
-        least = umin(least, dpp<0x140>(least));   // rows
-        of_group = GL == 16 || !(lane & 8);
+    if (GL == 16 || k <= NT / 8) {
+        least = umin(least, dpp<0x141>(least));   // half rows of 8 lanes
+        of_group = !(lane & 4);
     }
-    if (k <= (GL == 16 ? 16 : 8)) {
+    if (GL == 16 || k <= NT / 16) {
+        least = umin(least, dpp<0x140>(least));   // rows
+        of_group = !(lane & 15 & ~(GL - 1));
+    }
+    if (k <= NT / 64) {
         least = rows_reduce(least, umin);   // waves
         of_group = lane < GL;
-    } else if (k <= (GL == 16 ? 32 : 16)) {
+    } else if (k <= NT / 32) {
         least = umin(least, dpp<0x142, 0xa>(least));   // row_bcast:15: half waves
-        of_group = (lane & 16) && (GL == 16 || !(lane & 8));
+        of_group = (lane & 16) && !(lane & 15 & ~(GL - 1));
     }
     if (lane % GL == 0)
         S.group_min[wave * (WAVE / GL) + lane / GL] = of_group ? least : 0u;
@@ -485,23 +488,22 @@ __global__ __launch_bounds__(WAVE) void from_list_kernel(const SelectArgs A)
 hipError_t launch_select(int dtype, const SelectArgs &a, hipStream_t s)
 {
     // one workgroup of 16 waves per compute unit while there are enough units;
-    // more requests go in workgroups of 8, two to a unit, so that one's chain of
-    // accesses runs beside the other's reading (1,024 requests over 1,000,000 x
-    // 1,024: 1,861 us a lookup for 1,871; 20 neighbours of 100 requests instead
-    // lose 4 us of 145 that way)
-#define RB_SELECT(DT, NT)                                                                        \
-    hipLaunchKernelGGL((select_kernel<DT, NT>), dim3(a.B), dim3(NT), 0, s, a)
-    if (a.B <= SEL_WIDE_B) {
-        if (dtype == 1)
-            RB_SELECT(1, SEL_THREADS);
-        else
-            RB_SELECT(0, SEL_THREADS);
-    } else {
-        if (dtype == 1)
-            RB_SELECT(1, SEL_THREADS / 2);
-        else
-            RB_SELECT(0, SEL_THREADS / 2);
-    }
+    // more requests go in workgroups of 4, four to a unit, so that one's chain of
+    // accesses and barriers runs beside the others' (whole lookups, in
+    // workgroups of 8 and 4: 2,000 requests over 3,381 x 96 64 / 43 us, 600 over
+    // 3,381 x 96 33 / 25, 1,024 over 30,000 x 768, 32 neighbours, 176 / 165; 1,024
+    // over 1,000,000 x 1,024 the same)
+#define RB_SELECT(NT)                                                                            \
+    do {                                                                                         \
+        if (dtype == 1)                                                                          \
+            hipLaunchKernelGGL((select_kernel<1, NT>), dim3(a.B), dim3(NT), 0, s, a);            \
+        else                                                                                     \
+            hipLaunchKernelGGL((select_kernel<0, NT>), dim3(a.B), dim3(NT), 0, s, a);            \
+    } while (0)
+    if (a.B <= SEL_WIDE_B)
+        RB_SELECT(SEL_THREADS);
+    else
+        RB_SELECT(SEL_THREADS / 4);
 #undef RB_SELECT
     return hipGetLastError();
 }
