@@ -38,9 +38,10 @@ constexpr int RES_WAVES = 8;
 constexpr int RES_RING = 8;
 constexpr int RES_MAX_NG = 8;
 constexpr int RES_HOLD = 16;   // super tiles whose maxima a wave holds
-// The selection: one workgroup of SEL_THREADS threads per request (a quarter
-// of them for more than SEL_WIDE_B requests); up to SEL_CAP super tiles or rows
-// held in LDS at once; SEL_ROUND row tiles recomputed per round.
+// The selection: one workgroup of SEL_THREADS threads per request (half of
+// them for more than SEL_WIDE_B requests, a quarter for more than twice as
+// many); up to SEL_CAP super tiles or rows held in LDS at once; SEL_ROUND row
+// tiles recomputed per round.
 constexpr int SEL_THREADS = 1024;
 constexpr int SEL_WIDE_B = 256;
 constexpr int SEL_CAP = 2048;
@@ -48,6 +49,9 @@ constexpr int SEL_ROUND = 64;
 constexpr int SEL_MAX_EPS = 16;            // row tiles per super tile, at most
 constexpr int SEL_MAX_ROW_BYTES = 8192;    // of one embedding (RB_MAX_D fp32)
 constexpr long SEL_WANT_SUP = 16384;       // super tiles per request worth reading one by one
+// bf16 batches of more than SEL_WIDE_B requests over at most this many rows
+// (and 1,024 k) go to the LDS-resident scan, which keeps their values.
+constexpr int KEEP_ROWS = 8192;
 // Bytes of maxima a call's workspace takes at most: a bank that would leave
 // more goes by in parts, each with its own scan and selection.
 constexpr size_t MAXIMA_LIMIT = (size_t)1 << 30;

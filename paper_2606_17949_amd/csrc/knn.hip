@@ -209,10 +209,26 @@ int res_eps(int N)
 // workspace may, where that is more work than a sixteenth of the scan's
 // (2,022 x 2,312 x 512, 64 neighbours: 547 us computed again, 127 kept; 1,000 x
 // 48,000 x 384, 10 neighbours: 365 and 341). bf16 scans, sixteen times as fast,
-// lose more to the stores.
+// lose more to the stores over all but small banks.
 size_t keep_limit(int dtype, int N, int d, int k)
 {
-    return dtype == 0 && (long)N <= 16L * k * d ? MAXIMA_LIMIT : KEEP_LIMIT;
+    const bool keep = dtype == 0 ? (long)N <= 16L * k * d : N <= KEEP_ROWS;
+    return keep ? MAXIMA_LIMIT : KEEP_LIMIT;
+}
+
+// bf16 batches of more than SEL_WIDE_B requests over a small bank, whose
+// selections take longer than the scan if they compute row tiles again.
+bool keeps_small_bank(int B, int N, int k)
+{
+    return B > SEL_WIDE_B && N <= KEEP_ROWS && (long)N <= 1024L * k;
+}
+
+// Bytes of the LDS-resident scan's layout over a bank of single row tiles, every
+// row's value kept.
+size_t res_bytes(int B, int N, int k)
+{
+    const size_t b = B, tiles = ((size_t)N + 15) / 16;
+    return 2 * align256(b * k * 4) + align256(b * tiles * 4) + align256(b * tiles * 64);
 }
 
 // Chunks for n_qt request tiles: one workgroup per compute unit (the LDS use
@@ -305,8 +321,8 @@ size_t ordered_bytes(int B, int N, int d, int dtype, int k, int num_cu)
 {
     const size_t b = B > 0 ? B : 1;
     const long rowb = (long)d * (dtype == 1 ? 2 : 4);
-    // LDS-resident scan: bf16 batches of at most 64
-    const size_t b0 = dtype == 1 && b > 64 ? 64 : b;
+    // LDS-resident scan: bf16 batches of at most 64, or over a small bank
+    const size_t b0 = dtype == 1 && b > 64 && !keeps_small_bank(B, N, k) ? 64 : b;
     const size_t eps = res_eps(N), n0 = ((size_t)N + 16 * eps - 1) / (16 * eps);
     const size_t all = b0 * n0 * eps * 64, kl = keep_limit(dtype, N, d, k);
     const size_t keep = all < kl ? all : kl;
@@ -367,7 +383,12 @@ int plan_knn(int B, int N, int d, int dtype, int k, int num_cu, KnnPlan *p, int 
     // the LDS-resident scan reads the bank for two), over at least a macro
     // tile of rows per compute unit (64 requests, 1,536 elements: 490 us for
     // 577 over 700,000 rows, 61 for 64 over 48,001, but 57 for 40 over 32,001).
-    // Everything else, all fp32 batches among it, goes to the LDS-resident scan.
+    // Everything else, all fp32 batches among it, goes to the LDS-resident scan,
+    // and so does a large bf16 batch over a small bank, if the workspace can
+    // keep its values (10 neighbours: 2,000 x 3,000 x 768 101 us by the
+    // GEMM-structured scan, 54 so, 600 x 8,000 x 1,024 69 and 42; but 1,024 x
+    // 16,000 x 2,048 168 and 245, and one neighbour, 1,024 x 8,000 x 768, 37 and
+    // 41).
     const bool rq_rows = B > 64 || (long)N >= (long)RQ_SMALL_B_MIN_ROWS * num_cu;
     if (dtype == 1 && d % (4 * vec) == 0 && rq_rows && rq_shape(p->nks, B, &p->qw, &p->rs)) {
         p->kind = 1;
@@ -375,8 +396,9 @@ int plan_knn(int B, int N, int d, int dtype, int k, int num_cu, KnnPlan *p, int 
         p->lds_bytes =
             rq_layout(p->qw, p->rs, p->nks / rq_spb(p->nks), RQ_SLOTS).bytes;
         plan_chunked(p, num_cu, reserve, limit);
-    } else if (dtype == 1 && (B > 64 || ((B + 15) / 16 > res_groups(p->nks) &&
-                                         (long)N >= (long)GM_ROWS * num_cu))) {
+    } else if (dtype == 1 && !(keeps_small_bank(B, N, k) && res_bytes(B, N, k) <= limit) &&
+               (B > 64 || ((B + 15) / 16 > res_groups(p->nks) &&
+                           (long)N >= (long)GM_ROWS * num_cu))) {
         p->kind = 2;
         p->qw = B > 128 ? 4 : 2;
         p->n_qt = (B + 64 * p->qw - 1) / (64 * p->qw);

@@ -221,7 +221,12 @@ def test_bank_in_parts_gemm(B, N, k):
     (70, 777, 8, 10),           # one 16-byte piece of a row: a stage of padding
     (128, 5_000, 200, 64),      # tiles of 128 requests, ragged rows
     (90, 3_000, 1_000, 10),
-    (1_025, 2_050, 136, 10),    # five request tiles
+    (1_025, 2_050, 136, 10),    # nine request tiles, every value kept
+    (1_025, 9_000, 136, 10),    # five request tiles
+    (257, 8_192, 640, 8),       # values kept at the fewest requests, most rows
+    (257, 8_193, 640, 8),       # ... and one row more
+    (700, 1_025, 768, 1),       # one neighbour, one row past what it keeps
+    (300, 2_000, 768, 64),
     (64, 70_001, 1_536, 10),    # a small batch too long for LDS as one tile
     (33, 65_536, 2_048, 10),    # ... at the fewest requests and rows
     (33, 65_535, 2_048, 10),    # ... and one row below
