@@ -188,13 +188,13 @@ __global__ __launch_bounds__(NT, 1024 / NT) void select_kernel(const SelectArgs 
     // groups of GL lanes, 64 of them; each step up halves their number, as far
     // as k allows (a group of its pair: 0, which no maximum takes)
     constexpr int GL = NT / WAVE;
-    static_assert(GL == 16 || GL == 4, "rows or quads of lanes");
+    static_assert(GL == 16 || GL == 8 || GL == 4, "rows, half rows or quads of lanes");
     least = umin(least, dpp<0xb1>(least));
     least = umin(least, dpp<0x4e>(least));
     bool of_group = true;
-    if (GL == 16 || k <= NT / 8) {
+    if (GL >= 8 || k <= NT / 8) {
         least = umin(least, dpp<0x141>(least));   // half rows of 8 lanes
-        of_group = !(lane & 4);
+        of_group = GL >= 8 || !(lane & 4);
     }
     if (GL == 16 || k <= NT / 16) {
         least = umin(least, dpp<0x140>(least));   // rows
@@ -488,11 +488,11 @@ __global__ __launch_bounds__(WAVE) void from_list_kernel(const SelectArgs A)
 hipError_t launch_select(int dtype, const SelectArgs &a, hipStream_t s)
 {
     // one workgroup of 16 waves per compute unit while there are enough units;
-    // more requests go in workgroups of 4, four to a unit, so that one's chain of
-    // accesses and barriers runs beside the others' (whole lookups, in
-    // workgroups of 8 and 4: 2,000 requests over 3,381 x 96 64 / 43 us, 600 over
-    // 3,381 x 96 33 / 25, 1,024 over 30,000 x 768, 32 neighbours, 176 / 165; 1,024
-    // over 1,000,000 x 1,024 the same)
+    // more requests go in workgroups of 8, two to a unit, and past those in
+    // workgroups of 4, so that one's chain of accesses and barriers runs beside
+    // the others' (whole lookups, in workgroups of 8 and 4: 2,000 requests over
+    // 3,381 x 96 64 / 43 us, 600 over 3,381 x 96 33 / 25, 1,024 over 30,000 x 768,
+    // 32 neighbours, 176 / 165; but 300 over 16,000 x 2,048 100 / 103)
 #define RB_SELECT(NT)                                                                            \
     do {                                                                                         \
         if (dtype == 1)                                                                          \
@@ -502,6 +502,8 @@ hipError_t launch_select(int dtype, const SelectArgs &a, hipStream_t s)
     } while (0)
     if (a.B <= SEL_WIDE_B)
         RB_SELECT(SEL_THREADS);
+    else if (a.B <= 2 * SEL_WIDE_B)
+        RB_SELECT(SEL_THREADS / 2);
     else
         RB_SELECT(SEL_THREADS / 4);
 #undef RB_SELECT
