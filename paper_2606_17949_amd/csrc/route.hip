@@ -543,8 +543,7 @@ __global__ __launch_bounds__((CW + WIDE_PRODUCERS) * WAVE) void assign_wide_kern
         // ---- producers
         const int w = wave - CW;
         if (w >= GR) {
-            stream_barrier();
-            for (int t = 0; t < B; ++t)
+            for (int t = -2; t < B; ++t)
                 stream_barrier();
             return;
         }
@@ -621,8 +620,10 @@ __global__ __launch_bounds__((CW + WIDE_PRODUCERS) * WAVE) void assign_wide_kern
                 }
             }
         };
-        // groups 0 and 1 before the first step
-        for (int g = 0; g < 2; ++g) {
+        // groups 0 and 1 before the first step (sixteen slots both, always,
+        // and each group after them: as a condition it costs them registers,
+        // and 1,000 instances 1,160 ns a step for 935)
+        for (int g = 0; g < (SL > 1 ? 2 : min(2, n_gr)); ++g) {
             const Req q = request(g);
             labels(q, qv, lv, 0, NS);
             wide_for<0, GR>([&](auto K) { piece(K, q, g); });
@@ -630,6 +631,7 @@ __global__ __launch_bounds__((CW + WIDE_PRODUCERS) * WAVE) void assign_wide_kern
         Req q = request(2), qn = request(3);
         labels(q, qv, lv, 0, NS);
         stream_barrier();
+        stream_barrier();   // (the deciding waves' first latencies)
         for (int g = 0; g < n_gr; ++g) {
             // (with every piece a share of the loads of the next group's row; all
             // with the first where sixteen slots leave no registers to spread them)
@@ -638,9 +640,11 @@ __global__ __launch_bounds__((CW + WIDE_PRODUCERS) * WAVE) void assign_wide_kern
             wide_for<0, GR>([&](auto K) {
                 constexpr int k = decltype(K)::value;
                 if (g * GR + k < B) {
-                    labels(qn, qx, lx, SL == 1 ? k * (NS / GR) : k == 0 ? 0 : NS,
-                           SL == 1 ? (k + 1) * (NS / GR) : NS);
-                    piece(K, q, g + 2);
+                    if (SL > 1 || g + 2 < n_gr) {
+                        labels(qn, qx, lx, SL == 1 ? k * (NS / GR) : k == 0 ? 0 : NS,
+                               SL == 1 ? (k + 1) * (NS / GR) : NS);
+                        piece(K, q, g + 2);
+                    }
                     stream_barrier();
                 }
             });
@@ -704,19 +708,16 @@ __global__ __launch_bounds__((CW + WIDE_PRODUCERS) * WAVE) void assign_wide_kern
 #pragma unroll
     for (int u = 0; u < SL; ++u)
         T[u] = latency(p[u], a[u], rP[u], rD[u], l, lv[u]);
-    // the first step's largest latency: every wave over the whole table
-    float tmax;
-    {
-        int tt = TINY;
-        for (int i = lane; i < Sh::IP; i += WAVE) {
-            const int m = i < I ? in.model[i] : -1;
-            const Pair v = S.pair[0][0][i];
-            if ((unsigned)m < (unsigned)M && v.base == v.base)
-                tt = imax(tt, __float_as_int(latency(in.p[i], in.a[i], 1.f / in.P[i],
-                                                     1.f / in.D[i], l, v.lv)));
-        }
-        tmax = __int_as_float(wave_imax(tt));
-    }
+    // the first step's largest latency, through the packets of step -1
+    int tt = TINY;
+#pragma unroll
+    for (int u = 0; u < SL; ++u)
+        tt = imax(tt, bs[u] == bs[u] ? __float_as_int(T[u]) : 0);
+    tt = wave_imax(tt);
+    if (lane == 0)
+        S.pick[1][wave].t0 = tt;
+    stream_barrier();
+    float tmax = __int_as_float(imax_waves(S.pick[1][lane & (CW - 1)].t0));
     for (int t = 0; t < B; ++t) {
         float bs2[SL], lv2[SL], l2;   // the step after the next, in flight
         fetch(t + 2, bs2, lv2, l2);
