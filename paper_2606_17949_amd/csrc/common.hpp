@@ -15,6 +15,23 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
+template <int I> struct Int {
+    static constexpr int value = I;
+};
+template <bool V> struct Bool {
+    static constexpr bool value = V;
+};
+
+// f(Int<I>) for I = B..E-1, unrolled at compile time.
+template <int B, int E, typename F>
+__device__ __forceinline__ void static_for(F &&f)
+{
+    if constexpr (B < E) {
+        f(Int<B>{});
+        static_for<B + 1, E>(f);
+    }
+}
+
 // Order-preserving map from fp32 to uint32: a < b (as floats, non-NaN) iff
 // key(a) < key(b) as unsigned integers. Used so that distances can be compared,
 // selected bit by bit and combined with atomicMin as plain integers.
@@ -31,18 +48,8 @@ __device__ __forceinline__ float key2f(uint32_t k)
 }
 
 constexpr uint32_t KEY_NONE = 0xffffffffu;   // larger than the key of any finite distance
-constexpr int32_t IDX_NONE = 0x7fffffff;
 
 __device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
-
-__device__ __forceinline__ int popc(uint64_t m) { return __builtin_popcountll(m); }
-
-// Number of set bits of m below this lane.
-__device__ __forceinline__ int mbcnt(uint64_t m)
-{
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                     __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (WAVE - 1); }
 
@@ -128,36 +135,14 @@ __device__ __forceinline__ void reduce_max_pair(uint32_t &hi, uint32_t &lo)
     }
 }
 
-template <typename F>
-__device__ __forceinline__ float wave_reduce_f(float v, F op)
-{
-    return wave_reduce(v, op);
-}
-
-template <typename F>
-__device__ __forceinline__ uint32_t wave_reduce_u32(uint32_t v, F op)
-{
-    return wave_reduce(v, op);
-}
-
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
-{
-    return wave_reduce_u32(v, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
-}
-
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v)
-{
-    return wave_reduce_u32(v, [](uint32_t a, uint32_t b) { return a < b ? a : b; });
-}
-
 __device__ __forceinline__ float wave_max(float v)
 {
-    return wave_reduce_f(v, [](float a, float b) { return fmaxf(a, b); });
+    return wave_reduce(v, [](float a, float b) { return fmaxf(a, b); });
 }
 
 __device__ __forceinline__ float wave_sum(float v)
 {
-    return wave_reduce_f(v, [](float a, float b) { return a + b; });
+    return wave_reduce(v, [](float a, float b) { return a + b; });
 }
 
 // Workgroup barrier once this wave's LDS accesses are done, with no release

@@ -280,23 +280,6 @@ __device__ __forceinline__ void wait_vmcnt()
     __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
-template <int I> struct Int {
-    static constexpr int value = I;
-};
-template <bool V> struct Bool {
-    static constexpr bool value = V;
-};
-
-// f(Int<I>) for I = B..E-1, unrolled at compile time.
-template <int B, int E, typename F>
-__device__ __forceinline__ void static_for(F &&f)
-{
-    if constexpr (B < E) {
-        f(Int<B>{});
-        static_for<B + 1, E>(f);
-    }
-}
-
 __device__ __forceinline__ uint64_t pack(uint32_t key, int32_t idx)
 {
     return ((uint64_t)key << 32) | (uint32_t)idx;

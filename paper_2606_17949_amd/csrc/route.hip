@@ -487,19 +487,6 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void assign_kernel(
 // once and an exact-remainder step per ratio 579.)
 constexpr int WIDE_PRODUCERS = 8;
 
-template <int I> struct WideInt {
-    static constexpr int value = I;
-};
-// f(WideInt<K>) for K = B..E-1, unrolled at compile time.
-template <int B, int E, typename F>
-__device__ __forceinline__ void wide_for(F &&f)
-{
-    if constexpr (B < E) {
-        f(WideInt<B>{});
-        wide_for<B + 1, E>(f);
-    }
-}
-
 struct WidePick {
     int key, inst;      // key of the wave's pick (LEAST_KEY: none), its instance
     int t0;             // the next step's largest latency bits with the state as it stands
@@ -626,7 +613,7 @@ __global__ __launch_bounds__((CW + WIDE_PRODUCERS) * WAVE) void assign_wide_kern
         for (int g = 0; g < (SL > 1 ? 2 : min(2, n_gr)); ++g) {
             const Req q = request(g);
             labels(q, qv, lv, 0, NS);
-            wide_for<0, GR>([&](auto K) { piece(K, q, g); });
+            static_for<0, GR>([&](auto K) { piece(K, q, g); });
         }
         Req q = request(2), qn = request(3);
         labels(q, qv, lv, 0, NS);
@@ -637,7 +624,7 @@ __global__ __launch_bounds__((CW + WIDE_PRODUCERS) * WAVE) void assign_wide_kern
             // with the first where sixteen slots leave no registers to spread them)
             float qx[NS], lx[NS];
             const Req qnn = request(g + 4);
-            wide_for<0, GR>([&](auto K) {
+            static_for<0, GR>([&](auto K) {
                 constexpr int k = decltype(K)::value;
                 if (g * GR + k < B) {
                     if (SL > 1 || g + 2 < n_gr) {
