@@ -114,7 +114,11 @@ const char *rb_status_string(rb_status s);
  * rb_route_batch_ex need for these sizes on the current device (with or without
  * RB_FLAG_OVERLAP), written to *bytes (a host pointer). The value
  * depends on the device's compute-unit count; query it on the device that will
- * run the call. Errors: RB_ERR_NULL (bytes), RB_ERR_DIMS / RB_ERR_DTYPE as for
+ * run the call. It holds the neighbour lists, the scan's maxima (at most 1 GiB
+ * while one super tile of 256 rows fits that: 68 bytes per request and 256 rows,
+ * or every value of a small scan; what passes it goes by with one entry for 64
+ * rows, then in parts), and at least the floor that decides what
+ * rb_route_batch_noalloc takes. Errors: RB_ERR_NULL (bytes), RB_ERR_DIMS / RB_ERR_DTYPE as for
  * rb_knn_topk, RB_ERR_HIP if the device cannot be queried. */
 rb_status rb_workspace_size(int B, int N, int d, rb_dtype dtype, int k, int M, size_t *bytes);
 
@@ -172,7 +176,10 @@ rb_status rb_predict(const int32_t *nbr_idx, const float *nbr_dist, int B, int k
  *            + w_lat *(1 - T[r][i]/max_j T[r][j])
  * with C and T as in rb_instances; a zero maximum makes its ratio 0. The state
  * is read, not modified. fp32 arithmetic.
- *   q_hat, l_hat [B][M] fp32; prompt_len [B] int32 (input tokens l_r >= 1);
+ *   q_hat [B][M] fp32 (qualities in [0, 1]), l_hat [B][M] fp32 (predicted
+ *   lengths, not negative; NaN: the request has no prediction for the model,
+ *   whose instances then score NaN and are never assigned it); prompt_len [B]
+ *   int32 (input tokens l_r >= 1);
  *   inst: host struct of device arrays of length I; score0 [B][I] fp32 (output).
  * Errors: RB_ERR_NULL, RB_ERR_DIMS (B < 0, M < 1, M > RB_MAX_M, I < 1,
  * I > RB_MAX_I), RB_ERR_WEIGHTS, RB_ERR_HIP. */
@@ -185,7 +192,8 @@ rb_status rb_score(const float *q_hat, const float *l_hat, const int32_t *prompt
  * every instance at the CURRENT state (as rb_score does for one row), pick
  * i* = argmax (the lowest index among exactly equal scores), then
  *   prefill_q[i*] += l_r;  decode_q[i*] += L[r][m(i*)].
- * Rates and prices are unchanged. Runs on one wavefront, fp32.
+ * Rates and prices are unchanged. fp32, on one wavefront for up to 256
+ * instances, else on eight.
  *   assign [B] int32 (output); chosen_score [B] fp32 (output, may be NULL);
  *   decided [B][I] fp32 (output, may be NULL): row r holds the Eq. 1 scores
  *   of request r against every instance at the state it was decided in (the
@@ -331,11 +339,26 @@ rb_status rb_route_batch_ex(const void *queries, const void *bank, const float *
  * nothing in it has to start cleared: calls that overlap in time on one GPU
  * (on different streams, or from different host threads without ordering)
  * race on it and give undefined results; calls ordered on one stream are
- * safe. The workspace these sizes need is rb_workspace_size's; sizes needing
- * more than RB_SCRATCH_BYTES (for instance more than 64 requests of 768-d
- * bf16 rows through the tile scan, whose worst-case candidate overflow area
- * grows with the batch) are refused with RB_ERR_SCRATCH before anything is
- * enqueued. Errors: those of rb_route_batch (RB_ERR_WORKSPACE aside), plus
+ * safe.
+ *
+ * Which sizes are taken: rb_workspace_size is no measure of it, because the
+ * maxima of a scan are cut to what the array has left, the bank going by in
+ * parts if need be (256 requests over 1,000,000 x 768 ask for 73 MB and are
+ * taken). Refused with RB_ERR_SCRATCH, before anything is enqueued, are sizes
+ * whose neighbour lists, predictions and one super tile's maxima do not fit,
+ * and those whose floor of workspace does not (what scans with candidate lists
+ * needed; it is kept so that the same sizes are taken). That is, with one
+ * workgroup per compute unit but at most one per 16 bank rows and request tile,
+ *   49,152 * g - 12,288 bytes a workgroup, g = 1, 2, 4, 8, 16 groups of 16
+ *   requests as the batch has (fewer if k and that many do not fit LDS), or
+ *   780,288 bytes for more than 256 bf16 requests, a multiple of 64 elements
+ *   from 128 on and k of at most 10,
+ * and the lists; only the lists for bf16 rows of 384, 512, 768 or 1,024
+ * elements with at most 512, 256, 256 or 128 requests (of 64 or fewer over at
+ * least 2,048 rows per compute unit). So up to 64 requests are taken over any
+ * bank, 65 to 128 that are not of that kind over about 2,700 rows.
+ *
+ * Errors: those of rb_route_batch (RB_ERR_WORKSPACE aside), plus
  * RB_ERR_SCRATCH, and RB_ERR_HIP if the array's address cannot be found. */
 rb_status rb_route_batch_noalloc(const void *queries, const void *bank, const float *bank_norms,
                                  rb_dtype dtype, int B, int N, int d, int k,
@@ -359,8 +382,8 @@ rb_status rb_advance_state(const rb_instances *inst, int I, float dt_seconds, vo
  * RB_FLAG_FROM_LISTS) made from the calling host thread records `begin` (a
  * hipEvent_t) on the call's stream immediately before the bank-scan kernel and
  * `end` immediately after it, so hipEventElapsedTime(begin, end) is that
- * kernel's duration (for a scan in two passes, the span of both scan launches
- * and the bound between them). Pass NULL, NULL to stop. The setting is per
+ * kernel's duration (for a bank in parts, the span of all scan launches and of
+ * the selections between them). Pass NULL, NULL to stop. The setting is per
  * host thread; the events stay owned by the caller. Always returns RB_OK. */
 rb_status rb_profile_scan_events(void *begin, void *end);
 

@@ -84,11 +84,9 @@ KNN_CASES = [
     ("bf16", 33, 3000, 2048, 10),   # largest d
     ("f32", 20, 500, 2048, 5),      # largest d, fp32
     ("bf16", 40, 64, 40, 33),       # fewer rows than chunks can use
-    ("bf16", 256, 150, 512, 10),    # no seed (8 sample groups < k): every pair of the
-                                    # first iteration is a candidate, most past the LDS staging
-    # the seed bound's wave holds each lane's two smallest group minima
-    ("bf16", 100, 700, 768, 20),    # 40 groups: fewer than the wave's lanes
-    ("bf16", 100, 1600, 768, 64),   # 100 groups, one or two per lane, largest k
+    ("bf16", 256, 150, 512, 10),    # ten row tiles: no more than neighbours
+    ("bf16", 100, 700, 768, 20),    # few super tiles beside k
+    ("bf16", 100, 1600, 768, 64),   # the same at the largest k
     # bf16 rows of 384, 512, 768 or 1024 elements take the query-resident
     # scan while the batch fits its registers: (query groups per wave, row
     # halves) of (1, 2) up to 64 requests, (2, 2) up to 128, then (4, 2) for
@@ -99,42 +97,40 @@ KNN_CASES = [
     ("bf16", 200, 9000, 768, 17),
     ("bf16", 70, 20, 768, 10),      # fewer bank rows than one of its 32-row blocks
     ("bf16", 65, 1, 768, 1),        # a single bank row
-    ("bf16", 256, 600, 768, 10),    # a full batch with a 36-group seed
-    ("bf16", 200, 4096, 768, 16),   # 128 seed groups: exactly two per lane of the bound
+    ("bf16", 256, 600, 768, 10),    # a full batch over a small bank
+    ("bf16", 200, 4096, 768, 16),   # one 16-row chunk per compute unit
     ("bf16", 1, 530000, 768, 10),   # a single request: two active waves
     ("bf16", 64, 530000, 768, 64),  # (1, 2), k = 64 (batches of up to 64 take it from
                                     # 2,048 rows per compute unit)
     ("bf16", 90, 60000, 768, 20),   # (2, 2), k = 20
     ("bf16", 40, 530000, 384, 10),  # d = 384, (1, 2)
-    ("bf16", 40, 530000, 384, 64),  # d = 384, (1, 2), k = 64: a two-slot ring
-    ("bf16", 40, 30000, 384, 10),   # the same batch over a small bank: the tile scan
+    ("bf16", 40, 530000, 384, 64),  # d = 384, (1, 2), k = 64
+    ("bf16", 40, 30000, 384, 10),   # the same batch over a small bank: the LDS-resident scan
     ("bf16", 100, 30000, 384, 20),  # d = 384, (2, 2), k = 20
     ("bf16", 256, 50000, 384, 10),  # d = 384, (4, 2)
     ("bf16", 512, 60000, 384, 10),  # d = 384, (4, 1): the wide workload's batch, tiles one
                                     # after the other
-    ("bf16", 300, 20000, 384, 16),  # (4, 1), k = 16: a two-slot ring; a partly filled wave
+    ("bf16", 300, 20000, 384, 16),  # (4, 1), k = 16; a partly filled wave
     ("bf16", 64, 530000, 512, 64),  # d = 512, (1, 2), k = 64
     ("bf16", 128, 40000, 512, 20),  # d = 512, (2, 2)
     ("bf16", 250, 40000, 512, 10),  # d = 512, (2, 1)
     ("bf16", 64, 530000, 1024, 10), # d = 1024, (1, 2)
-    ("bf16", 128, 30000, 1024, 64), # d = 1024, (1, 1), k = 64: half-block stages
+    ("bf16", 128, 30000, 1024, 64), # d = 1024, (1, 1), k = 64
     ("bf16", 100, 40, 1024, 33),    # fewer rows than chunks
     ("bf16", 100, 60000, 1024, 20), # d = 1024, (1, 1), k = 20
-    # batches of more than 128 over a bank of more than 32 x 32,768 rows (where
-    # the seed covers less than 1/32 of it): two passes, the first eighth of
-    # every chunk, then the rest under the k-th smallest entry of the first
-    # pass's lists, each pass leaving its own lists
-    ("bf16", 160, 1101825, 384, 10),  # (4, 2); the last chunk ends inside the first pass
+    # banks of over a million rows: more super tiles of a chunk than wait in LDS
+    ("bf16", 160, 1101825, 384, 10),  # (4, 2); the last chunk shorter
     ("bf16", 300, 1100000, 384, 20),  # (4, 1), tiles one after the other
     ("bf16", 200, 1100000, 768, 10),  # (2, 1)
-    ("bf16", 129, 1100000, 512, 32),  # (2, 1), k = 32: the smallest batch that splits
-    # more than 256 bf16 requests whose rows are whole 64-element lines, k <= 10,
-    # take the GEMM-structured scan: 256 x 256 macro tiles, 32x32x16 MFMAs
-    ("bf16", 257, 3000, 128, 10),   # a second request tile of one request; two stages per tile
+    ("bf16", 129, 1100000, 512, 32),  # (2, 1), k = 32
+    # bf16 batches that the query-resident scan does not hold take the
+    # GEMM-structured scan (256 x 256 macro tiles, 32x32x16 MFMAs), or over at
+    # most 8,192 rows (and 1,024 k) the LDS-resident one
+    ("bf16", 257, 3000, 128, 10),   # a second request tile of one request
     ("bf16", 600, 20000, 384, 10),  # three request tiles, the last partly filled
     ("bf16", 1024, 50000, 1024, 10),# four request tiles: the largebatch shape over a small bank
     ("bf16", 513, 10007, 768, 5),   # ragged bank: the last macro tile of a chunk partly filled
-    ("bf16", 400, 30, 256, 10),     # fewer rows than one macro tile, most chunks empty
+    ("bf16", 400, 30, 256, 10),     # two row tiles
     ("bf16", 300, 100000, 512, 1),  # k = 1
 ]
 
@@ -161,9 +157,9 @@ def test_knn_exact_ties_take_lower_index():
 
 @pytest.mark.parametrize("label,B,N,d,k", [
     ("query-resident scan", 200, 70000, 768, 10),
-    ("query-resident scan, two passes", 200, 1100000, 384, 10),
-    ("seeded tile scan, one tile", 64, 70000, 768, 10),
-    ("seeded tile scan, two tiles", 300, 66000, 256, 16),
+    ("query-resident scan, a long bank", 200, 1100000, 384, 10),
+    ("LDS-resident scan", 64, 70000, 768, 10),
+    ("GEMM-structured scan, 16 neighbours", 300, 66000, 256, 16),
     ("GEMM-structured scan", 300, 66000, 256, 10),
 ])
 def test_knn_exact_ties_across_kth(label, B, N, d, k):

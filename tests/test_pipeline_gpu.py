@@ -48,7 +48,7 @@ def test_knn_predict_overlap_flag_changes_nothing(name, over):
             outs.append((flags, wt, idx.cpu().numpy(), dist.cpu().numpy(), qh.cpu().numpy(),
                          lh.cpu().numpy()))
             # the same lookup in two calls on two streams: the scan half, an
-            # event, the merge half
+            # event, the second half (the label average)
             s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
             ws = rb.workspace(cfg.B, cfg.N, cfg.d, rb._dtype_code(c["bank"]), cfg.k, cfg.M, DEV)
             ev = torch.cuda.Event()
@@ -89,7 +89,7 @@ def test_knn_predict_overlap_flag_changes_nothing(name, over):
 @pytest.mark.parametrize("name,batches,split", [("online", 5, False), ("highload", 4, False),
                                                 ("online", 5, True), ("highload", 4, True)])
 def test_pipelined_schedule_matches_sequential(name, batches, split):
-    """split: the scan half of every lookup on one stream, the merge half with
+    """split: the first half of every lookup on one stream, the second with
     the greedy pass on the other, each batch with its own workspace."""
     cfg = synth.CONFIGS[name]
     say(f"pipeline {name}: B={cfg.B} N={cfg.N}, {batches} carried batches, split={split}")

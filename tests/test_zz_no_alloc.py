@@ -63,8 +63,7 @@ def test_noalloc_matches_route_batch():
         ("smaller fp32 batch", synth.CONFIGS["tiny"]),
         ("query-resident scan", synth.tiny_config(B=200, N=200_000, d=768, dtype="bf16",
                                                  clusters=1024)),
-        # more than 128 requests over more than 32 x 32,768 rows: two passes
-        ("query-resident scan in two passes",
+        ("query-resident scan, a long bank",
          synth.tiny_config(B=160, N=1_100_000, d=384, dtype="bf16", clusters=1024)),
     ]
     for label, cfg in cases:
@@ -80,7 +79,7 @@ def test_noalloc_matches_route_batch():
 def test_noalloc_refuses_sizes_past_its_workspace():
     import paper_2606_17949_amd as rb
     # (a batch of 1024 requests of 384 elements goes to the GEMM-structured
-    # scan, whose per-wave overflow areas alone exceed the static workspace)
+    # scan, whose floor of workspace alone exceeds the static array)
     cfg = synth.tiny_config(B=1024, N=100_000, d=384, dtype="bf16", clusters=256)
     need = rb.rb_workspace_size(cfg.B, cfg.N, cfg.d, rb.RB_BF16, cfg.k, cfg.M)
     say(f"noalloc refusal: B={cfg.B} needs {need / 2**20:.1f} MiB of {rb.RB_SCRATCH_BYTES >> 20}")
