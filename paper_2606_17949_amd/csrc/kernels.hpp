@@ -31,6 +31,7 @@ constexpr int GM_SLOTS = 2;
 constexpr int GM_SLOT_LOADS = 64;
 constexpr int GM_EPS = 16;     // entries of a macro tile
 constexpr int GM_HOLD = 8;     // macro tiles whose maxima wait in LDS
+enum GmOut { GM_ENTRIES, GM_FOLDED, GM_VALUES };   // what goes out beside the super tiles' maxima
 // The LDS-resident scan: up to RES_WAVES waves per workgroup, each with
 // RES_RING k-steps of bank loads in flight; request tiles of up to RES_MAX_NG
 // groups of 16.
@@ -50,7 +51,8 @@ constexpr int SEL_MAX_EPS = 16;            // row tiles per super tile, at most
 constexpr int SEL_MAX_ROW_BYTES = 8192;    // of one embedding (RB_MAX_D fp32)
 constexpr long SEL_WANT_SUP = 16384;       // super tiles per request worth reading one by one
 // bf16 batches of more than SEL_WIDE_B requests over at most this many rows
-// (and 1,024 k) go to the LDS-resident scan, which keeps their values.
+// (and 1,024 k, and 1,024 elements times it) go to the LDS-resident scan, which
+// keeps their values.
 constexpr int KEEP_ROWS = 8192;
 // Bytes of maxima a call's workspace takes at most: a bank that would leave
 // more goes by in parts, each with its own scan and selection.
@@ -80,7 +82,7 @@ struct KnnPlan {
     int nks;            // 64-byte k-steps per row
     int ng;             // LDS-resident scan: groups of 16 requests per tile,
     int wg_waves;       //   waves per workgroup,
-    bool keep_acc;      //   every row's value kept (at off_ent)
+    bool keep_acc;      //   (and GEMM-structured scan) every row's value kept (at off_ent)
     int qw, rs;         // query-resident scan: query groups per wave, row halves; GEMM-structured
                         //   scan: 32-request tiles per wave (qw)
     int n_seg, n_qt, n_chunks, eps, grid;

@@ -216,11 +216,19 @@ size_t keep_limit(int dtype, int N, int d, int k)
     return keep ? MAXIMA_LIMIT : KEEP_LIMIT;
 }
 
+// Whether the GEMM-structured scan keeps every row's value, as far as the
+// workspace may: 4 bytes stored a row and request where the selection would
+// read 32 k d of the bank again for each (computed again / kept: 1,024 x 12,000
+// x 2,048 160 / 96 us, with 32 neighbours 329 / 121, 1,024 x 12,000 x 1,000 85 /
+// 74, 1,024 x 16,000 x 1,024 88 / 87; past the line 1,024 x 16,000 x 640 61 / 77).
+bool gemm_keeps(int N, int d, int k) { return 2L * N <= 3L * k * d; }
+
 // bf16 batches of more than SEL_WIDE_B requests over a small bank, whose
 // selections take longer than the scan if they compute row tiles again.
-bool keeps_small_bank(int B, int N, int k)
+bool keeps_small_bank(int B, int N, int d, int k)
 {
-    return B > SEL_WIDE_B && N <= KEEP_ROWS && (long)N <= 1024L * k;
+    return B > SEL_WIDE_B && N <= KEEP_ROWS && (long)N <= 1024L * k &&
+           (long)N * d <= KEEP_ROWS * 1024L;
 }
 
 // Bytes of the LDS-resident scan's layout over a bank of single row tiles, every
@@ -322,7 +330,7 @@ size_t ordered_bytes(int B, int N, int d, int dtype, int k, int num_cu)
     const size_t b = B > 0 ? B : 1;
     const long rowb = (long)d * (dtype == 1 ? 2 : 4);
     // LDS-resident scan: bf16 batches of at most 64, or over a small bank
-    const size_t b0 = dtype == 1 && b > 64 && !keeps_small_bank(B, N, k) ? 64 : b;
+    const size_t b0 = dtype == 1 && b > 64 && !keeps_small_bank(B, N, d, k) ? 64 : b;
     const size_t eps = res_eps(N), n0 = ((size_t)N + 16 * eps - 1) / (16 * eps);
     const size_t all = b0 * n0 * eps * 64, kl = keep_limit(dtype, N, d, k);
     const size_t keep = all < kl ? all : kl;
@@ -335,7 +343,11 @@ size_t ordered_bytes(int B, int N, int d, int dtype, int k, int num_cu)
     if (dtype == 1 && (b > 32 || (long)N >= (long)GM_ROWS * num_cu)) {
         size_t chunks = (size_t)num_cu, split = 2 * (size_t)((long)N * rowb >> 30) + 2;
         chunks = chunks > split ? chunks : split;
-        chunked = b * ((size_t)N / (RQ_EPS * 16) + chunks + chunks / 16 + 2) * 4 * (1 + RQ_EPS);
+        const size_t n12 = (size_t)N / (RQ_EPS * 16) + chunks + chunks / 16 + 2;
+        chunked = b * n12 * 4 * (1 + RQ_EPS);
+        const size_t values = b * n12 * 4 + b * (((size_t)N + 15) / 16) * 64;
+        if (gemm_keeps(N, d, k) && values > chunked)
+            chunked = values;
     }
     static_assert(RQ_EPS == GM_EPS, "one size of super tile");
     size_t maxima = res > chunked ? res : chunked;
@@ -385,10 +397,9 @@ int plan_knn(int B, int N, int d, int dtype, int k, int num_cu, KnnPlan *p, int 
     // 577 over 700,000 rows, 61 for 64 over 48,001, but 57 for 40 over 32,001).
     // Everything else, all fp32 batches among it, goes to the LDS-resident scan,
     // and so does a large bf16 batch over a small bank, if the workspace can
-    // keep its values (10 neighbours: 2,000 x 3,000 x 768 101 us by the
-    // GEMM-structured scan, 54 so, 600 x 8,000 x 1,024 69 and 42; but 1,024 x
-    // 16,000 x 2,048 168 and 245, and one neighbour, 1,024 x 8,000 x 768, 37 and
-    // 41).
+    // keep its values (10 neighbours: 2,000 x 3,000 x 768 73 us by the
+    // GEMM-structured scan, 54 so, 600 x 8,000 x 1,024 54 and 42; but 1,024 x
+    // 8,000 x 2,048 86 and 135, and one neighbour, 1,024 x 8,000 x 768, 38 and 41).
     const bool rq_rows = B > 64 || (long)N >= (long)RQ_SMALL_B_MIN_ROWS * num_cu;
     if (dtype == 1 && d % (4 * vec) == 0 && rq_rows && rq_shape(p->nks, B, &p->qw, &p->rs)) {
         p->kind = 1;
@@ -396,7 +407,7 @@ int plan_knn(int B, int N, int d, int dtype, int k, int num_cu, KnnPlan *p, int 
         p->lds_bytes =
             rq_layout(p->qw, p->rs, p->nks / rq_spb(p->nks), RQ_SLOTS).bytes;
         plan_chunked(p, num_cu, reserve, limit);
-    } else if (dtype == 1 && !(keeps_small_bank(B, N, k) && res_bytes(B, N, k) <= limit) &&
+    } else if (dtype == 1 && !(keeps_small_bank(B, N, d, k) && res_bytes(B, N, k) <= limit) &&
                (B > 64 || ((B + 15) / 16 > res_groups(p->nks) &&
                            (long)N >= (long)GM_ROWS * num_cu))) {
         p->kind = 2;
@@ -417,8 +428,11 @@ int plan_knn(int B, int N, int d, int dtype, int k, int num_cu, KnnPlan *p, int 
     p->off_sup = off;
     off += align256(b * p->n_sup * 4);
     p->off_ent = off;
-    const size_t keep = align256(b * p->n_sup * p->eps * 16 * 4);
-    p->keep_acc = p->kind == 0 && p->n_seg == 1 && keep <= keep_limit(dtype, N, d, k) && off + keep <= limit;
+    const size_t keep = align256(b * (((size_t)N + 15) / 16) * 64);
+    p->keep_acc = p->kind != 1 && p->n_seg == 1 && off + keep <= limit &&
+                  keep <= (p->kind == 0 ? keep_limit(dtype, N, d, k)
+                           : gemm_keeps(N, d, k) ? MAXIMA_LIMIT
+                                                 : 0);
     off += p->keep_acc ? keep : p->eps > 1 ? align256(b * p->n_sup * entries_of(*p) * 4) : 0;
     p->bytes = off;
     return 0;

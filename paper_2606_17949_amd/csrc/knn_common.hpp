@@ -31,7 +31,7 @@ struct ScanArgs {
     int eps;
     long rows_per_chunk, sup_per_chunk;   // (LDS-resident scan: one chunk of all rows)
     Maxima m;
-    float *acc;           // [n_sup * eps][B][16] every row's <q, x> - |x|^2/2, or null
+    float *acc;           // [row tiles][B][16] every row's <q, x> - |x|^2/2, or null
 };
 
 // The selection from those maxima.

@@ -40,8 +40,9 @@ __device__ __forceinline__ f32x16 mfma32(const i32x4 &a, const i32x4 &b, const f
 // barrier. After a macro tile's last stage each wave takes, per request, the
 // maxima of its accumulators (a lane's 16 rows of a 32 x 32 tile are one
 // entry, a macro tile's 16 entries one super tile) into LDS; they go out after
-// the next barrier, 64 bytes per request.
-template <int TPQ, bool FOLDED>
+// the next barrier, 64 bytes per request. With OUT = GM_VALUES the accumulators
+// themselves go out in place of the entries.
+template <int TPQ, int OUT>
 __global__ __launch_bounds__(GM_WAVES * WAVE, 1) void gemm_scan_kernel(const ScanArgs A)
 {
     constexpr int QRY = 64 * TPQ;                 // requests of a tile
@@ -241,8 +242,10 @@ __global__ __launch_bounds__(GM_WAVES * WAVE, 1) void gemm_scan_kernel(const Sca
             m = fmaxf(m, dpp<0x4e>(m));   // quad_perm [2,3,0,1]
             if (part == 0)
                 sst[q * GM_HOLD + rt % GM_HOLD] = m;
-            put_entries<FOLDED>(make_rsrc(ent + 16L * i * A.m.ent_q, 0x7fffffffu), q < nq,
-                                (uint32_t)((lane >> 2) * A.m.ent_q), lane, v);
+            if constexpr (OUT != GM_VALUES)
+                put_entries<OUT == GM_FOLDED>(make_rsrc(ent + 16L * i * A.m.ent_q, 0x7fffffffu),
+                                              q < nq, (uint32_t)((lane >> 2) * A.m.ent_q), lane,
+                                              v);
         }
         if (rt % GM_HOLD == GM_HOLD - 1)
             put_sup(rt + 1 - GM_HOLD, rt + 1);
@@ -307,7 +310,7 @@ __global__ __launch_bounds__(GM_WAVES * WAVE, 1) void gemm_scan_kernel(const Sca
         // slot z & 1 are done; after the barrier the same holds for every
         // wave, so the slot takes stage z + 2
         __builtin_amdgcn_sched_barrier(0);
-        if (flushed)
+        if (flushed && OUT != GM_VALUES)
             wait_vmcnt<GPW>();
         else
             wait_vmcnt<0>();
@@ -337,6 +340,22 @@ __global__ __launch_bounds__(GM_WAVES * WAVE, 1) void gemm_scan_kernel(const Sca
                 for (int r = 1; r < 16; ++r)
                     m = fmaxf(m, v[r]);
                 stg[(2 * (2 * wr + i) + hl) * PITCH + 32 * TPQ * wq + 32 * u + (lane & 31)] = m;
+                if constexpr (OUT == GM_VALUES) {
+                    // every row's value: four rows of a request at a time, the
+                    // row tiles' requests side by side (a row tile past the
+                    // chunk is the next chunk's)
+                    const int q = 32 * TPQ * wq + 32 * u + (lane & 31);
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const int r0 = rt * GM_ROWS + 64 * wr + 32 * i + 8 * g;   // (of the chunk)
+                        float *const at =
+                            A.acc + (((cbeg + r0) >> 4) * A.B + q0) * 16 + (g & 1) * 8;
+                        store16_nt(make_rsrc(at, 0x7fffffffu),
+                                   q < nq && r0 < nrows ? (uint32_t)(q * 16 + hl * 4) * 4u
+                                                        : OFF_NONE,
+                                   f32x4{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]});
+                    }
+                }
                 __builtin_amdgcn_sched_barrier(0);
             });
         });

@@ -314,8 +314,10 @@ __global__ __launch_bounds__(NT, 1024 / NT) void select_kernel(const SelectArgs 
         if (A.acc) {
             for (int i = r0 + tid; i < r1; i += NT) {
                 const int per = A.eps * 16, j = i / per;
-                const long row = (long)S.sup[j] * per + (i - j * per);
-                const float v = row < A.rows
+                const long si = S.sup[j], ch = si / A.sup_per_chunk;
+                const long in_ch = (si - ch * A.sup_per_chunk) * per + (i - j * per);
+                const long row = ch * A.rows_per_chunk + in_ch;
+                const float v = row < A.rows && in_ch < A.rows_per_chunk
                                     ? A.acc[((size_t)(row >> 4) * A.B + b) * 16 + (row & 15)]
                                     : __builtin_nanf("");
                 const uint32_t key = key_of(v);

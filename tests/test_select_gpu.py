@@ -227,6 +227,11 @@ def test_bank_in_parts_gemm(B, N, k):
     (257, 8_193, 640, 8),       # ... and one row more
     (700, 1_025, 768, 1),       # one neighbour, one row past what it keeps
     (300, 2_000, 768, 64),
+    (400, 8_192, 1_032, 10),    # too long for that: the GEMM-structured scan, values kept
+    (129, 15_360, 1_024, 10),   # values kept over the longest bank of these rows
+    (129, 15_361, 1_024, 10),   # ... and one row more
+    (70, 777, 640, 64),         # 128 requests a tile, values kept, chunks of 16 rows
+    (1_025, 40_011, 1_000, 33), # chunks of several macro tiles, the last one short
     (64, 70_001, 1_536, 10),    # a small batch too long for LDS as one tile
     (33, 65_536, 2_048, 10),    # ... at the fewest requests and rows
     (33, 65_535, 2_048, 10),    # ... and one row below
