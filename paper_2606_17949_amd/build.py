@@ -1,8 +1,8 @@
 """Build the gfx950 routing library ``librouteb.so`` in-tree with hipcc.
 
-Each source is compiled to an object in parallel (the bank-scan
-instantiations are split over four units, which dominate the compile time),
-then the objects are linked into the shared library.
+Each source is compiled to an object in parallel (the bank scans'
+instantiations, split over units of their own, dominate the compile time), then
+the objects are linked into the shared library.
 """
 from __future__ import annotations
 
