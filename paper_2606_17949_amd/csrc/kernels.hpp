@@ -55,14 +55,16 @@ constexpr long SEL_WANT_SUP = 16384;       // super tiles per request worth read
 // keeps their values.
 constexpr int KEEP_ROWS = 8192;
 // Bytes of maxima a call's workspace takes at most: a bank that would leave
-// more goes by in parts, each with its own scan and selection.
+// more goes by with folded entries, then in parts, each with its own scan and
+// selection.
 constexpr size_t MAXIMA_LIMIT = (size_t)1 << 30;
 // Row tiles of one entry where the bank would otherwise go by in parts: the
 // selection then computes up to FOLD times the row tiles again, and the maxima
 // take 20 bytes for 68.
 constexpr int FOLD = 4;
 
-// Bytes of single values a scan keeps at most: then the selection takes 10 us
+// Bytes of single values a scan keeps at most where storing them is not known
+// to cost less than computing some again: then the selection takes 10 us
 // for 19 (it computes no row tile again), while 26 MB of them made a scan of
 // 64 x 100,000 take 55 us for 44.
 constexpr size_t KEEP_LIMIT = (size_t)8 << 20;

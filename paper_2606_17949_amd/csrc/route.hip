@@ -179,11 +179,12 @@ __global__ __launch_bounds__(LPT_THREADS) void lpt_order_kernel(const float *__r
 // the pick itself is taken off it: while step t's maximum is reduced, every
 // lane works out step t+1's latency both as the state stands and as it would
 // be had it been picked, and the former's maximum. A pick only adds to its
-// instance's queues, so the maximum of step t+1 is the larger of that maximum
-// and the picked lane's second latency: one lane read instead of a second
-// reduction. (ns a step with both reductions in the chain, and now: 231 / 150 on
-// 13 instances, 268 / 175 on 64, 330 / 267 on 128, 495 / 402 on 256.) The pick's latency and Tmax are captured, one step per lane,
-// and every 64 steps the wave writes the picks and computes their Eq. 1 scores
+// instance's queues (lengths are not negative), so the maximum of step t+1 is
+// the larger of that maximum and the picked lane's second latency: one lane
+// read instead of a second reduction. (ns a step with both reductions in the
+// chain, and now: 231 / 138 on 13 instances, 268 / 165 on 64, 330 / 260 on 128,
+// 495 / 398 on 256; the loop is bound by instruction issue, about 2 ns each.)
+// The pick's latency and Tmax are captured, one step per lane, and every 64 steps the wave writes the picks and computes their Eq. 1 scores
 // (with the division, exactly as the dense score kernel does) in one vector
 // pass. A request without candidates gets -1 and changes no state.
 constexpr int ASSIGN_THREADS = 1024;
@@ -481,8 +482,8 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void assign_kernel(
 // the group after the next is made, a row of it (one request) per wave, cut
 // into GR pieces so that the producers meet every step's barrier too. Their
 // global loads run a group ahead (and the request's index two), so no barrier
-// waits for one. (512 instances: 767 ns a step on one wave, 510 so; 1,000: 1,392
-// and 950. Four waves of two slots: 607. The longest piece of a row sets the
+// waits for one. (512 instances: 767 ns a step on one wave, 500 so; 1,000: 1,392
+// and 938. Four waves of two slots: 607. The longest piece of a row sets the
 // step: with all loads in the first piece 526, with a row's reciprocal taken
 // once and an exact-remainder step per ratio 579.)
 constexpr int WIDE_PRODUCERS = 8;
@@ -875,7 +876,7 @@ hipError_t launch_assign(const float *q_hat, const float *l_hat, const int32_t *
             RB_ASSIGN((assign_wide_kernel<CW, SL, false>), (CW + WIDE_PRODUCERS) * WAVE, lds);   \
     } while (0)
     // one wave walks up to four slots of 64 instances faster than several
-    // exchange theirs (256 instances: 402 against 523 ns a step; 512: 800
+    // exchange theirs (256 instances: 398 against 523 ns a step; 512: 800
     // against 526)
     if (I <= 16)
         RB_NARROW(1, 16);

@@ -1,7 +1,8 @@
 // The bank scan of the exact k-nearest-neighbour search (RouteBalance Sec. 4.2:
 // the KNN lookup of Alg. 1) for large batches, where the distance pass is a
 // dense contraction bound by the matrix cores: bf16 rows of any length, batches
-// that the query-resident scan cannot hold.
+// that the query-resident scan cannot hold (and small batches of rows too long
+// for the LDS-resident one).
 #pragma once
 
 #include "knn_common.hpp"

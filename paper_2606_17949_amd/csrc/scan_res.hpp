@@ -1,7 +1,7 @@
 // The bank scan of the exact k-nearest-neighbour search (RouteBalance Sec. 4.2:
 // the KNN lookup of Alg. 1) for request tiles that stay in LDS: fp32 banks,
-// and bf16 batches of at most 64 requests over rows or banks the
-// query-resident scan does not take.
+// bf16 batches of at most 64 requests over rows or banks the query-resident
+// scan does not take, and large bf16 batches over small banks.
 #pragma once
 
 #include "knn_common.hpp"
@@ -19,10 +19,10 @@ namespace {
 // across tile ends, and no wave waits for another after the request tile has
 // landed. A row tile leaves one value per request, the largest
 // <q, x> - |x|^2/2 of its 16 rows; eps consecutive tiles (a super tile, all
-// one wave's) one more; a small scan keeps every row's value too, which spares
-// the selection from computing any again. There is no bound, no list and no candidate test: the
-// selection takes the k best super tiles and recomputes the few row tiles
-// that matter.
+// one wave's) one more; some scans keep every row's value too, which spares the
+// selection from computing any again. There is no bound, no list and no
+// candidate test: the selection takes the k best super tiles and recomputes
+// the few row tiles that matter.
 template <int DT, int NG>
 __global__ __launch_bounds__(RES_WAVES * WAVE, 1) void res_scan_kernel(const ScanArgs A)
 {
