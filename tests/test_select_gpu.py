@@ -235,6 +235,9 @@ def test_bank_in_parts_gemm(B, N, k):
     (64, 70_001, 1_536, 10),    # a small batch too long for LDS as one tile
     (33, 65_536, 2_048, 10),    # ... at the fewest requests and rows
     (33, 65_535, 2_048, 10),    # ... and one row below
+    (1_151, 11_013, 384, 64),   # fewer super tiles than neighbours: many rounds of rows
+    (1_025, 700, 136, 64),      # ... one round
+    (1_030, 1_100, 1_000, 40),  # ... a short second one
 ])
 def test_bf16_scans_are_exact(B, N, d, k):
     q, bank = draw(B, N, d, "bf16", -1, 1, 6)
