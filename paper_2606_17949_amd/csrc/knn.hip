@@ -207,8 +207,8 @@ int res_eps(int N)
 // selection computes k row tiles again for every request by itself, a
 // sixteenth of each MFMA's columns used: fp32 batches keep them, as far as the
 // workspace may, where that is more work than a sixteenth of the scan's
-// (2,022 x 2,312 x 512, 64 neighbours: 547 us computed again, 127 kept; 1,000 x
-// 48,000 x 384, 10 neighbours: 365 and 341). bf16 scans, sixteen times as fast,
+// (2,022 x 2,312 x 512, 64 neighbours: 529 us computed again, 102 kept; 1,000 x
+// 48,000 x 384, 10 neighbours: 354 and 332). bf16 scans, sixteen times as fast,
 // lose more to the stores over all but small banks.
 size_t keep_limit(int dtype, int N, int d, int k)
 {

@@ -526,8 +526,8 @@ hipError_t launch_select(int dtype, const SelectArgs &a, hipStream_t s)
     // more requests go in workgroups of 8, two to a unit, and past those in
     // workgroups of 4, so that one's chain of accesses and barriers runs beside
     // the others' (whole lookups, in workgroups of 8 and 4: 2,000 requests over
-    // 3,381 x 96 64 / 43 us, 600 over 3,381 x 96 33 / 25, 1,024 over 30,000 x 768,
-    // 32 neighbours, 176 / 165; but 300 over 16,000 x 2,048 100 / 103)
+    // 3,381 x 96 62 / 38 us, 600 over 3,381 x 96 30 / 21, 1,024 over 30,000 x 768,
+    // 32 neighbours, 159 / 137; but 300 over 16,000 x 2,048 100 / 103)
 #define RB_SELECT(NT)                                                                            \
     do {                                                                                         \
         if (dtype == 1)                                                                          \
